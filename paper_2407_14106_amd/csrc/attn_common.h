@@ -7,45 +7,53 @@
 
 namespace gt {
 
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
+// exp2 as the hardware gives it (v_exp_f32: results below 2^-126 become 0).
+__device__ __forceinline__ float ex2(float x) { return __builtin_amdgcn_exp2f(x); }
+
 // Lane layout of the edge kernels: each (node, head) is owned by L = D / F
-// consecutive lanes, each holding F consecutive features (32 bytes of bf16, 64
-// of fp32), which keeps the per-lane register footprint small enough for
-// several resident wavefronts per SIMD to overlap their gathers.
+// consecutive lanes, each holding F features (32 bytes; 64 of fp32 where the
+// node's features would not fit one wavefront otherwise), which keeps the
+// per-lane register footprint small enough for several resident wavefronts
+// per SIMD to overlap their gathers.  A bf16 lane's features are consecutive.
+// An fp32 lane's come in 16-byte pieces dealt round-robin over the L lanes: a
+// run of 64 bytes a lane has each of its four loads touch every cache line of
+// a row (gathering 512-byte rows of a clustered graph: 14.2 TB/s in runs of 64
+// bytes, 19.9 TB/s dealt; with 32 bytes a lane 20.3 and 20.7 TB/s, and the column
+// pass measured 4% slower dealt, so bf16 keeps its runs).
 template <typename T, int D, int H>
 struct EdgeCfg {
-    static constexpr int F = 16;                        // features per lane
+    static constexpr int F = sizeof(T) == 4 && H * D / 8 <= kWave ? 8 : 16;  // features per lane
     static constexpr int L = D / F;                     // lanes per (node, head)
     static constexpr int G = H * L;                     // lanes per node
     static constexpr int NPW = kWave / G;               // nodes per wavefront
-    static_assert(D % F == 0 && G <= kWave && kWave % G == 0, "unsupported (d, H)");
+    static constexpr int RUN = sizeof(T) == 4 ? 4 : F;  // consecutive features of a lane
+    static constexpr int STR = L * RUN;                 // features between a lane's runs
+    static_assert(D % F == 0 && F % RUN == 0 && G <= kWave && kWave % G == 0, "unsupported (d, H)");
+    // The head's feature held as value i of lane `part`.
+    __device__ __forceinline__ static int feat(int part, int i) { return (i / RUN) * STR + part * RUN + i % RUN; }
 };
 
-// F features of one row slice, stored packed as loaded.
-template <typename T, int F>
+// F features of one row slice, stored packed as loaded: a run of 16 (bf16), or
+// runs of 4 features STR apart (fp32).
+template <typename T, int F, int STR>
 struct Slice;
 
-template <int F>
-struct Slice<uint16_t, F> {
+template <int F, int STR>
+struct Slice<uint16_t, F, STR> {
     uint32_t w[F / 2];
     __device__ __forceinline__ void load(const uint16_t* p) {
-        const uint4* q = reinterpret_cast<const uint4*>(p);
 #pragma unroll
         for (int i = 0; i < F / 8; ++i) {
-            uint4 v = q[i];
+            const uint4 v = *reinterpret_cast<const uint4*>(p + 8 * i);
             w[4 * i + 0] = v.x;
             w[4 * i + 1] = v.y;
             w[4 * i + 2] = v.z;
             w[4 * i + 3] = v.w;
         }
-    }
-    __device__ __forceinline__ void zero() {
-#pragma unroll
-        for (int i = 0; i < F / 2; ++i) w[i] = 0;
     }
     __device__ __forceinline__ float f(int i) const { return (i & 1) ? bf16hi(w[i >> 1]) : bf16lo(w[i >> 1]); }
     __device__ __forceinline__ float dot(const Slice& o) const {
@@ -72,23 +80,18 @@ struct Slice<uint16_t, F> {
     }
 };
 
-template <int F>
-struct Slice<float, F> {
+template <int F, int STR>
+struct Slice<float, F, STR> {
     float w[F];
     __device__ __forceinline__ void load(const float* p) {
-        const float4* q = reinterpret_cast<const float4*>(p);
 #pragma unroll
         for (int i = 0; i < F / 4; ++i) {
-            float4 v = q[i];
+            const float4 v = *reinterpret_cast<const float4*>(p + i * STR);
             w[4 * i + 0] = v.x;
             w[4 * i + 1] = v.y;
             w[4 * i + 2] = v.z;
             w[4 * i + 3] = v.w;
         }
-    }
-    __device__ __forceinline__ void zero() {
-#pragma unroll
-        for (int i = 0; i < F; ++i) w[i] = 0.f;
     }
     __device__ __forceinline__ float f(int i) const { return w[i]; }
     __device__ __forceinline__ float dot(const Slice& o) const {
@@ -102,19 +105,14 @@ struct Slice<float, F> {
     }
 };
 
-// acc[i] += p * x[i]
-template <typename T, int F>
-__device__ __forceinline__ void axpy(float (&acc)[F], float p, const Slice<T, F>& x) {
-#pragma unroll
-    for (int i = 0; i < F; ++i) acc[i] = fmaf(p, x.f(i), acc[i]);
-}
+template <typename T, int D, int H>
+using SliceOf = Slice<T, EdgeCfg<T, D, H>::F, EdgeCfg<T, D, H>::STR>;
 
-// Store F fp32 values, times scale, as T (bf16: round to nearest even).
-template <typename T, int F>
+// Store a lane's F fp32 values, times scale, as T (bf16: round to nearest
+// even), laid out like Slice.
+template <typename T, int F, int STR>
 __device__ __forceinline__ void store_slice(T* p, const float (&v)[F], float scale) {
     if constexpr (sizeof(T) == 2) {
-        static_assert(F % 8 == 0, "bf16 slices are stored 16 bytes at a time");
-        uint4* q = reinterpret_cast<uint4*>(p);
 #pragma unroll
         for (int i = 0; i < F / 8; ++i) {
             uint4 o;
@@ -122,26 +120,29 @@ __device__ __forceinline__ void store_slice(T* p, const float (&v)[F], float sca
             o.y = pack_bf16x2(v[8 * i + 2] * scale, v[8 * i + 3] * scale);
             o.z = pack_bf16x2(v[8 * i + 4] * scale, v[8 * i + 5] * scale);
             o.w = pack_bf16x2(v[8 * i + 6] * scale, v[8 * i + 7] * scale);
-            q[i] = o;
+            *reinterpret_cast<uint4*>(p + 8 * i) = o;
         }
     } else {
-        static_assert(F % 4 == 0, "fp32 slices are stored 16 bytes at a time");
-        float4* q = reinterpret_cast<float4*>(p);
 #pragma unroll
         for (int i = 0; i < F / 4; ++i)
-            q[i] = make_float4(v[4 * i] * scale, v[4 * i + 1] * scale, v[4 * i + 2] * scale, v[4 * i + 3] * scale);
+            *reinterpret_cast<float4*>(p + i * STR) =
+                make_float4(v[4 * i] * scale, v[4 * i + 1] * scale, v[4 * i + 2] * scale, v[4 * i + 3] * scale);
     }
 }
 
-// Sum over the L lanes that share one (node, head).  Groups of 2 or 4 lanes sit
-// inside one DPP quad, so the exchanges are quad permutes (xor 1, xor 2) that
-// stay off the LDS; every lane of a group is active whenever one is.
+// Sum over the L lanes (2, 4 or 8) that share one (node, head): DPP exchanges
+// inside a quad (xor 1, xor 2), then the mirrored lane of the other quad; every
+// lane of a group is active whenever one is.
+template <int Ctrl>
+__device__ __forceinline__ float dpp_f32(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), Ctrl, 0xF, 0xF, true));
+}
 template <int L>
 __device__ __forceinline__ float group_sum(float x) {
-    if constexpr (L >= 2) x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xB1, 0xF, 0xF, false));
-    if constexpr (L >= 4) x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x4E, 0xF, 0xF, false));
-#pragma unroll
-    for (int o = 4; o < L; o <<= 1) x += __shfl_xor(x, o, kWave);
+    static_assert(L == 2 || L == 4 || L == 8, "lanes per (node, head)");
+    x += dpp_f32<0xB1>(x);                           // quad_perm 1,0,3,2
+    if constexpr (L >= 4) x += dpp_f32<0x4E>(x);     // quad_perm 2,3,0,1
+    if constexpr (L >= 8) x += dpp_f32<0x141>(x);    // row_half_mirror
     return x;
 }
 

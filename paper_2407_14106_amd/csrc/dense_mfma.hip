@@ -51,7 +51,6 @@ template <bool B>
 struct Flag {
     static constexpr bool value = B;
 };
-__device__ __forceinline__ float ex2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 __device__ __forceinline__ f32x16_t zero16() {
     f32x16_t z;

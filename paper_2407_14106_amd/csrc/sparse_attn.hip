@@ -3,17 +3,15 @@
 // points that also run the dense-tile kernels (tile_attn.hip).
 //
 // Edge kernels ("rows" and "cols"): a wavefront serves 64 / (H * d/F) nodes at
-// once, each (node, head) owned by d/F lanes that hold F consecutive features
-// (64 bytes) of it.  The node's own vectors stay in registers while the lanes
-// walk its edge list two edges at a time, gathering the neighbours' 64-byte
-// slices; every gathered row is read as whole 64-byte pieces by neighbouring
-// lanes.  Scores use the paper's scaled dot product in the exp2 domain; the
-// forward keeps an online max / sum per (node, head), so nothing per edge is
-// ever written to memory.
+// once, each (node, head) owned by d/F lanes that hold F features (32 bytes of
+// bf16) of it.  The node's own vectors stay in registers while the lanes walk
+// its edge list, gathering the neighbours' slices.  Scores use the paper's
+// scaled dot product in the exp2 domain; the forward keeps an online max / sum
+// per (node, head), so nothing per edge is ever written to memory.
 //
 // Nodes with more than GT_LONG_ROW remainder edges are left to the "long"
-// kernels: one workgroup per node, its edges dealt round-robin over the
-// workgroup's lane groups and the partial results merged in LDS.
+// kernels: one workgroup per chunk of a node's edges, each lane group walking
+// a run of them and the partial results merged in LDS.
 //
 // The backward never uses atomics: dQ is gathered per row over the CSR, dK and
 // dV per column over the remainder's transpose.
@@ -27,6 +25,25 @@ namespace {
 constexpr int kThreads = 256;
 constexpr float kNegInf = -__builtin_huge_valf();
 
+// The passes are bound by the rate of the row gathers through L2 and L1: over
+// 1M nodes of 8 x 32 bf16 features and 31 edges a node of a clustered graph the
+// gathers alone take 1.51 ms, with each node's own row read and a result row
+// written 1.76 ms (100K nodes of 8 x 64, 17 edges: 0.150 and 0.206).  The forward takes two
+// edges at a time with nothing in flight meanwhile, at 6 wavefronts per SIMD:
+// 1.88 ms (0.225), no slower than with rows in flight at 4 (1.87; with pairs in
+// flight 2.0, the registers spill).  The row pass holds 4 wavefronts, so it keeps
+// the rows of the next kAheadRows edges in flight while one is used: 1.90 ms
+// (0.251) against 2.42 (0.32) with none and 2.10 (0.285) when every quad waited for
+// its ids.  The column pass takes two edges at a time with none in flight:
+// 2.14 ms (0.304); with 2 in flight 2.22, its row statistics take the registers.
+constexpr int kAheadRows = 2;
+template <typename T, int D, int H>
+constexpr int kLaneBytes = EdgeCfg<T, D, H>::F * int(sizeof(T));
+// Wavefronts per SIMD the row pass is compiled for (3 where a lane holds 64
+// bytes of a row; the backward with a bias takes one less).
+template <typename T, int D, int H>
+constexpr int kEdgeWaves = kLaneBytes<T, D, H> > 32 ? 3 : 4;
+
 template <typename T, int D, int H>
 struct Lanes {
     using C = EdgeCfg<T, D, H>;
@@ -36,7 +53,7 @@ struct Lanes {
         h = (t / C::L) % H;
         part = t % C::L;
     }
-    __device__ __forceinline__ int64_t off(int64_t node) const { return (node * H + h) * D + part * C::F; }
+    __device__ __forceinline__ int64_t off(int64_t node) const { return (node * H + h) * D + part * C::RUN; }
 };
 
 // Per-edge additive bias (the graph encoding added to the scaled product,
@@ -70,10 +87,14 @@ struct Acc {
     }
 };
 
+// A running maximum starts at a finite value below every finite score, so
+// that a missing edge (score -inf) weighs exp2(-inf - m) = 0 with no test.
+constexpr float kMinRef = -3.0e38f;
+
 // Online-softmax state of one (node, head) slice.
 template <int F>
 struct Online {
-    float m = kNegInf;  // running max, log2 domain
+    float m = kMinRef;  // running max, log2 domain
     float l = 0.f;      // running sum of exp2(s - m)
     float acc[F];       // running sum of exp2(s - m) * v
     __device__ __forceinline__ Online() {
@@ -82,21 +103,26 @@ struct Online {
     }
 };
 
+// A lane's F fp32 values of a [n, H, D] array.
+template <int F, int RUN, int STR>
+__device__ __forceinline__ void load_f32_slice(float (&dst)[F], const float* src) {
+#pragma unroll
+    for (int i = 0; i < F; i += 4) {
+        const float4 v = *reinterpret_cast<const float4*>(src + (i / RUN) * STR + i % RUN);
+        dst[i] = v.x;
+        dst[i + 1] = v.y;
+        dst[i + 2] = v.z;
+        dst[i + 3] = v.w;
+    }
+}
+
 template <typename T, int D, int H>
 __device__ __forceinline__ void load_fwd_partial(Online<EdgeCfg<T, D, H>::F>& st, const TilePartials& tp, int64_t node,
                                                  int h, int64_t off) {
-    constexpr int F = EdgeCfg<T, D, H>::F;
-    st.m = tp.m[node * H + h];
+    using C = EdgeCfg<T, D, H>;
+    st.m = fmaxf(tp.m[node * H + h], kMinRef);
     st.l = tp.l[node * H + h];
-    const float4* a = reinterpret_cast<const float4*>(tp.acc + off);
-#pragma unroll
-    for (int i = 0; i < F / 4; ++i) {
-        float4 v = a[i];
-        st.acc[4 * i] = v.x;
-        st.acc[4 * i + 1] = v.y;
-        st.acc[4 * i + 2] = v.z;
-        st.acc[4 * i + 3] = v.w;
-    }
+    load_f32_slice<C::F, C::RUN, C::STR>(st.acc, tp.acc + off);
 }
 
 // The running max is a lazy reference: it moves only when a score exceeds it
@@ -104,99 +130,183 @@ __device__ __forceinline__ void load_fwd_partial(Online<EdgeCfg<T, D, H>::F>& st
 // rarely; weights stay below 2^8 and the result is unchanged.
 constexpr float kRescale = 8.f;
 
-// Weight p as the bf16 pairs (p, 0) and (0, p) for Slice::axpy_w.
-__device__ __forceinline__ void weight_pairs(float p, uint32_t& lo, uint32_t& hi) {
-    lo = uint32_t(f32_to_bf16(p));
-    hi = lo << 16;
-}
+// One partner row of each of two arrays, as gathered.
+template <typename T, int D, int H>
+struct Rows {
+    SliceOf<T, D, H> a, b;  // bf16: 16 registers
+    __device__ __forceinline__ void load(const T* __restrict__ A, const T* __restrict__ B, int64_t off) {
+        a.load(A + off);
+        b.load(B + off);
+    }
+};
 
-// One block of two edges for the forward state.  j0/j1 are always valid
-// node ids (callers substitute a valid id for missing edges); ok0/ok1 say
-// which of the two are edges.
-template <typename T, int D, int H, bool kBias = false>
-__device__ __forceinline__ void fwd_step(Online<EdgeCfg<T, D, H>::F>& st, const Slice<T, EdgeCfg<T, D, H>::F>& q,
+// Two edges for the forward state.  j0/j1 are always valid node ids (callers
+// substitute a valid id for missing edges); ok0/ok1 say which of the two are
+// edges.
+template <typename T, int D, int H>
+__device__ __forceinline__ void fwd_step(Online<EdgeCfg<T, D, H>::F>& st, const SliceOf<T, D, H>& q,
                                          const T* __restrict__ K, const T* __restrict__ V, int64_t j0, int64_t j1,
                                          bool ok0, bool ok1, const Lanes<T, D, H>& ln, float sl2, float b0 = 0.f,
                                          float b1 = 0.f) {
     using C = EdgeCfg<T, D, H>;
-    Slice<T, C::F> k0, k1, v0, v1;
-    k0.load(K + ln.off(j0));
-    k1.load(K + ln.off(j1));
-    v0.load(V + ln.off(j0));
-    v1.load(V + ln.off(j1));
-    float s0 = ok0 ? group_sum<C::L>(q.dot(k0)) * sl2 : kNegInf;
-    float s1 = ok1 ? group_sum<C::L>(q.dot(k1)) * sl2 : kNegInf;
-    if constexpr (kBias) {
-        s0 += b0;
-        s1 += b1;
-    }
+    Rows<T, D, H> x0, x1;
+    x0.load(K, V, ln.off(j0));
+    x1.load(K, V, ln.off(j1));
+    float s0 = fmaf(group_sum<C::L>(q.dot(x0.a)), sl2, b0);
+    float s1 = fmaf(group_sum<C::L>(q.dot(x1.a)), sl2, b1);
+    s0 = ok0 ? s0 : kNegInf;
+    s1 = ok1 ? s1 : kNegInf;
     const float mb = fmaxf(s0, s1);
-    if (mb > st.m + kRescale) {
-        const float alpha = st.m == kNegInf ? 0.f : exp2f(st.m - mb);
+    const bool grow = mb > st.m + kRescale;
+    if (__builtin_amdgcn_ballot_w64(grow)) {  // wave-uniform; alpha is exactly 1 where the maximum stays
+        const float mn = grow ? mb : st.m;
+        const float alpha = ex2(st.m - mn);
         st.l *= alpha;
 #pragma unroll
         for (int i = 0; i < C::F; ++i) st.acc[i] *= alpha;
-        st.m = mb;
+        st.m = mn;
     }
-    const float p0 = ok0 ? exp2f(s0 - st.m) : 0.f;
-    const float p1 = ok1 ? exp2f(s1 - st.m) : 0.f;
+    const float p0 = ex2(s0 - st.m);
+    const float p1 = ex2(s1 - st.m);
     st.l += p0 + p1;
     if constexpr (sizeof(T) == 2) {
-        uint32_t a0, b0, a1, b1;
-        weight_pairs(p0, a0, b0);
-        weight_pairs(p1, a1, b1);
-        v0.axpy_w(st.acc, a0, b0);
-        v1.axpy_w(st.acc, a1, b1);
+        const uint32_t w = pack_bf16x2(p0, p1);
+        x0.b.axpy_w(st.acc, w & 0xFFFFu, w << 16);
+        x1.b.axpy_w(st.acc, w >> 16, w & 0xFFFF0000u);
     } else {
 #pragma unroll
-        for (int i = 0; i < C::F; ++i) st.acc[i] = fmaf(p1, v1.f(i), fmaf(p0, v0.f(i), st.acc[i]));
+        for (int i = 0; i < C::F; ++i) st.acc[i] = fmaf(p1, x1.b.f(i), fmaf(p0, x0.b.f(i), st.acc[i]));
     }
 }
 
-// Neighbour ids of edges t .. t+3 of a row whose list is cl[a, a + deg) in an
-// array of `len` entries: one 16-byte load where the array allows it (ids past
-// the row are read but replaced).  Missing edges get a valid id: the row's
-// edge t if it exists, else `self`.
-__device__ __forceinline__ int4 edge_quad(const int32_t* __restrict__ cl, int64_t len, int64_t a, int deg, int t,
-                                          int32_t self) {
-    if (deg <= t) return make_int4(self, self, self, self);
-    int4 v;
-    if (a + t + 4 <= len) {
-        v = *reinterpret_cast<const int4*>(cl + a + t);
-    } else {
-        const int last = deg - 1;
-        v.x = cl[a + t];
-        v.y = cl[a + (t + 1 < last ? t + 1 : last)];
-        v.z = cl[a + (t + 2 < last ? t + 2 : last)];
-        v.w = cl[a + (t + 3 < last ? t + 3 : last)];
+// The ids of a row's edges, held by the row's G lanes: lane l of the group has
+// edges t0 + l (and t0 + G + l where a group is small) of the chunk at t0, one
+// coalesced load for the whole chunk, so a chunk can be loaded while the one
+// before it is worked on.  An edge's id then goes to the group by a lane
+// permute.  (Loading each quad's ids in every lane made each wavefront wait
+// for the ids before it could issue the quad's gathers.)
+template <int G>
+struct EdgeIds {
+    static constexpr int R = G < 16 ? 2 : 1;
+    static constexpr int kChunk = R * G;
+    int v[R];
+    // Past the row's end the last edge is repeated; `first` may be read there.
+    __device__ __forceinline__ void load(const int32_t* __restrict__ first, int last, int t0, int l) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int e = t0 + r * G + l;
+            v[r] = first[e < last ? e : last];
+        }
     }
-    if (t + 1 >= deg) v.y = v.x;
-    if (t + 2 >= deg) v.z = v.x;
-    if (t + 3 >= deg) v.w = v.x;
-    return v;
-}
-
-// Walk a row's edges four at a time up to the wavefront maximum dmax, the ids
-// of the next four fetched before the current four are used; step(j0, j1, t,
-// ok0, ok1) takes two edges, the row's edges t and t + 1.
-template <class Step>
-__device__ __forceinline__ void walk_edges(const int32_t* __restrict__ cl, int64_t len, int64_t a, int deg, int dmax,
-                                           int32_t self, Step step) {
-    int4 cur = edge_quad(cl, len, a, deg, 0, self), nxt = cur;
-    for (int t = 0; t < dmax; t += 4) {
-        if (t + 4 < dmax) nxt = edge_quad(cl, len, a, deg, t + 4, self);
-        step(cur.x, cur.y, t, t < deg, t + 1 < deg);
-        if (t + 2 < dmax) step(cur.z, cur.w, t + 2, t + 2 < deg, t + 3 < deg);
-        cur = nxt;
+    // Value of chunk entry u (u0 + a lane's own du, u0 uniform and u0 + du on one side of G).
+    __device__ __forceinline__ int pick(int u0, int du, int group4) const {
+        int x = v[0];
+        if constexpr (R == 2) x = u0 < G ? v[0] : v[1];
+        return __builtin_amdgcn_ds_bpermute(group4 + 4 * ((u0 + du) & (G - 1)), x);
     }
-}
+    __device__ __forceinline__ int pick(int u, int group4) const {
+        if constexpr (G == kWave) return __builtin_amdgcn_readlane(v[0], u);
+        return pick(u, 0, group4);
+    }
+};
 
-// The value of lane 0 of each L-lane group, in every lane of the group.
-template <int L>
-__device__ __forceinline__ float group_bcast0(float x) {
-    if constexpr (L == 2) return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xA0, 0xF, 0xF, false));
-    if constexpr (L == 4) return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x00, 0xF, 0xF, false));
-    return x;
+// The edge list of one lane group: `deg` ids at cl + a.  Every lane of the
+// wavefront takes part in a walk, dmax (uniform) edges long: past its own end
+// a group repeats its last edge, and a group without edges reads some row of
+// the list, whose weight is 0 but whose values may be infinite, so the caller
+// resets what such a group has summed.
+template <int G>
+struct EdgeList {
+    const int32_t* first;
+    int deg, last, l, group4;
+    __device__ __forceinline__ EdgeList(const int32_t* __restrict__ cl, int64_t len, int64_t a, int deg_, int lane)
+        : deg(deg_), last(deg_ > 0 ? deg_ - 1 : 0), l(lane & (G - 1)), group4(4 * (lane & ~(G - 1))) {
+        if (deg_ <= 0) a = a < len ? a : len - 1;  // read only where dmax > 0, so len > 0
+        first = cl + a;
+    }
+    __device__ __forceinline__ void ids(EdgeIds<G>& x, int t0) const { x.load(first, last, t0, l); }
+    // One edge at a time, the rows of the next DEP edges in flight while one is
+    // used: load(x, j) issues an edge's gathers, use(x, t, k) takes edge t (an edge
+    // if t < deg; k, a constant, is t mod DEP).
+    template <int DEP, class X, class Load, class Use>
+    __device__ __forceinline__ void walk_ahead(int dmax, Load load, Use use) const {
+        using Ids = EdgeIds<G>;
+        constexpr int CH = Ids::kChunk;
+        static_assert(CH % DEP == 0, "a block of edges does not straddle chunks");
+        if (dmax <= 0) return;
+        Ids cur, nxt;
+        ids(cur, 0);
+        X x[DEP];
+        int id[DEP];
+        auto pick = [&](const Ids& from, int u) {
+#pragma unroll
+            for (int k = 0; k < DEP; ++k) id[k] = from.pick(u + k, group4);
+        };
+        pick(cur, 0);
+#pragma unroll
+        for (int k = 0; k < DEP; ++k) load(x[k], id[k]);
+        for (int t0 = 0; t0 < dmax; t0 += CH) {
+            nxt = cur;
+            if (t0 + CH < dmax) ids(nxt, t0 + CH);
+            const int m = dmax - t0 < CH ? dmax - t0 : CH;
+            int u = 0;
+            // whole blocks followed by whole blocks: no branch around a load, so that
+            // the compiler counts the loads in flight instead of waiting for them all;
+            // the next ids by a branch, so that only a chunk's last block waits for nxt
+            for (; u < m && t0 + u + 2 * DEP <= dmax; u += DEP) {
+                if (u + DEP < CH) pick(cur, u + DEP);
+                else pick(nxt, 0);
+#pragma unroll
+                for (int k = 0; k < DEP; ++k) {
+                    use(x[k], t0 + u + k, k);
+                    load(x[k], id[k]);
+                }
+            }
+            for (; u < m; u += DEP) {
+                if (t0 + u + DEP < dmax) {
+                    if (u + DEP < CH) pick(cur, u + DEP);
+                    else pick(nxt, 0);
+                }
+#pragma unroll
+                for (int k = 0; k < DEP; ++k) {
+                    const int t = t0 + u + k;
+                    if (t < dmax) {
+                        use(x[k], t, k);
+                        if (t + DEP < dmax) load(x[k], id[k]);
+                    }
+                }
+            }
+            cur = nxt;
+        }
+    }
+    // Two edges at a time: step(j0, j1, t, ok0, ok1) takes edges t and t + 1.
+    template <class Step>
+    __device__ __forceinline__ void walk(int dmax, Step step) const {
+        using Ids = EdgeIds<G>;
+        if (dmax <= 0) return;
+        Ids cur, nxt;
+        ids(cur, 0);
+        for (int t0 = 0; t0 < dmax; t0 += Ids::kChunk) {
+            nxt = cur;
+            if (t0 + Ids::kChunk < dmax) ids(nxt, t0 + Ids::kChunk);
+            const int m = dmax - t0 < Ids::kChunk ? dmax - t0 : Ids::kChunk;
+            for (int u = 0; u < m; u += 2) {
+                const int t = t0 + u;
+                step(cur.pick(u, group4), cur.pick(u + 1, group4), t, t < deg, t + 1 < deg);
+            }
+            cur = nxt;
+        }
+    }
+};
+
+// The value of lane k (0 or 1) of each L-lane group, in every lane of the group.
+template <int L, int k>
+__device__ __forceinline__ float group_bcast(float x) {
+    const int v = __float_as_int(x);
+    if constexpr (L == 2) return __int_as_float(__builtin_amdgcn_mov_dpp(v, k ? 0xF5 : 0xA0, 0xF, 0xF, true));
+    const int q = __builtin_amdgcn_mov_dpp(v, k ? 0x55 : 0x00, 0xF, 0xF, true);  // in each quad
+    if constexpr (L == 4) return __int_as_float(q);
+    return __int_as_float(__builtin_amdgcn_update_dpp(q, q, 0x114, 0xF, 0xA, false));  // row_shr:4 into the odd quads
 }
 
 // The value of the first lane of each G-lane group (one node's lanes), in
@@ -211,39 +321,30 @@ __device__ __forceinline__ int group_first(int x) {
     else return __shfl(x, lane_id() & ~(G - 1), kWave);
 }
 
-// Bias (exp2 domain) of a row's edges t and t + 1 at CSR offset a; 0 where
-// the edge is missing.  One lane of each (node, head) group reads it.
+// Bias (exp2 domain) of a row's edge t at remainder offset a; 0 where the edge
+// is missing.  One lane of each (node, head) group reads it.
 template <typename LN>
-__device__ __forceinline__ void bias_pair(const EdgeBias& eb, int64_t a, int t, bool ok0, bool ok1, int H,
-                                          const LN& ln, float& b0, float& b1) {
-    float x0 = 0.f, x1 = 0.f;
-    if (ln.part == 0) {
-        x0 = ok0 ? eb.at(a + t, H, ln.h) : 0.f;
-        x1 = ok1 ? eb.at(a + t + 1, H, ln.h) : 0.f;
-    }
-    b0 = group_bcast0<LN::C::L>(x0);
-    b1 = group_bcast0<LN::C::L>(x1);
+__device__ __forceinline__ float bias_one(const EdgeBias& eb, int64_t a, int t, bool ok, int H, const LN& ln) {
+    float x = 0.f;
+    if (ln.part == 0 && ok) x = eb.at(a + t, H, ln.h);
+    return group_bcast<LN::C::L, 0>(x);
 }
 
 // The bias of four edges of each of a wavefront's nodes moves through LDS, so
-// that a lane reads one vector (the floats 4H/G g .. of the quad's block, all
-// within one edge) instead of one float per edge: kPer floats per lane, each
-// group's block of 4H floats at `s`.  The wavefront alone uses its block, and
-// its LDS operations take effect in program order, so no barrier is needed.
+// that a lane reads one vector (kPer floats, all of one edge, of the quad's
+// block of 4 H floats) instead of one float per edge, each group's block at
+// `s`.  The wavefront alone uses its block, and its LDS operations take effect
+// in program order, so no barrier is needed.
 template <typename T, int D, int H>
 struct BiasStage {
     using C = EdgeCfg<T, D, H>;
-    static constexpr int kPer = 4 * H / C::G;
-    static constexpr bool kOn = kPer >= 1 && kPer <= H;
+    static constexpr int kPer = 4 * H >= C::G ? 4 * H / C::G : 1;
+    static constexpr bool kOn = kPer <= H;
     static constexpr int kWaveFloats = C::NPW * 4 * H;
-};
-
-// Input-CSR positions of a row's (column's) edges t .. t + 3: base + off[u].
-struct Quad {
-    int64_t base;
-    int4 off;
-    __device__ __forceinline__ int64_t at(int u) const {
-        return base + (u == 0 ? off.x : u == 1 ? off.y : u == 2 ? off.z : off.w);
+    // First float of this lane's share; lanes from 4 H on have none.
+    __device__ __forceinline__ static int at(const Lanes<T, D, H>& ln) { return (ln.h * C::L + ln.part) * kPer; }
+    __device__ __forceinline__ static bool mine(const Lanes<T, D, H>& ln) {
+        return kPer * C::G <= 4 * H || at(ln) < 4 * H;
     }
 };
 
@@ -271,24 +372,24 @@ __device__ __forceinline__ void lds_order() {
     asm volatile("" ::: "memory");
 }
 
-// This lane's share of the quad's bias block (kPer floats of one edge); 0 past deg.
-template <typename T, int D, int H, int P>
-__device__ __forceinline__ void bias_share(float (&v)[P], const float* __restrict__ b, const Quad& q, int t, int deg,
-                                           const Lanes<T, D, H>& ln) {
-    const int e0 = (ln.h * EdgeCfg<T, D, H>::L + ln.part) * P, u = e0 / H;
+// This lane's share of the quad's bias block (kPer floats of the edge at input position pos); 0 where !on.
+template <int P>
+__device__ __forceinline__ void bias_share(float (&v)[P], const float* __restrict__ b, int64_t pos, int H, int e0,
+                                           bool on) {
 #pragma unroll
     for (int k = 0; k < P; ++k) v[k] = 0.f;
-    if (t + u < deg) ld_floats<P>(v, b + q.at(u) * H + e0 % H);
+    if (on) ld_floats<P>(v, b + pos * H + e0 % H);
 }
 
 // The shares of a group through LDS: the bias (exp2 domain) of the quad's four
 // edges for this lane's head.
 template <typename T, int D, int H, int P>
 __device__ __forceinline__ float4 bias_swap(const float (&v)[P], const Lanes<T, D, H>& ln, float* s) {
-    const int e0 = (ln.h * EdgeCfg<T, D, H>::L + ln.part) * P;
+    using BS = BiasStage<T, D, H>;
     lds_order();
+    if (BS::mine(ln))
 #pragma unroll
-    for (int k = 0; k < P; ++k) s[e0 + k] = v[k];
+        for (int k = 0; k < P; ++k) s[BS::at(ln) + k] = v[k];
     lds_order();
     float4 x = make_float4(s[ln.h], s[H + ln.h], s[2 * H + ln.h], s[3 * H + ln.h]);
     lds_order();
@@ -296,11 +397,12 @@ __device__ __forceinline__ float4 bias_swap(const float (&v)[P], const Lanes<T, 
     return x;
 }
 
-// Write ds (this lane's head, edges t .. t + 3) to db at the quad's positions.
+// Write ds (this lane's head, a quad's four edges) to db: this lane's share, at the input position pos.
 template <typename T, int D, int H>
-__device__ __forceinline__ void db_quad(float* __restrict__ db, const Quad& q, int t, int deg, float4 ds,
+__device__ __forceinline__ void db_quad(float* __restrict__ db, int64_t pos, bool on, float4 ds,
                                         const Lanes<T, D, H>& ln, float* s) {
-    constexpr int P = BiasStage<T, D, H>::kPer;
+    using BS = BiasStage<T, D, H>;
+    constexpr int P = BS::kPer;
     lds_order();
     if (ln.part == 0) {
         s[ln.h] = ds.x;
@@ -309,85 +411,74 @@ __device__ __forceinline__ void db_quad(float* __restrict__ db, const Quad& q, i
         s[3 * H + ln.h] = ds.w;
     }
     lds_order();
-    const int e0 = (ln.h * EdgeCfg<T, D, H>::L + ln.part) * P, u = e0 / H;
-    float v[P];
-#pragma unroll
-    for (int k = 0; k < P; ++k) v[k] = s[e0 + k];
-    lds_order();
-    if (t + u < deg) st_floats<P>(db + q.at(u) * H + e0 % H, v);
-}
-
-// Positions of a row's remainder edges t .. t + 3 (through sp_pos when the
-// plan has one) or of a column's in-edges (through csc_pos); past deg they
-// repeat a valid position.
-__device__ __forceinline__ Quad row_quad(const EdgeBias& eb, int64_t len, int64_t a, int deg, int t) {
-    Quad q;
-    if (eb.sp_pos) {
-        q.base = 0;
-        q.off = edge_quad(eb.sp_pos, len, a, deg, t, 0);
-    } else {
-        q.base = a;
-        q.off = make_int4(t, t + 1 < deg ? t + 1 : t, t + 2 < deg ? t + 2 : t, t + 3 < deg ? t + 3 : t);
-    }
-    return q;
-}
-__device__ __forceinline__ Quad col_quad(const EdgeBias& eb, int64_t len, int64_t a, int deg, int t) {
-    Quad q;
-    q.base = 0;
-    q.off = edge_quad(eb.csc_pos, len, a, deg, t, 0);
-    return q;
-}
-
-// walk_edges for a bias kernel, the bias exchanged in LDS when a quad starts;
-// step(j0, j1, t, ok0, ok1, b0, b1) takes two edges, after(t, q) runs once the
-// quad's steps are done (the column pass writes dB there).  kAhead: positions
-// two quads ahead and bias shares one quad ahead, their loads in flight across
-// a quad's steps (the forward and the column pass; the row pass, with more
-// live registers, reads each quad's when it starts).
-template <typename T, int D, int H, bool kAhead, class QuadOf, class Step, class After>
-__device__ __forceinline__ void walk_edges_bias(const int32_t* __restrict__ cl, int64_t len, int64_t a, int deg,
-                                                int dmax, int32_t self, const float* __restrict__ b,
-                                                const Lanes<T, D, H>& ln, float* s, QuadOf quad_of, Step step,
-                                                After after) {
-    constexpr int P = BiasStage<T, D, H>::kPer;
-    int4 cur = edge_quad(cl, len, a, deg, 0, self), nxt = cur;
-    if constexpr (kAhead) {
-        Quad q0 = quad_of(0);
-        Quad q1 = 4 < dmax ? quad_of(4) : q0;
+    if (on) {
         float v[P];
-        bias_share<T, D, H, P>(v, b, q0, 0, deg, ln);
-        for (int t = 0; t < dmax; t += 4) {
+#pragma unroll
+        for (int k = 0; k < P; ++k) v[k] = s[BS::at(ln) + k];
+        st_floats<P>(db + pos * H + BS::at(ln) % H, v);
+    }
+    lds_order();
+}
+
+// EdgeList::walk for a bias kernel, four edges at a time, the bias exchanged
+// in LDS when a quad starts; step(j0, j1, t, ok0, ok1, b0, b1) takes two edges,
+// after(pos, on) runs once the quad's steps are done (the column pass writes
+// dB there).  A lane needs the input position of one edge of each quad, the
+// one its share belongs to: from the position list `pos` (read in chunks like
+// the ids), or the list position a + t itself where pos is null.  Its share of
+// the next quad is loaded a quad ahead.
+template <typename T, int D, int H, class Step, class After>
+__device__ __forceinline__ void walk_bias(const EdgeList<EdgeCfg<T, D, H>::G>& el, const int32_t* __restrict__ pos,
+                                          int64_t a, int dmax, const float* __restrict__ b, const Lanes<T, D, H>& ln,
+                                          float* s, Step step, After after) {
+    using BS = BiasStage<T, D, H>;
+    using Ids = EdgeIds<EdgeCfg<T, D, H>::G>;
+    constexpr int P = BS::kPer, CH = Ids::kChunk;
+    static_assert(CH % 4 == 0, "quads do not cross chunks");
+    if (dmax <= 0) return;
+    const int e0 = BS::at(ln), u = (e0 / H) & 3;
+    const bool mine = BS::mine(ln);
+    const int32_t* pfirst = pos ? pos + (el.deg > 0 ? a : 0) : nullptr;
+    Ids cur, nxt, pcur, pnxt;
+    el.ids(cur, 0);
+    pcur = cur;
+    if (pos) pcur.load(pfirst, el.last, 0, el.l);
+    nxt = cur;
+    pnxt = pcur;
+    // this lane's edge of the quad at chunk offset c (uniform) of the chunk at t0
+    auto at = [&](const Ids& p, int t0, int c) -> int64_t { return pos ? int64_t(p.pick(c, u, el.group4)) : a + t0 + c + u; };
+    float v[P];
+    int64_t p0 = at(pcur, 0, 0);
+    bias_share<P>(v, b, p0, H, e0, mine && u < el.deg);
+    for (int t0 = 0; t0 < dmax; t0 += CH) {
+        const bool more = t0 + CH < dmax;
+        if (more) {
+            el.ids(nxt, t0 + CH);
+            if (pos) pnxt.load(pfirst, el.last, t0 + CH, el.l);
+        }
+        const int m = dmax - t0 < CH ? dmax - t0 : CH;
+        for (int c = 0; c < m; c += 4) {
+            const int t = t0 + c;
             float vn[P];
 #pragma unroll
             for (int k = 0; k < P; ++k) vn[k] = 0.f;
-            Quad q2 = q1;
-            if (t + 4 < dmax) {
-                nxt = edge_quad(cl, len, a, deg, t + 4, self);
-                bias_share<T, D, H, P>(vn, b, q1, t + 4, deg, ln);
+            int64_t p1 = p0;
+            if (t + 4 < dmax) {  // the next quad's share
+                p1 = c + 4 < CH ? at(pcur, t0, c + 4) : at(pnxt, t0 + CH, 0);
+                bias_share<P>(vn, b, p1, H, e0, mine && t + 4 + u < el.deg);
             }
-            if (t + 8 < dmax) q2 = quad_of(t + 8);
             const float4 x = bias_swap<T, D, H, P>(v, ln, s);
-            step(cur.x, cur.y, t, t < deg, t + 1 < deg, x.x, x.y);
-            if (t + 2 < dmax) step(cur.z, cur.w, t + 2, t + 2 < deg, t + 3 < deg, x.z, x.w);
-            after(t, q0);
-            cur = nxt;
-            q0 = q1;
-            q1 = q2;
+            step(cur.pick(c, el.group4), cur.pick(c + 1, el.group4), t, t < el.deg, t + 1 < el.deg, x.x, x.y);
+            if (t + 2 < dmax)
+                step(cur.pick(c + 2, el.group4), cur.pick(c + 3, el.group4), t + 2, t + 2 < el.deg, t + 3 < el.deg,
+                     x.z, x.w);
+            after(p0, mine && t + u < el.deg);
+            p0 = p1;
 #pragma unroll
             for (int k = 0; k < P; ++k) v[k] = vn[k];
         }
-    } else {
-        for (int t = 0; t < dmax; t += 4) {
-            if (t + 4 < dmax) nxt = edge_quad(cl, len, a, deg, t + 4, self);
-            const Quad q = quad_of(t);
-            float v[P];
-            bias_share<T, D, H, P>(v, b, q, t, deg, ln);
-            const float4 x = bias_swap<T, D, H, P>(v, ln, s);
-            step(cur.x, cur.y, t, t < deg, t + 1 < deg, x.x, x.y);
-            if (t + 2 < dmax) step(cur.z, cur.w, t + 2, t + 2 < deg, t + 3 < deg, x.z, x.w);
-            after(t, q);
-            cur = nxt;
-        }
+        cur = nxt;
+        pcur = pnxt;
     }
 }
 
@@ -413,33 +504,41 @@ __global__ __launch_bounds__(kThreads) void k_fwd_rows(int64_t n, const int64_t*
         const int64_t dg = rp[i + 1] - a;
         deg = dg > GT_LONG_ROW ? -1 : int(dg);
     }
-    const int dmax = wave_max(deg);
+    const int dmax = uniform(wave_max(deg));
     const int64_t off = ln.off(self);
-    Slice<T, C::F> q;
+    SliceOf<T, D, H> q;
     q.load(Q + off);
     Online<C::F> st;
-    if (live && deg >= 0 && tp.has_row(i)) load_fwd_partial<T, D, H>(st, tp, i, ln.h, off);
+    auto begin = [&] {
+        st = Online<C::F>();
+        if (live && deg >= 0 && tp.has_row(i)) load_fwd_partial<T, D, H>(st, tp, i, ln.h, off);
+    };
+    begin();
+    const EdgeList<C::G> el(cl, len, a, deg, lane_id());
     using BS = BiasStage<T, D, H>;
     if constexpr (kBias && BS::kOn) {
         __shared__ float s_bias[kThreads / kWave][BS::kWaveFloats];
         float* sb = s_bias[threadIdx.x / kWave] + ln.slot * 4 * H;
-        walk_edges_bias<T, D, H, true>(
-            cl, len, a, deg, dmax, int32_t(self), eb.b, ln, sb,
-            [&](int t) { return row_quad(eb, len, a, deg, t); },
+        walk_bias<T, D, H>(
+            el, eb.sp_pos, a, dmax, eb.b, ln, sb,
             [&](int64_t j0, int64_t j1, int, bool ok0, bool ok1, float b0, float b1) {
-                fwd_step<T, D, H, true>(st, q, K, V, j0, j1, ok0, ok1, ln, sl2, b0, b1);
+                fwd_step<T, D, H>(st, q, K, V, j0, j1, ok0, ok1, ln, sl2, b0, b1);
             },
-            [](int, const Quad&) {});
+            [](int64_t, bool) {});
     } else {
-        walk_edges(cl, len, a, deg, dmax, int32_t(self), [&](int64_t j0, int64_t j1, int t, bool ok0, bool ok1) {
+        el.walk(dmax, [&](int64_t j0, int64_t j1, int t, bool ok0, bool ok1) {
             float b0 = 0.f, b1 = 0.f;
-            if constexpr (kBias) bias_pair(eb, a, t, ok0, ok1, H, ln, b0, b1);
-            fwd_step<T, D, H, kBias>(st, q, K, V, j0, j1, ok0, ok1, ln, sl2, b0, b1);
+            if constexpr (kBias) {
+                b0 = bias_one(eb, a, t, ok0, H, ln);
+                b1 = bias_one(eb, a, t + 1, ok1, H, ln);
+            }
+            fwd_step<T, D, H>(st, q, K, V, j0, j1, ok0, ok1, ln, sl2, b0, b1);
         });
     }
+    if (deg <= 0) begin();
     if (live && deg >= 0) {
         const float inv = st.l > 0.f ? 1.f / st.l : 0.f;
-        store_slice<T, C::F>(O + off, st.acc, inv);
+        store_slice<T, C::F, C::STR>(O + off, st.acc, inv);
         if (ln.part == 0) LSE[i * H + ln.h] = st.l > 0.f ? (st.m + __log2f(st.l)) * kLn2 : kNegInf;
     }
 }
@@ -455,65 +554,40 @@ __global__ __launch_bounds__(kThreads) void k_fwd_rows(int64_t n, const int64_t*
 template <int F>
 struct RowSums {
     Acc<F> a, b;
-    float d = 0.f;
+    float d[2] = {0.f, 0.f};  // D over the even and the odd edges
 };
 
-template <typename T, int D, int H, bool kBias = false>
-__device__ __forceinline__ void dq_step(RowSums<EdgeCfg<T, D, H>::F>& rs, const Slice<T, EdgeCfg<T, D, H>::F>& q,
-                                        const Slice<T, EdgeCfg<T, D, H>::F>& g, float lse2, const T* __restrict__ K,
-                                        const T* __restrict__ V, int64_t j0, int64_t j1, bool ok0, bool ok1,
-                                        const Lanes<T, D, H>& ln, float sl2, float b0 = 0.f, float b1 = 0.f) {
+template <typename T, int D, int H>
+__device__ __forceinline__ void dq_step(RowSums<EdgeCfg<T, D, H>::F>& rs, const SliceOf<T, D, H>& q,
+                                        const SliceOf<T, D, H>& g, float lse2, const Rows<T, D, H>& x, bool ok,
+                                        int odd, float sl2, float bias = 0.f) {
     using C = EdgeCfg<T, D, H>;
-    Slice<T, C::F> k0, k1, v0, v1;
-    k0.load(K + ln.off(j0));
-    k1.load(K + ln.off(j1));
-    v0.load(V + ln.off(j0));
-    v1.load(V + ln.off(j1));
-    float s0 = group_sum<C::L>(q.dot(k0)) * sl2;
-    float s1 = group_sum<C::L>(q.dot(k1)) * sl2;
-    if constexpr (kBias) {
-        s0 += b0;
-        s1 += b1;
-    }
-    const float dp0 = group_sum<C::L>(g.dot(v0));
-    const float dp1 = group_sum<C::L>(g.dot(v1));
-    const float p0 = ok0 ? exp2f(s0 - lse2) : 0.f;
-    const float p1 = ok1 ? exp2f(s1 - lse2) : 0.f;
-    const float w0 = p0 * dp0;
-    const float w1 = p1 * dp1;
-    rs.d += w0 + w1;
+    const float s = fmaf(group_sum<C::L>(q.dot(x.a)), sl2, bias);
+    const float dp = group_sum<C::L>(g.dot(x.b));
+    const float e = ex2(s - lse2);
+    const float p = ok ? e : 0.f;
+    const float w = p * dp;
+    rs.d[odd] += w;
 #pragma unroll
     for (int f = 0; f < C::F; ++f) {
-        const float x0 = k0.f(f), x1 = k1.f(f);
-        rs.a.v[f] = fmaf(w1, x1, fmaf(w0, x0, rs.a.v[f]));
-        rs.b.v[f] = fmaf(p1, x1, fmaf(p0, x0, rs.b.v[f]));
-    }
-}
-
-template <int F>
-__device__ __forceinline__ void load_f32_slice(float (&dst)[F], const float* src) {
-    const float4* a = reinterpret_cast<const float4*>(src);
-#pragma unroll
-    for (int i = 0; i < F / 4; ++i) {
-        float4 v = a[i];
-        dst[4 * i] = v.x;
-        dst[4 * i + 1] = v.y;
-        dst[4 * i + 2] = v.z;
-        dst[4 * i + 3] = v.w;
+        const float k = x.a.f(f);
+        rs.a.v[f] = fmaf(w, k, rs.a.v[f]);
+        rs.b.v[f] = fmaf(p, k, rs.b.v[f]);
     }
 }
 
 template <typename T, int D, int H>
 __device__ __forceinline__ void load_row_partial(RowSums<EdgeCfg<T, D, H>::F>& rs, const TilePartials& tp,
                                                  int64_t node, int h, int64_t off) {
-    constexpr int F = EdgeCfg<T, D, H>::F;
-    load_f32_slice<F>(rs.a.v, tp.acc + off);
-    load_f32_slice<F>(rs.b.v, tp.acc2 + off);
-    rs.d = tp.m[node * H + h];
+    using C = EdgeCfg<T, D, H>;
+    load_f32_slice<C::F, C::RUN, C::STR>(rs.a.v, tp.acc + off);
+    load_f32_slice<C::F, C::RUN, C::STR>(rs.b.v, tp.acc2 + off);
+    rs.d[0] = tp.m[node * H + h];
 }
 
 template <typename T, int D, int H, bool kBias>
-__global__ __launch_bounds__(kThreads) void k_bwd_rows(int64_t n, const int64_t* __restrict__ rp,
+__global__ __launch_bounds__(kThreads)
+__attribute__((amdgpu_waves_per_eu(kBias ? kEdgeWaves<T, D, H> - 1 : kEdgeWaves<T, D, H>))) void k_bwd_rows(int64_t n, const int64_t* __restrict__ rp,
                                                        const int32_t* __restrict__ cl, int64_t len,
                                                        const T* __restrict__ Q,
                                                        const T* __restrict__ K, const T* __restrict__ V,
@@ -533,37 +607,50 @@ __global__ __launch_bounds__(kThreads) void k_bwd_rows(int64_t n, const int64_t*
         const int64_t dg = rp[i + 1] - a;
         deg = dg > GT_LONG_ROW ? -1 : int(dg);
     }
-    const int dmax = wave_max(deg);
+    const int dmax = uniform(wave_max(deg));
     const int64_t off = ln.off(self);
-    Slice<T, C::F> q, g;
+    SliceOf<T, D, H> q, g;
     q.load(Q + off);
     g.load(dO + off);
     const float lse2 = LSE[self * H + ln.h] * kLog2e;
     RowSums<C::F> rs;
-    if (live && deg >= 0 && tp.has_row(i)) load_row_partial<T, D, H>(rs, tp, i, ln.h, off);
+    auto begin = [&] {
+        rs = RowSums<C::F>();
+        if (live && deg >= 0 && tp.has_row(i)) load_row_partial<T, D, H>(rs, tp, i, ln.h, off);
+    };
+    begin();
+    const EdgeList<C::G> el(cl, len, a, deg, lane_id());
     using BS = BiasStage<T, D, H>;
     if constexpr (kBias && BS::kOn) {
         __shared__ float s_bias[kThreads / kWave][BS::kWaveFloats];
         float* sb = s_bias[threadIdx.x / kWave] + ln.slot * 4 * H;
-        walk_edges_bias<T, D, H, false>(
-            cl, len, a, deg, dmax, int32_t(self), eb.b, ln, sb,
-            [&](int t) { return row_quad(eb, len, a, deg, t); },
+        walk_bias<T, D, H>(
+            el, eb.sp_pos, a, dmax, eb.b, ln, sb,
             [&](int64_t j0, int64_t j1, int, bool ok0, bool ok1, float b0, float b1) {
-                dq_step<T, D, H, true>(rs, q, g, lse2, K, V, j0, j1, ok0, ok1, ln, sl2, b0, b1);
+                Rows<T, D, H> x0, x1;
+                x0.load(K, V, ln.off(j0));
+                x1.load(K, V, ln.off(j1));
+                dq_step<T, D, H>(rs, q, g, lse2, x0, ok0, 0, sl2, b0);
+                dq_step<T, D, H>(rs, q, g, lse2, x1, ok1, 1, sl2, b1);
             },
-            [](int, const Quad&) {});
+            [](int64_t, bool) {});
     } else {
-        walk_edges(cl, len, a, deg, dmax, int32_t(self), [&](int64_t j0, int64_t j1, int t, bool ok0, bool ok1) {
-            float b0 = 0.f, b1 = 0.f;
-            if constexpr (kBias) bias_pair(eb, a, t, ok0, ok1, H, ln, b0, b1);
-            dq_step<T, D, H, kBias>(rs, q, g, lse2, K, V, j0, j1, ok0, ok1, ln, sl2, b0, b1);
-        });
+        el.template walk_ahead<kAheadRows, Rows<T, D, H>>(
+            dmax, [&](Rows<T, D, H>& x, int64_t jj) { x.load(K, V, ln.off(jj)); },
+            [&](const Rows<T, D, H>& x, int t, int k) {
+                const bool ok = t < el.deg;
+                float b = 0.f;
+                if constexpr (kBias) b = bias_one(eb, a, t, ok, H, ln);
+                dq_step<T, D, H>(rs, q, g, lse2, x, ok, k & 1, sl2, b);
+            });
     }
+    if (deg <= 0) begin();
     if (live && deg >= 0) {
+        const float d = rs.d[0] + rs.d[1];
 #pragma unroll
-        for (int f = 0; f < C::F; ++f) rs.a.v[f] = fmaf(-rs.d, rs.b.v[f], rs.a.v[f]);
-        store_slice<T, C::F>(dQ + off, rs.a.v, scale);
-        if (ln.part == 0) Dv[i * H + ln.h] = rs.d;
+        for (int f = 0; f < C::F; ++f) rs.a.v[f] = fmaf(-d, rs.b.v[f], rs.a.v[f]);
+        store_slice<T, C::F, C::STR>(dQ + off, rs.a.v, scale);
+        if (ln.part == 0) Dv[i * H + ln.h] = d;
     }
 }
 
@@ -572,28 +659,24 @@ __global__ __launch_bounds__(kThreads) void k_bwd_rows(int64_t n, const int64_t*
 // dB = dS written at their CSR positions.
 template <typename T, int D, int H, bool kBias = false>
 __device__ __forceinline__ void dkv_step(Acc<EdgeCfg<T, D, H>::F>& dk, Acc<EdgeCfg<T, D, H>::F>& dv,
-                                         const Slice<T, EdgeCfg<T, D, H>::F>& k,
-                                         const Slice<T, EdgeCfg<T, D, H>::F>& v, const T* __restrict__ Q,
+                                         const SliceOf<T, D, H>& k, const SliceOf<T, D, H>& v,
+                                         const T* __restrict__ Q,
                                          const T* __restrict__ dO, const float2* __restrict__ stat, int64_t i0,
                                          int64_t i1, bool ok0, bool ok1, const Lanes<T, D, H>& ln, float sl2,
                                          const EdgeBias& eb = EdgeBias{}, int64_t c0 = 0, int64_t c1 = 0,
                                          float* staged = nullptr) {
     using C = EdgeCfg<T, D, H>;
-    Slice<T, C::F> q0, q1, g0, g1;
-    q0.load(Q + ln.off(i0));
-    q1.load(Q + ln.off(i1));
-    g0.load(dO + ln.off(i0));
-    g1.load(dO + ln.off(i1));
-    // one lane of each (node, head) group reads the pair; the others take it by DPP
-    float2 st0 = make_float2(0.f, 0.f), st1 = make_float2(0.f, 0.f);
-    if (ln.part == 0) {
-        st0 = stat[i0 * H + ln.h];
-        st1 = stat[i1 * H + ln.h];
-    }
-    const float l0 = group_bcast0<C::L>(st0.x), D0 = group_bcast0<C::L>(st0.y);
-    const float l1 = group_bcast0<C::L>(st1.x), D1 = group_bcast0<C::L>(st1.y);
-    float s0 = group_sum<C::L>(q0.dot(k)) * sl2;
-    float s1 = group_sum<C::L>(q1.dot(k)) * sl2;
+    Rows<T, D, H> r0, r1;
+    r0.load(Q, dO, ln.off(i0));
+    r1.load(Q, dO, ln.off(i1));
+    // lane 0 of each (node, head) group reads the first edge's pair, lane 1 the second's; both go to the group
+    // by DPP (one load with all its lanes of use; two loads of one lane in two each: 2.18 against 2.13 ms at
+    // 1M x 8 x 32, 31 edges a node)
+    const float2 stt = stat[(ln.part & 1 ? i1 : i0) * H + ln.h];
+    const float l0 = group_bcast<C::L, 0>(stt.x), D0 = group_bcast<C::L, 0>(stt.y);
+    const float l1 = group_bcast<C::L, 1>(stt.x), D1 = group_bcast<C::L, 1>(stt.y);
+    float s0 = group_sum<C::L>(r0.a.dot(k)) * sl2;
+    float s1 = group_sum<C::L>(r1.a.dot(k)) * sl2;
     int64_t e0 = 0, e1 = 0;
     if (kBias && staged) {
         // staged: the bias came through LDS (staged[0..1]), dS goes back in staged[2..3]
@@ -608,18 +691,19 @@ __device__ __forceinline__ void dkv_step(Acc<EdgeCfg<T, D, H>::F>& dk, Acc<EdgeC
         }
         e0 = group_first<C::G>(p0);
         e1 = group_first<C::G>(p1);
-        float x0 = 0.f, x1 = 0.f;
+        float y0 = 0.f, y1 = 0.f;
         if (ln.part == 0) {
-            x0 = ok0 ? eb.at_input(e0, H, ln.h) : 0.f;
-            x1 = ok1 ? eb.at_input(e1, H, ln.h) : 0.f;
+            y0 = ok0 ? eb.at_input(e0, H, ln.h) : 0.f;
+            y1 = ok1 ? eb.at_input(e1, H, ln.h) : 0.f;
         }
-        s0 += group_bcast0<C::L>(x0);
-        s1 += group_bcast0<C::L>(x1);
+        s0 += group_bcast<C::L, 0>(y0);
+        s1 += group_bcast<C::L, 0>(y1);
     }
-    const float dp0 = group_sum<C::L>(g0.dot(v));
-    const float dp1 = group_sum<C::L>(g1.dot(v));
-    const float p0 = ok0 ? exp2f(s0 - l0) : 0.f;
-    const float p1 = ok1 ? exp2f(s1 - l1) : 0.f;
+    const float dp0 = group_sum<C::L>(r0.b.dot(v));
+    const float dp1 = group_sum<C::L>(r1.b.dot(v));
+    const float x0 = ex2(s0 - l0), x1 = ex2(s1 - l1);
+    const float p0 = ok0 ? x0 : 0.f;
+    const float p1 = ok1 ? x1 : 0.f;
     const float ds0 = p0 * (dp0 - D0);
     const float ds1 = p1 * (dp1 - D1);
     if (kBias && staged) {
@@ -633,13 +717,14 @@ __device__ __forceinline__ void dkv_step(Acc<EdgeCfg<T, D, H>::F>& dk, Acc<EdgeC
     }
 #pragma unroll
     for (int f = 0; f < C::F; ++f) {
-        dk.v[f] = fmaf(ds1, q1.f(f), fmaf(ds0, q0.f(f), dk.v[f]));
-        dv.v[f] = fmaf(p1, g1.f(f), fmaf(p0, g0.f(f), dv.v[f]));
+        dk.v[f] = fmaf(ds1, r1.a.f(f), fmaf(ds0, r0.a.f(f), dk.v[f]));
+        dv.v[f] = fmaf(p1, r1.b.f(f), fmaf(p0, r0.b.f(f), dv.v[f]));
     }
 }
 
 template <typename T, int D, int H, bool kBias>
-__global__ __launch_bounds__(kThreads) void k_bwd_cols(int64_t n, const int64_t* __restrict__ cp,
+__global__ __launch_bounds__(kThreads)
+__attribute__((amdgpu_waves_per_eu(kBias ? kEdgeWaves<T, D, H> - 1 : 1))) void k_bwd_cols(int64_t n, const int64_t* __restrict__ cp,
                                                        const int32_t* __restrict__ rw, int64_t len,
                                                        const T* __restrict__ Q,
                                                        const T* __restrict__ K, const T* __restrict__ V,
@@ -660,39 +745,44 @@ __global__ __launch_bounds__(kThreads) void k_bwd_cols(int64_t n, const int64_t*
         const int64_t dg = cp[j + 1] - a;
         deg = dg > GT_LONG_ROW ? -1 : int(dg);
     }
-    const int dmax = wave_max(deg);
+    const int dmax = uniform(wave_max(deg));
     const int64_t off = ln.off(self);
-    Slice<T, C::F> k, v;
+    SliceOf<T, D, H> k, v;
     k.load(K + off);
     v.load(V + off);
     Acc<C::F> dk, dv;
-    if (live && deg >= 0 && tpk.has_col(j)) {
-        load_f32_slice<C::F>(dk.v, tpk.acc + off);
-        load_f32_slice<C::F>(dv.v, tpv.acc + off);
-    }
+    auto begin = [&] {
+        dk = dv = Acc<C::F>();
+        if (live && deg >= 0 && tpk.has_col(j)) {
+            load_f32_slice<C::F, C::RUN, C::STR>(dk.v, tpk.acc + off);
+            load_f32_slice<C::F, C::RUN, C::STR>(dv.v, tpv.acc + off);
+        }
+    };
+    begin();
+    const EdgeList<C::G> el(rw, len, a, deg, lane_id());
     using BS = BiasStage<T, D, H>;
     if constexpr (kBias && BS::kOn) {
         __shared__ float s_bias[kThreads / kWave][BS::kWaveFloats];
         float* sb = s_bias[threadIdx.x / kWave] + ln.slot * 4 * H;
         float4 ds = make_float4(0.f, 0.f, 0.f, 0.f);
-        walk_edges_bias<T, D, H, true>(
-            rw, len, a, deg, dmax, int32_t(self), eb.b, ln, sb,
-            [&](int t) { return col_quad(eb, len, a, deg, t); },
+        walk_bias<T, D, H>(
+            el, eb.csc_pos, a, dmax, eb.b, ln, sb,
             [&](int64_t i0, int64_t i1, int t, bool ok0, bool ok1, float b0, float b1) {
                 float x[4] = {b0, b1, 0.f, 0.f};
                 dkv_step<T, D, H, true>(dk, dv, k, v, Q, dO, stat, i0, i1, ok0, ok1, ln, sl2, eb, 0, 0, x);
                 if (t & 2) ds.z = x[2], ds.w = x[3];
                 else ds.x = x[2], ds.y = x[3], ds.z = 0.f, ds.w = 0.f;
             },
-            [&](int t, const Quad& q) { db_quad<T, D, H>(eb.db, q, t, deg, ds, ln, sb); });
+            [&](int64_t pos, bool on) { db_quad<T, D, H>(eb.db, pos, on, ds, ln, sb); });
     } else {
-        walk_edges(rw, len, a, deg, dmax, int32_t(self), [&](int64_t i0, int64_t i1, int t, bool ok0, bool ok1) {
+        el.walk(dmax, [&](int64_t i0, int64_t i1, int t, bool ok0, bool ok1) {
             dkv_step<T, D, H, kBias>(dk, dv, k, v, Q, dO, stat, i0, i1, ok0, ok1, ln, sl2, eb, a + t, a + t + 1);
         });
     }
+    if (deg <= 0) begin();
     if (live && deg >= 0) {
-        store_slice<T, C::F>(dK + off, dk.v, scale);
-        store_slice<T, C::F>(dV + off, dv.v, 1.f);
+        store_slice<T, C::F, C::STR>(dK + off, dk.v, scale);
+        store_slice<T, C::F, C::STR>(dV + off, dv.v, 1.f);
     }
 }
 
@@ -784,26 +874,28 @@ __global__ __launch_bounds__(kThreads) void k_fwd_long(const int32_t* __restrict
     const int deg = int(rp[i + 1] - a);
     const int e1 = e0 + kChunk < deg ? e0 + kChunk : deg;
     const int64_t off = ln.off(i);
-    Slice<T, C::F> q;
+    SliceOf<T, D, H> q;
     q.load(Q + off);
     Online<C::F> st;
-    for (int t = e0 + ln.slot; t < e1; t += 2 * S) {
-        const bool ok1 = t + S < e1;
-        const int64_t j0 = cl[a + t];
-        const int64_t j1 = ok1 ? cl[a + t + S] : j0;
+    // each lane group walks its own run of the chunk's edges
+    const int run = int(cdiv(e1 - e0, S)), g0 = e0 + ln.slot * run;
+    const int gdeg = g0 < e1 ? (g0 + run < e1 ? run : e1 - g0) : 0;
+    const EdgeList<C::G> el(cl, a + deg, a + g0, gdeg, lane_id());
+    el.walk(run, [&](int64_t j0, int64_t j1, int t, bool ok0, bool ok1) {
         float b0 = 0.f, b1 = 0.f;
         if constexpr (kBias) {
-            b0 = eb.at(a + t, H, ln.h);
-            b1 = ok1 ? eb.at(a + t + S, H, ln.h) : 0.f;
+            b0 = bias_one(eb, a + g0, t, ok0, H, ln);
+            b1 = bias_one(eb, a + g0, t + 1, ok1, H, ln);
         }
-        fwd_step<T, D, H, kBias>(st, q, K, V, j0, j1, true, ok1, ln, sl2, b0, b1);
-    }
+        fwd_step<T, D, H>(st, q, K, V, j0, j1, ok0, ok1, ln, sl2, b0, b1);
+    });
+    if (gdeg == 0) st = Online<C::F>();  // no edges: whatever the stand-in row held
     if (ln.part == 0) {
         s_m[ln.slot][ln.h] = st.m;
         s_l[ln.slot][ln.h] = st.l;
     }
 #pragma unroll
-    for (int f = 0; f < C::F; ++f) s_acc[ln.slot][ln.h * D + ln.part * C::F + f] = st.acc[f];
+    for (int f = 0; f < C::F; ++f) s_acc[ln.slot][ln.h * D + C::feat(ln.part, f)] = st.acc[f];
     __syncthreads();
     float* out = part + blockIdx.x * FwdLongF<H, D>;
     for (int idx = threadIdx.x; idx < H * D; idx += kThreads) {
@@ -813,7 +905,7 @@ __global__ __launch_bounds__(kThreads) void k_fwd_long(const int32_t* __restrict
         float lsum = 0.f, o = 0.f;
         if (M != kNegInf) {
             for (int g = 0; g < S; ++g) {
-                const float w = exp2f(s_m[g][h] - M);
+                const float w = ex2(s_m[g][h] - M);
                 lsum += s_l[g][h] * w;
                 o += s_acc[g][idx] * w;
             }
@@ -841,13 +933,13 @@ __global__ __launch_bounds__(kThreads) void k_fwd_long_merge(const int32_t* __re
         float lsum = 0.f, o = 0.f;
         if (M != kNegInf) {
             if (tile) {
-                const float w = exp2f(tp.m[i * H + h] - M);
+                const float w = ex2(tp.m[i * H + h] - M);
                 lsum = tp.l[i * H + h] * w;
                 o = tp.acc[i * H * D + idx] * w;
             }
             for (int64_t c = c0; c < c1; ++c) {
                 const float* pc = part + c * FwdLongF<H, D>;
-                const float w = exp2f(pc[h] - M);
+                const float w = ex2(pc[h] - M);
                 lsum += pc[H + h] * w;
                 o += pc[2 * H + idx] * w;
             }
@@ -883,28 +975,30 @@ __global__ __launch_bounds__(kThreads) void k_bwd_rows_long(const int32_t* __res
     const int deg = int(rp[i + 1] - a);
     const int e1 = e0 + kChunk < deg ? e0 + kChunk : deg;
     const int64_t off = ln.off(i);
-    Slice<T, C::F> q, g;
+    SliceOf<T, D, H> q, g;
     q.load(Q + off);
     g.load(dO + off);
     const float lse2 = LSE[i * H + ln.h] * kLog2e;
     RowSums<C::F> rs;
-    for (int t = e0 + ln.slot; t < e1; t += 2 * S) {
-        const bool ok1 = t + S < e1;
-        const int64_t j0 = cl[a + t];
-        const int64_t j1 = ok1 ? cl[a + t + S] : j0;
-        float b0 = 0.f, b1 = 0.f;
-        if constexpr (kBias) {
-            b0 = eb.at(a + t, H, ln.h);
-            b1 = ok1 ? eb.at(a + t + S, H, ln.h) : 0.f;
-        }
-        dq_step<T, D, H, kBias>(rs, q, g, lse2, K, V, j0, j1, true, ok1, ln, sl2, b0, b1);
-    }
+    // each lane group walks its own run of the chunk's edges
+    const int run = int(cdiv(e1 - e0, S)), g0 = e0 + ln.slot * run;
+    const int gdeg = g0 < e1 ? (g0 + run < e1 ? run : e1 - g0) : 0;
+    const EdgeList<C::G> el(cl, a + deg, a + g0, gdeg, lane_id());
+    el.template walk_ahead<kAheadRows, Rows<T, D, H>>(
+        run, [&](Rows<T, D, H>& x, int64_t jj) { x.load(K, V, ln.off(jj)); },
+        [&](const Rows<T, D, H>& x, int t, int k) {
+            const bool ok = t < el.deg;
+            float b = 0.f;
+            if constexpr (kBias) b = bias_one(eb, a + g0, t, ok, H, ln);
+            dq_step<T, D, H>(rs, q, g, lse2, x, ok, k & 1, sl2, b);
+        });
+    if (gdeg == 0) rs = RowSums<C::F>();  // no edges: whatever the stand-in row held
 #pragma unroll
     for (int f = 0; f < C::F; ++f) {
-        s_a[ln.slot][ln.h * D + ln.part * C::F + f] = rs.a.v[f];
-        s_b[ln.slot][ln.h * D + ln.part * C::F + f] = rs.b.v[f];
+        s_a[ln.slot][ln.h * D + C::feat(ln.part, f)] = rs.a.v[f];
+        s_b[ln.slot][ln.h * D + C::feat(ln.part, f)] = rs.b.v[f];
     }
-    if (ln.part == 0) s_d[ln.slot][ln.h] = rs.d;
+    if (ln.part == 0) s_d[ln.slot][ln.h] = rs.d[0] + rs.d[1];
     __syncthreads();
     float* out = part + blockIdx.x * RowLongF<H, D>;
     for (int idx = threadIdx.x; idx < H * D; idx += kThreads) {
@@ -972,20 +1066,23 @@ __global__ __launch_bounds__(kThreads) void k_bwd_cols_long(const int32_t* __res
     const int deg = int(cp[j + 1] - a);
     const int e1 = e0 + kChunk < deg ? e0 + kChunk : deg;
     const int64_t off = ln.off(j);
-    Slice<T, C::F> k, v;
+    SliceOf<T, D, H> k, v;
     k.load(K + off);
     v.load(V + off);
     Acc<C::F> dk, dv;
-    for (int t = e0 + ln.slot; t < e1; t += 2 * S) {
-        const bool ok1 = t + S < e1;
-        const int64_t i0 = rw[a + t];
-        const int64_t i1 = ok1 ? rw[a + t + S] : i0;
-        dkv_step<T, D, H, kBias>(dk, dv, k, v, Q, dO, stat, i0, i1, true, ok1, ln, sl2, eb, a + t, a + t + S);
-    }
+    // each lane group walks its own run of the chunk's edges
+    const int run = int(cdiv(e1 - e0, S)), g0 = e0 + ln.slot * run;
+    const int gdeg = g0 < e1 ? (g0 + run < e1 ? run : e1 - g0) : 0;
+    const EdgeList<C::G> el(rw, a + deg, a + g0, gdeg, lane_id());
+    el.walk(run, [&](int64_t i0, int64_t i1, int t, bool ok0, bool ok1) {
+        dkv_step<T, D, H, kBias>(dk, dv, k, v, Q, dO, stat, i0, i1, ok0, ok1, ln, sl2, eb, a + g0 + t,
+                                 a + g0 + t + 1);
+    });
+    if (gdeg == 0) dk = dv = Acc<C::F>();  // no edges: whatever the stand-in row held
 #pragma unroll
     for (int f = 0; f < C::F; ++f) {
-        s_k[ln.slot][ln.h * D + ln.part * C::F + f] = dk.v[f];
-        s_v[ln.slot][ln.h * D + ln.part * C::F + f] = dv.v[f];
+        s_k[ln.slot][ln.h * D + C::feat(ln.part, f)] = dk.v[f];
+        s_v[ln.slot][ln.h * D + C::feat(ln.part, f)] = dv.v[f];
     }
     __syncthreads();
     float* out = part + blockIdx.x * ColLongF<H, D>;
@@ -1041,15 +1138,15 @@ __global__ void k_pack_stats(int64_t m, const float* __restrict__ LSE, const flo
 // edge of a row of at most GT_LONG_ROW edges reads its partner's two feature
 // rows, same lanes, same edge walk) with no arithmetic but an XOR, so the rate
 // the gather path allows for a plan can be timed beside the real kernels.
-template <int F>
-__device__ __forceinline__ uint32_t xor_words(const Slice<uint16_t, F>& x) {
+template <int F, int STR>
+__device__ __forceinline__ uint32_t xor_words(const Slice<uint16_t, F, STR>& x) {
     uint32_t r = 0;
 #pragma unroll
     for (int i = 0; i < F / 2; ++i) r ^= x.w[i];
     return r;
 }
-template <int F>
-__device__ __forceinline__ uint32_t xor_words(const Slice<float, F>& x) {
+template <int F, int STR>
+__device__ __forceinline__ uint32_t xor_words(const Slice<float, F, STR>& x) {
     uint32_t r = 0;
 #pragma unroll
     for (int i = 0; i < F; ++i) r ^= __float_as_uint(x.w[i]);
@@ -1076,15 +1173,14 @@ __global__ __launch_bounds__(kThreads) void k_gather_probe(int64_t n, const int6
         const int64_t dg = rp[i + 1] - a;
         deg = dg > GT_LONG_ROW ? -1 : int(dg);
     }
-    const int dmax = wave_max(deg);
+    const int dmax = uniform(wave_max(deg));
     uint32_t acc = 0;
-    walk_edges(cl, len, a, deg, dmax, int32_t(self), [&](int64_t j0, int64_t j1, int, bool, bool) {
-        Slice<T, C::F> a0, a1, b0, b1;
-        a0.load(A + ln.off(j0));
-        a1.load(A + ln.off(j1));
-        b0.load(B + ln.off(j0));
-        b1.load(B + ln.off(j1));
-        acc ^= xor_words(a0) ^ xor_words(a1) ^ xor_words(b0) ^ xor_words(b1);
+    const EdgeList<C::G> el(cl, len, a, deg, lane_id());
+    el.walk(dmax, [&](int64_t j0, int64_t j1, int, bool, bool) {
+        Rows<T, D, H> x0, x1;
+        x0.load(A, B, ln.off(j0));
+        x1.load(A, B, ln.off(j1));
+        acc ^= xor_words(x0.a) ^ xor_words(x1.a) ^ xor_words(x0.b) ^ xor_words(x1.b);
     });
     if (acc == kProbeSinkKey) sink[0] = acc;  // keeps the loads; practically never taken
 }

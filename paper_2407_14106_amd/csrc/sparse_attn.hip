@@ -9,9 +9,8 @@
 // scaled dot product in the exp2 domain; the forward keeps an online max / sum
 // per (node, head), so nothing per edge is ever written to memory.
 //
-// Nodes with more than GT_LONG_ROW remainder edges are left to the "long"
-// kernels: one workgroup per chunk of a node's edges, each lane group walking
-// a run of them and the partial results merged in LDS.
+// Nodes with more than GT_LONG_ROW remainder edges are cut into runs, each
+// walked like a short row in the same launch, and merged afterwards.
 //
 // The backward never uses atomics: dQ is gathered per row over the CSR, dK and
 // dV per column over the remainder's transpose.
@@ -39,10 +38,10 @@ constexpr float kNegInf = -__builtin_huge_valf();
 constexpr int kAheadRows = 2;
 template <typename T, int D, int H>
 constexpr int kLaneBytes = EdgeCfg<T, D, H>::F * int(sizeof(T));
-// Wavefronts per SIMD the row pass is compiled for (3 where a lane holds 64
+// Wavefronts per SIMD the row pass is compiled for (2 where a lane holds 64
 // bytes of a row; the backward with a bias takes one less).
 template <typename T, int D, int H>
-constexpr int kEdgeWaves = kLaneBytes<T, D, H> > 32 ? 3 : 4;
+constexpr int kEdgeWaves = kLaneBytes<T, D, H> > 32 ? 2 : 4;
 
 template <typename T, int D, int H>
 struct Lanes {
@@ -114,6 +113,13 @@ __device__ __forceinline__ void load_f32_slice(float (&dst)[F], const float* src
         dst[i + 2] = v.z;
         dst[i + 3] = v.w;
     }
+}
+
+template <int F, int RUN, int STR>
+__device__ __forceinline__ void store_f32_slice(float* dst, const float (&v)[F]) {
+#pragma unroll
+    for (int i = 0; i < F; i += 4)
+        *reinterpret_cast<float4*>(dst + (i / RUN) * STR + i % RUN) = make_float4(v[i], v[i + 1], v[i + 2], v[i + 3]);
 }
 
 template <typename T, int D, int H>
@@ -482,36 +488,272 @@ __device__ __forceinline__ void walk_bias(const EdgeList<EdgeCfg<T, D, H>::G>& e
     }
 }
 
+// ------------------------------------------------------- work distribution
+// Workgroups go to the 8 XCDs round-robin.  Each XCD walks contiguous runs of
+// kXcdRows nodes (runs c, c + 8, c + 16, ...), so the partners of neighbouring
+// rows share its L2, while a stretch of high-degree nodes, which a reordered
+// power-law graph has at its start, is spread over all XCDs (with one eighth of
+// the nodes per XCD the first one held 40% of the edges: forward and backward
+// of 1M power-law nodes, 4 x 32, 5.9 ms; in runs, and the long rows' runs in the
+// same launch, 3.0).  The runs per XCD divide the nodes evenly.
+constexpr int64_t kXcdRows = 2048;
+struct RowGrid {
+    unsigned run = 1;   // workgroups per run
+    unsigned grid = 8;  // workgroups in all
+};
+inline RowGrid row_grid(int64_t n, int64_t rows_per_block) {
+    const int64_t blocks = cdiv(n, rows_per_block);
+    const int64_t m = n / (kXcds * kXcdRows) > 1 ? n / (kXcds * kXcdRows) : 1;
+    RowGrid g;
+    g.run = unsigned(cdiv(blocks > 0 ? blocks : 1, kXcds * m));
+    g.grid = unsigned(kXcds * m * g.run);
+    return g;
+}
+__device__ __forceinline__ int64_t row_block(unsigned b, unsigned run) {
+    const unsigned k = b / kXcds;
+    return (int64_t(k / run) * kXcds + b % kXcds) * run + k % run;
+}
+
+// Remainder rows (columns) with more than GT_LONG_ROW edges, up to a row that
+// attends to every node, are cut into runs: a run is walked by one lane group
+// like a short row, in the same launch (the runs' workgroups first, the short
+// rows fill the chip behind them), leaves its partial state, and one
+// workgroup per long row merges its runs with the row's dense-tile partial.  A
+// run holds kMinRun edges, more where the long rows' edges would give more than
+// kMaxSpread runs.  (A token row and column of 980K edges beside 1M short rows:
+// chunks of 2,048 edges, a workgroup each, launched after the short rows took
+// 0.20 ms a pass and their merge 0.13-0.23 ms; forward and backward 2.84 -> 2.34
+// ms.  128 molecules and a token row of 3,137 edges: 155 -> 82 us, with one launch
+// and a merge per pass instead of six.)
+constexpr int kMinRun = 64;
+constexpr int64_t kMaxSpread = 4096;
+// Up to one wavefront of long rows, every lane group finds its run from the
+// rows' lengths itself; beyond, k_long_plan lists the rows' first runs before.
+constexpr int64_t kPlanFree = kWave;
+
+struct LongRows {
+    const int32_t* list = nullptr;
+    int64_t n = 0;
+    const int64_t* ptr = nullptr;
+    const int64_t* off = nullptr;  // [n + 2]: first run of each row, their number, the run length; null: none listed
+};
+
+__device__ __forceinline__ int run_length(int64_t edges) {
+    const int64_t c = (cdiv(edges, kMaxSpread) + kMinRun - 1) / kMinRun * kMinRun;
+    return c > kMinRun ? int(c) : kMinRun;
+}
+
+// Every long row's runs, one row per lane (lr.n <= kPlanFree).
+struct LaneRuns {
+    int incl, cnt, len;  // runs up to and with this row, its own, the run length
+    __device__ __forceinline__ explicit LaneRuns(const LongRows& lr) {
+        const int lane = lane_id();
+        int64_t deg = 0;
+        if (lane < lr.n) {
+            const int64_t i = lr.list[lane];
+            deg = lr.ptr[i + 1] - lr.ptr[i];
+        }
+        len = run_length(wave_sum(deg));
+        cnt = int(cdiv(deg, len));
+        incl = cnt;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int up = __shfl_up(incl, o, kWave);
+            if (lane >= o) incl += up;
+        }
+    }
+};
+
+// A run: its node and its edges at a, deg of them (-1 past the last run).
+struct Run {
+    int64_t a;
+    int32_t i;
+    int deg;
+};
+// Run v (each lane its own).  All lanes take part.
+__device__ __forceinline__ Run run_at(const LongRows& lr, int64_t v) {
+    int64_t r, first;
+    int len;
+    bool on;
+    if (!lr.off) {
+        const LaneRuns x(lr);
+        on = v < __shfl(x.incl, kWave - 1, kWave);
+        int k = 0;  // rows whose runs all lie before v
+#pragma unroll
+        for (int o = kWave / 2; o > 0; o >>= 1)
+            if (__shfl(x.incl, k + o - 1, kWave) <= v) k += o;
+        r = on ? k : 0;  // past the last run k would pass the list's end
+        first = __shfl(x.incl - x.cnt, int(r), kWave);
+        len = x.len;
+    } else {
+        on = v < lr.off[lr.n];
+        int64_t lo = 0, hi = lr.n;  // the last r with off[r] <= v
+        while (hi - lo > 1) {
+            const int64_t mid = (lo + hi) >> 1;
+            if (lr.off[mid] <= v) lo = mid;
+            else hi = mid;
+        }
+        r = lo;
+        first = lr.off[lo];
+        len = int(lr.off[lr.n + 1]);
+    }
+    const int32_t i = lr.list[r];
+    const int64_t a = lr.ptr[i], e0 = on ? (v - first) * len : 0, left = lr.ptr[i + 1] - a - e0;
+    return Run{a + e0, i, on ? (left < len ? int(left) : len) : -1};
+}
+// Runs [c0, c1) of list entry r (uniform).
+__device__ __forceinline__ void run_range(const LongRows& lr, int64_t r, int64_t& c0, int64_t& c1) {
+    if (!lr.off) {
+        const LaneRuns x(lr);
+        c1 = __shfl(x.incl, int(r), kWave);
+        c0 = c1 - __shfl(x.cnt, int(r), kWave);
+    } else {
+        c0 = lr.off[r];
+        c1 = lr.off[r + 1];
+    }
+}
+
+// What one lane group of a rows (columns) kernel walks: a node's edges, or a
+// run of a long row's; deg = -1 for nothing (a long row, or past the end).
+struct Work {
+    int64_t a;
+    int32_t i, run;  // run: -1 for a node's own row
+    int deg;
+    // Workgroups below run_blocks take runs, rows_per_block of them each.
+    __device__ __forceinline__ Work(int64_t n, const int64_t* __restrict__ ptr, const LongRows& lr,
+                                    unsigned run_blocks, unsigned xcd_run, int rows_per_block, int slot) {
+        if (blockIdx.x < run_blocks) {
+            run = int32_t(blockIdx.x) * rows_per_block + slot;
+            const Run r = run_at(lr, run);
+            i = r.i;
+            a = r.a;
+            deg = r.deg;
+            return;
+        }
+        run = -1;
+        const int64_t node = row_block(blockIdx.x - run_blocks, xcd_run) * rows_per_block + slot;
+        i = node < n ? int32_t(node) : 0;
+        a = ptr[i];
+        const int64_t dg = ptr[i + 1] - a;
+        deg = node < n && dg <= GT_LONG_ROW ? int(dg) : -1;
+    }
+    __device__ __forceinline__ bool own() const { return run < 0 && deg >= 0; }
+};
+
+// The first runs of more than kPlanFree long rows, in one workgroup.
+constexpr int kPlanThr = 1024;
+__global__ __launch_bounds__(kPlanThr) void k_long_plan(LongRows lr, int64_t* __restrict__ off) {
+    __shared__ int64_t s_w[kPlanThr / kWave];
+    const int t = threadIdx.x, w = t / kWave, lane = lane_id();
+    auto length = [&](int64_t r) -> int64_t {
+        if (r >= lr.n) return 0;
+        const int64_t i = lr.list[r];
+        return lr.ptr[i + 1] - lr.ptr[i];
+    };
+    int64_t sum = 0;
+    for (int64_t r = t; r < lr.n; r += kPlanThr) sum += length(r);
+    sum = wave_sum(sum);
+    if (lane == 0) s_w[w] = sum;
+    __syncthreads();
+    int64_t total = 0;
+    for (int k = 0; k < kPlanThr / kWave; ++k) total += s_w[k];
+    const int len = run_length(total);
+    int64_t base = 0;
+    for (int64_t r0 = 0; r0 < lr.n; r0 += kPlanThr) {
+        const int64_t cnt = cdiv(length(r0 + t), len);
+        int64_t incl = cnt;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int64_t up = __shfl_up(incl, o, kWave);
+            if (lane >= o) incl += up;
+        }
+        __syncthreads();  // s_w has been read
+        if (lane == kWave - 1) s_w[w] = incl;
+        __syncthreads();
+        int64_t before = base, all = 0;
+        for (int k = 0; k < kPlanThr / kWave; ++k) {
+            if (k < w) before += s_w[k];
+            all += s_w[k];
+        }
+        if (r0 + t < lr.n) off[r0 + t] = before + incl - cnt;
+        base += all;
+    }
+    if (t == 0) {
+        off[lr.n] = base;
+        off[lr.n + 1] = len;
+    }
+}
+
+// Floats a run leaves (float4-aligned): the forward acc[H D], m[H], l[H]; the
+// row pass a[H D], b[H D], d[H]; the column pass dk[H D], dv[H D].
+constexpr int64_t pad4(int64_t x) { return (x + 3) & ~int64_t(3); }
+constexpr int64_t fwd_run_floats(int H, int D) { return int64_t(H) * D + pad4(2 * H); }
+constexpr int64_t row_run_floats(int H, int D) { return 2 * int64_t(H) * D + pad4(H); }
+constexpr int64_t col_run_floats(int H, int D) { return 2 * int64_t(H) * D; }
+
+struct LongPlan {
+    int64_t* off = nullptr;  // [n_long + 2] where k_long_plan runs
+    float* part = nullptr;   // [max_runs, floats per run]
+    int64_t max_runs = 0;
+    int fold = 1;            // parts a row's runs are folded into before the merge (1: not folded)
+    unsigned blocks(int64_t rows_per_block) const {
+        return max_runs > 0 ? xcd_grid(cdiv(max_runs, rows_per_block)) : 0;
+    }
+};
+
+inline LongPlan long_plan_take(Ws& ws, int64_t n_long, int64_t nnz, int64_t per_run) {
+    LongPlan lp;
+    if (n_long <= 0) return lp;
+    const int64_t spread = nnz / kMinRun < kMaxSpread ? nnz / kMinRun : kMaxSpread;
+    lp.max_runs = n_long + spread;
+    // few long rows may hold thousands of runs each: 64 workgroups a row fold
+    // them first (more rows: fewer each, none from 2,048 rows on)
+    if (spread > 512) lp.fold = int(kMaxSpread / n_long < 1 ? 1 : kMaxSpread / n_long > 64 ? 64 : kMaxSpread / n_long);
+    if (n_long > kPlanFree) lp.off = ws.take<int64_t>(size_t(n_long + 2));
+    lp.part = ws.take<float>(size_t(lp.max_runs * per_run));
+    return lp;
+}
+
+gt_status long_rows(const int32_t* list, int64_t n_long, const int64_t* ptr, const LongPlan& lp, LongRows& lr,
+                    hipStream_t s) {
+    lr = LongRows{};
+    if (n_long <= 0) return GT_OK;
+    lr.list = list;
+    lr.n = n_long;
+    lr.ptr = ptr;
+    if (lp.off) {
+        k_long_plan<<<1, kPlanThr, 0, s>>>(lr, lp.off);
+        GT_LAUNCH_CHECK("long_plan");
+        lr.off = lp.off;
+    }
+    return GT_OK;
+}
+
 // ------------------------------------------------------------------ forward
 
 template <typename T, int D, int H, bool kBias>
-__global__ __launch_bounds__(kThreads) void k_fwd_rows(int64_t n, const int64_t* __restrict__ rp,
+__global__ __launch_bounds__(kThreads)
+__attribute__((amdgpu_waves_per_eu(kBias || kLaneBytes<T, D, H> > 32 ? 1 : 6))) void k_fwd_rows(int64_t n, const int64_t* __restrict__ rp,
                                                        const int32_t* __restrict__ cl, int64_t len,
                                                        const T* __restrict__ Q,
                                                        const T* __restrict__ K, const T* __restrict__ V, float sl2,
                                                        T* __restrict__ O, float* __restrict__ LSE, TilePartials tp,
-                                                       EdgeBias eb) {
+                                                       EdgeBias eb, unsigned xcd_run,
+    LongRows lr, unsigned run_blocks, float* __restrict__ part) {
     using C = EdgeCfg<T, D, H>;
     const Lanes<T, D, H> ln(lane_id());
-    const int64_t wave = xcd_block(blockIdx.x, gridDim.x) * (kThreads / kWave) + threadIdx.x / kWave;
-    const int64_t i = wave * C::NPW + ln.slot;
-    const bool live = i < n;
-    const int64_t self = live ? i : 0;
-    int64_t a = 0;
-    int deg = 0;
-    if (live) {
-        a = rp[i];
-        const int64_t dg = rp[i + 1] - a;
-        deg = dg > GT_LONG_ROW ? -1 : int(dg);
-    }
+    constexpr int kRows = C::NPW * (kThreads / kWave);
+    const Work w(n, rp, lr, run_blocks, xcd_run, kRows, int(threadIdx.x) / C::G);
+    const int64_t i = w.i, a = w.a;
+    const int deg = w.deg;
     const int dmax = uniform(wave_max(deg));
-    const int64_t off = ln.off(self);
+    const int64_t off = ln.off(i);
     SliceOf<T, D, H> q;
     q.load(Q + off);
     Online<C::F> st;
     auto begin = [&] {
         st = Online<C::F>();
-        if (live && deg >= 0 && tp.has_row(i)) load_fwd_partial<T, D, H>(st, tp, i, ln.h, off);
+        if (w.own() && tp.has_row(i)) load_fwd_partial<T, D, H>(st, tp, i, ln.h, off);
     };
     begin();
     const EdgeList<C::G> el(cl, len, a, deg, lane_id());
@@ -536,7 +778,16 @@ __global__ __launch_bounds__(kThreads) void k_fwd_rows(int64_t n, const int64_t*
         });
     }
     if (deg <= 0) begin();
-    if (live && deg >= 0) {
+    if (w.run >= 0) {
+        if (deg >= 0) {
+            float* out = part + int64_t(w.run) * fwd_run_floats(H, D);
+            store_f32_slice<C::F, C::RUN, C::STR>(out + ln.off(0), st.acc);
+            if (ln.part == 0) {
+                out[H * D + ln.h] = st.m;
+                out[H * D + H + ln.h] = st.l;
+            }
+        }
+    } else if (w.own()) {
         const float inv = st.l > 0.f ? 1.f / st.l : 0.f;
         store_slice<T, C::F, C::STR>(O + off, st.acc, inv);
         if (ln.part == 0) LSE[i * H + ln.h] = st.l > 0.f ? (st.m + __log2f(st.l)) * kLn2 : kNegInf;
@@ -587,36 +838,31 @@ __device__ __forceinline__ void load_row_partial(RowSums<EdgeCfg<T, D, H>::F>& r
 
 template <typename T, int D, int H, bool kBias>
 __global__ __launch_bounds__(kThreads)
-__attribute__((amdgpu_waves_per_eu(kBias ? kEdgeWaves<T, D, H> - 1 : kEdgeWaves<T, D, H>))) void k_bwd_rows(int64_t n, const int64_t* __restrict__ rp,
+__attribute__((amdgpu_waves_per_eu(kBias && kEdgeWaves<T, D, H> > 2 ? kEdgeWaves<T, D, H> - 1 : kEdgeWaves<T, D, H>))) void k_bwd_rows(int64_t n, const int64_t* __restrict__ rp,
                                                        const int32_t* __restrict__ cl, int64_t len,
                                                        const T* __restrict__ Q,
                                                        const T* __restrict__ K, const T* __restrict__ V,
                                                        const T* __restrict__ dO, const float* __restrict__ LSE,
-                                                       float* __restrict__ Dv, float sl2, float scale,
-                                                       T* __restrict__ dQ, TilePartials tp, EdgeBias eb) {
+                                                       float* __restrict__ Dv, float2* __restrict__ stat, float sl2,
+                                                       float scale,
+                                                       T* __restrict__ dQ, TilePartials tp, EdgeBias eb, unsigned xcd_run,
+    LongRows lr, unsigned run_blocks, float* __restrict__ part) {
     using C = EdgeCfg<T, D, H>;
     const Lanes<T, D, H> ln(lane_id());
-    const int64_t wave = xcd_block(blockIdx.x, gridDim.x) * (kThreads / kWave) + threadIdx.x / kWave;
-    const int64_t i = wave * C::NPW + ln.slot;
-    const bool live = i < n;
-    const int64_t self = live ? i : 0;
-    int64_t a = 0;
-    int deg = 0;
-    if (live) {
-        a = rp[i];
-        const int64_t dg = rp[i + 1] - a;
-        deg = dg > GT_LONG_ROW ? -1 : int(dg);
-    }
+    constexpr int kRows = C::NPW * (kThreads / kWave);
+    const Work w(n, rp, lr, run_blocks, xcd_run, kRows, int(threadIdx.x) / C::G);
+    const int64_t i = w.i, a = w.a;
+    const int deg = w.deg;
     const int dmax = uniform(wave_max(deg));
-    const int64_t off = ln.off(self);
+    const int64_t off = ln.off(i);
     SliceOf<T, D, H> q, g;
     q.load(Q + off);
     g.load(dO + off);
-    const float lse2 = LSE[self * H + ln.h] * kLog2e;
+    const float lse2 = LSE[i * H + ln.h] * kLog2e;
     RowSums<C::F> rs;
     auto begin = [&] {
         rs = RowSums<C::F>();
-        if (live && deg >= 0 && tp.has_row(i)) load_row_partial<T, D, H>(rs, tp, i, ln.h, off);
+        if (w.own() && tp.has_row(i)) load_row_partial<T, D, H>(rs, tp, i, ln.h, off);
     };
     begin();
     const EdgeList<C::G> el(cl, len, a, deg, lane_id());
@@ -645,12 +891,22 @@ __attribute__((amdgpu_waves_per_eu(kBias ? kEdgeWaves<T, D, H> - 1 : kEdgeWaves<
             });
     }
     if (deg <= 0) begin();
-    if (live && deg >= 0) {
+    if (w.run >= 0) {
+        if (deg >= 0) {
+            float* out = part + int64_t(w.run) * row_run_floats(H, D);
+            store_f32_slice<C::F, C::RUN, C::STR>(out + ln.off(0), rs.a.v);
+            store_f32_slice<C::F, C::RUN, C::STR>(out + H * D + ln.off(0), rs.b.v);
+            if (ln.part == 0) out[2 * H * D + ln.h] = rs.d[0] + rs.d[1];
+        }
+    } else if (w.own()) {
         const float d = rs.d[0] + rs.d[1];
 #pragma unroll
         for (int f = 0; f < C::F; ++f) rs.a.v[f] = fmaf(-d, rs.b.v[f], rs.a.v[f]);
         store_slice<T, C::F, C::STR>(dQ + off, rs.a.v, scale);
-        if (ln.part == 0) Dv[i * H + ln.h] = d;
+        if (ln.part == 0) {
+            if (Dv) Dv[i * H + ln.h] = d;
+            if (stat) stat[i * H + ln.h] = make_float2(lse2, d);
+        }
     }
 }
 
@@ -724,36 +980,30 @@ __device__ __forceinline__ void dkv_step(Acc<EdgeCfg<T, D, H>::F>& dk, Acc<EdgeC
 
 template <typename T, int D, int H, bool kBias>
 __global__ __launch_bounds__(kThreads)
-__attribute__((amdgpu_waves_per_eu(kBias ? kEdgeWaves<T, D, H> - 1 : 1))) void k_bwd_cols(int64_t n, const int64_t* __restrict__ cp,
+__attribute__((amdgpu_waves_per_eu(kBias && kEdgeWaves<T, D, H> > 2 ? kEdgeWaves<T, D, H> - 1 : 1))) void k_bwd_cols(int64_t n, const int64_t* __restrict__ cp,
                                                        const int32_t* __restrict__ rw, int64_t len,
                                                        const T* __restrict__ Q,
                                                        const T* __restrict__ K, const T* __restrict__ V,
                                                        const T* __restrict__ dO, const float2* __restrict__ stat,
                                                        float sl2, float scale, T* __restrict__ dK,
                                                        T* __restrict__ dV, TilePartials tpk, TilePartials tpv,
-                                                       EdgeBias eb) {
+                                                       EdgeBias eb, unsigned xcd_run,
+    LongRows lr, unsigned run_blocks, float* __restrict__ part) {
     using C = EdgeCfg<T, D, H>;
     const Lanes<T, D, H> ln(lane_id());
-    const int64_t wave = xcd_block(blockIdx.x, gridDim.x) * (kThreads / kWave) + threadIdx.x / kWave;
-    const int64_t j = wave * C::NPW + ln.slot;
-    const bool live = j < n;
-    const int64_t self = live ? j : 0;
-    int64_t a = 0;
-    int deg = 0;
-    if (live) {
-        a = cp[j];
-        const int64_t dg = cp[j + 1] - a;
-        deg = dg > GT_LONG_ROW ? -1 : int(dg);
-    }
+    constexpr int kRows = C::NPW * (kThreads / kWave);
+    const Work w(n, cp, lr, run_blocks, xcd_run, kRows, int(threadIdx.x) / C::G);
+    const int64_t j = w.i, a = w.a;
+    const int deg = w.deg;
     const int dmax = uniform(wave_max(deg));
-    const int64_t off = ln.off(self);
+    const int64_t off = ln.off(j);
     SliceOf<T, D, H> k, v;
     k.load(K + off);
     v.load(V + off);
     Acc<C::F> dk, dv;
     auto begin = [&] {
         dk = dv = Acc<C::F>();
-        if (live && deg >= 0 && tpk.has_col(j)) {
+        if (w.own() && tpk.has_col(j)) {
             load_f32_slice<C::F, C::RUN, C::STR>(dk.v, tpk.acc + off);
             load_f32_slice<C::F, C::RUN, C::STR>(dv.v, tpv.acc + off);
         }
@@ -780,349 +1030,227 @@ __attribute__((amdgpu_waves_per_eu(kBias ? kEdgeWaves<T, D, H> - 1 : 1))) void k
         });
     }
     if (deg <= 0) begin();
-    if (live && deg >= 0) {
+    if (w.run >= 0) {
+        if (deg >= 0) {
+            float* out = part + int64_t(w.run) * col_run_floats(H, D);
+            store_f32_slice<C::F, C::RUN, C::STR>(out + ln.off(0), dk.v);
+            store_f32_slice<C::F, C::RUN, C::STR>(out + H * D + ln.off(0), dv.v);
+        }
+    } else if (w.own()) {
         store_slice<T, C::F, C::STR>(dK + off, dk.v, scale);
         store_slice<T, C::F, C::STR>(dV + off, dv.v, 1.f);
     }
 }
 
-// ------------------------------------------------------------- long rows
-// Remainder rows (columns) with more than GT_LONG_ROW edges, up to a row that
-// attends to every node: each is cut into chunks of kChunk edges, one
-// workgroup per chunk leaves a partial state (its lane groups take the edges
-// round-robin and merge in LDS), and one workgroup per long row merges its
-// chunks with the row's dense-tile partial and writes the result.  The chunk
-// table is built on the device; the chunk grid is launched at its upper bound
-// (one chunk per long row plus one per kChunk remainder edges) and surplus
-// workgroups return at once.
-constexpr int kChunk = 2048;
-
+// --------------------------------------------------- merge of the long rows
+// Where a row may hold many runs, `parts` workgroups a row first fold them: each
+// sums (the forward: merges) its share of the runs into the first of them.
+// Then one workgroup per row: H D / 4 threads take four features of a run (or
+// of a share's first run) each, NG groups of them every NG-th one, and the groups' sums
+// are added in order in LDS.  All in a fixed order: results are reproducible.
 template <int H, int D>
-constexpr int64_t FwdLongF = int64_t(H) * D + 2 * H;  // floats per chunk: m[H], l[H], acc[H D]
-template <int H, int D>
-constexpr int64_t RowLongF = 2 * int64_t(H) * D + H;  // a[H D], b[H D], d[H]
-template <int H, int D>
-constexpr int64_t ColLongF = 2 * int64_t(H) * D;      // dk[H D], dv[H D]
-
-struct LongPlan {
-    int32_t* counts = nullptr;     // [n_long]: chunks of each long row
-    int64_t* chunk_off = nullptr;  // [n_long + 1]: exclusive scan of counts
-    float* part = nullptr;         // [max_chunks, floats per chunk]
-    int64_t max_chunks = 0;
-    ScanTmp scan;
+struct MergeCfg {
+    static constexpr int Q4 = H * D / 4, NG = kThreads / Q4;
+    static_assert(kThreads % Q4 == 0, "threads per run divide the workgroup");
 };
+__device__ __forceinline__ int64_t fold_share(int64_t runs, int parts) { return parts > 1 ? cdiv(runs, parts) : 1; }
 
-inline LongPlan long_plan_take(Ws& ws, int64_t n_long, int64_t nnz, int64_t per_chunk) {
-    LongPlan lp;
-    if (n_long <= 0) return lp;
-    lp.max_chunks = n_long + nnz / kChunk + 1;
-    lp.counts = ws.take<int32_t>(size_t(n_long));
-    lp.chunk_off = ws.take<int64_t>(size_t(n_long + 1));
-    lp.scan.block_sums = ws.take<int64_t>(size_t(scan_tmp_elems(n_long)));
-    lp.part = ws.take<float>(size_t(lp.max_chunks * per_chunk));
-    return lp;
+template <typename T>
+__device__ __forceinline__ void store4(T* __restrict__ p, float4 v) {
+    if constexpr (sizeof(T) == 2)
+        *reinterpret_cast<uint2*>(p) = make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
+    else
+        *reinterpret_cast<float4*>(p) = v;
+}
+__device__ __forceinline__ float4 add4(float4 a, float4 b) {
+    return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
+}
+// a wa + b wb
+__device__ __forceinline__ float4 mix4(float4 a, float wa, float4 b, float wb) {
+    return make_float4(fmaf(b.x, wb, a.x * wa), fmaf(b.y, wb, a.y * wa), fmaf(b.z, wb, a.z * wa),
+                       fmaf(b.w, wb, a.w * wa));
 }
 
-__global__ void k_long_counts(const int32_t* __restrict__ list, int64_t n_long, const int64_t* __restrict__ ptr,
-                              int32_t* __restrict__ counts) {
-    const int64_t r = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (r >= n_long) return;
-    const int64_t i = list[r];
-    counts[r] = int32_t(cdiv(ptr[i + 1] - ptr[i], kChunk));
-}
-
-gt_status long_chunks(const int32_t* list, int64_t n_long, const int64_t* ptr, const LongPlan& lp, hipStream_t s) {
-    k_long_counts<<<grid_for(n_long, 256), 256, 0, s>>>(list, n_long, ptr, lp.counts);
-    GT_LAUNCH_CHECK("long_counts");
-    return exclusive_scan_i32(lp.counts, n_long, lp.chunk_off, lp.scan, s);
-}
-
-// Chunk b -> (long row r, chunk c of that row, its edge range [e0, e1) inside
-// the row); false for the surplus of the grid.
-__device__ __forceinline__ bool chunk_of(const int64_t* __restrict__ off, int64_t n_long, int64_t b, int64_t& r,
-                                         int& e0) {
-    if (b >= off[n_long]) return false;
-    int64_t lo = 0, hi = n_long;  // the last r with off[r] <= b
-    while (hi - lo > 1) {
-        const int64_t mid = (lo + hi) >> 1;
-        if (off[mid] <= b) lo = mid;
-        else hi = mid;
+template <int D, int H>
+__global__ __launch_bounds__(kThreads) void k_fwd_fold(LongRows lr, int parts, float* __restrict__ part) {
+    constexpr int64_t kF = fwd_run_floats(H, D);
+    int64_t c0, c1;
+    run_range(lr, blockIdx.x / parts, c0, c1);
+    const int64_t share = fold_share(c1 - c0, parts);
+    c0 += (blockIdx.x % parts) * share;
+    c1 = c0 + share < c1 ? c0 + share : c1;
+    const int q = threadIdx.x, h = 4 * q / D;
+    if (q >= H * D / 4 || c1 - c0 < 2) return;
+    float m = kMinRef, l = 0.f;
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 8
+    for (int64_t c = c0; c < c1; ++c) {
+        const float* pc = part + c * kF;
+        const float4 v = *reinterpret_cast<const float4*>(pc + 4 * q);
+        const float pm = pc[H * D + h], pl = pc[H * D + H + h];
+        const float mn = fmaxf(m, pm), wa = ex2(m - mn), wb = ex2(pm - mn);
+        o = mix4(o, wa, v, wb);
+        l = fmaf(pl, wb, l * wa);
+        m = mn;
     }
-    r = lo;
-    e0 = int(b - off[lo]) * kChunk;
-    return true;
+    // a head's m and l are read by the D / 4 lanes of one wavefront, which all
+    // have read them when its first lane writes
+    float* out = part + c0 * kF;
+    *reinterpret_cast<float4*>(out + 4 * q) = o;
+    if (4 * q % D == 0) {
+        out[H * D + h] = m;
+        out[H * D + H + h] = l;
+    }
 }
 
-template <typename T, int D, int H, bool kBias>
-__global__ __launch_bounds__(kThreads) void k_fwd_long(const int32_t* __restrict__ list, int64_t n_long,
-                                                       const int64_t* __restrict__ chunk_off,
-                                                       const int64_t* __restrict__ rp,
-                                                       const int32_t* __restrict__ cl, const T* __restrict__ Q,
-                                                       const T* __restrict__ K, const T* __restrict__ V, float sl2,
-                                                       float* __restrict__ part, EdgeBias eb) {
-    using C = EdgeCfg<T, D, H>;
-    constexpr int S = kThreads / C::G;  // lane groups per workgroup
-    __shared__ float s_m[S][H];
-    __shared__ float s_l[S][H];
-    __shared__ float s_acc[S][H * D];
-    int64_t r;
-    int e0;
-    if (!chunk_of(chunk_off, n_long, blockIdx.x, r, e0)) return;
-    const Lanes<T, D, H> ln(threadIdx.x);
-    const int64_t i = list[r];
-    const int64_t a = rp[i];
-    const int deg = int(rp[i + 1] - a);
-    const int e1 = e0 + kChunk < deg ? e0 + kChunk : deg;
-    const int64_t off = ln.off(i);
-    SliceOf<T, D, H> q;
-    q.load(Q + off);
-    Online<C::F> st;
-    // each lane group walks its own run of the chunk's edges
-    const int run = int(cdiv(e1 - e0, S)), g0 = e0 + ln.slot * run;
-    const int gdeg = g0 < e1 ? (g0 + run < e1 ? run : e1 - g0) : 0;
-    const EdgeList<C::G> el(cl, a + deg, a + g0, gdeg, lane_id());
-    el.walk(run, [&](int64_t j0, int64_t j1, int t, bool ok0, bool ok1) {
-        float b0 = 0.f, b1 = 0.f;
-        if constexpr (kBias) {
-            b0 = bias_one(eb, a + g0, t, ok0, H, ln);
-            b1 = bias_one(eb, a + g0, t + 1, ok1, H, ln);
-        }
-        fwd_step<T, D, H>(st, q, K, V, j0, j1, ok0, ok1, ln, sl2, b0, b1);
-    });
-    if (gdeg == 0) st = Online<C::F>();  // no edges: whatever the stand-in row held
-    if (ln.part == 0) {
-        s_m[ln.slot][ln.h] = st.m;
-        s_l[ln.slot][ln.h] = st.l;
-    }
-#pragma unroll
-    for (int f = 0; f < C::F; ++f) s_acc[ln.slot][ln.h * D + C::feat(ln.part, f)] = st.acc[f];
-    __syncthreads();
-    float* out = part + blockIdx.x * FwdLongF<H, D>;
-    for (int idx = threadIdx.x; idx < H * D; idx += kThreads) {
-        const int h = idx / D;
-        float M = kNegInf;
-        for (int g = 0; g < S; ++g) M = fmaxf(M, s_m[g][h]);
-        float lsum = 0.f, o = 0.f;
-        if (M != kNegInf) {
-            for (int g = 0; g < S; ++g) {
-                const float w = ex2(s_m[g][h] - M);
-                lsum += s_l[g][h] * w;
-                o += s_acc[g][idx] * w;
-            }
-        }
-        out[2 * H + idx] = o;
-        if (idx % D == 0) {
-            out[h] = M;
-            out[H + h] = lsum;
-        }
+// F floats per run, summed.
+template <int64_t F>
+__global__ __launch_bounds__(kThreads) void k_sum_fold(LongRows lr, int parts, float* __restrict__ part) {
+    int64_t c0, c1;
+    run_range(lr, blockIdx.x / parts, c0, c1);
+    const int64_t share = fold_share(c1 - c0, parts);
+    c0 += (blockIdx.x % parts) * share;
+    c1 = c0 + share < c1 ? c0 + share : c1;
+    if (c1 - c0 < 2) return;
+    for (int q = threadIdx.x; q < F / 4; q += kThreads) {
+        float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 8
+        for (int64_t c = c0; c < c1; ++c) o = add4(o, *reinterpret_cast<const float4*>(part + c * F + 4 * q));
+        *reinterpret_cast<float4*>(part + c0 * F + 4 * q) = o;
     }
 }
 
 template <typename T, int D, int H>
-__global__ __launch_bounds__(kThreads) void k_fwd_long_merge(const int32_t* __restrict__ list,
-                                                             const int64_t* __restrict__ chunk_off,
-                                                             const float* __restrict__ part, TilePartials tp,
-                                                             T* __restrict__ O, float* __restrict__ LSE) {
-    const int64_t i = list[blockIdx.x];
-    const int64_t c0 = chunk_off[blockIdx.x], c1 = chunk_off[blockIdx.x + 1];
-    const bool tile = tp.has_row(i);
-    for (int idx = threadIdx.x; idx < H * D; idx += kThreads) {
-        const int h = idx / D;
-        float M = tile ? tp.m[i * H + h] : kNegInf;
-        for (int64_t c = c0; c < c1; ++c) M = fmaxf(M, part[c * FwdLongF<H, D> + h]);
-        float lsum = 0.f, o = 0.f;
-        if (M != kNegInf) {
-            if (tile) {
-                const float w = ex2(tp.m[i * H + h] - M);
-                lsum = tp.l[i * H + h] * w;
-                o = tp.acc[i * H * D + idx] * w;
-            }
-            for (int64_t c = c0; c < c1; ++c) {
-                const float* pc = part + c * FwdLongF<H, D>;
-                const float w = ex2(pc[h] - M);
-                lsum += pc[H + h] * w;
-                o += pc[2 * H + idx] * w;
-            }
-        }
-        const float val = lsum > 0.f ? o / lsum : 0.f;
-        if (sizeof(T) == 2)
-            reinterpret_cast<uint16_t*>(O)[i * H * D + idx] = f32_to_bf16(val);
-        else
-            reinterpret_cast<float*>(O)[i * H * D + idx] = val;
-        if (idx % D == 0) LSE[i * H + h] = lsum > 0.f ? (M + __log2f(lsum)) * kLn2 : kNegInf;
+__global__ __launch_bounds__(kThreads) void k_fwd_long_merge(LongRows lr, int parts, const float* __restrict__ part, TilePartials tp,
+                                                       T* __restrict__ O, float* __restrict__ LSE) {
+    using M = MergeCfg<H, D>;
+    constexpr int64_t kF = fwd_run_floats(H, D);
+    __shared__ float4 s_o[M::NG][M::Q4];
+    __shared__ float s_m[M::NG][M::Q4], s_l[M::NG][M::Q4];
+    const int64_t i = lr.list[blockIdx.x];
+    int64_t c0, c1;
+    run_range(lr, blockIdx.x, c0, c1);
+    const int64_t step = fold_share(c1 - c0, parts);
+    const int g = threadIdx.x / M::Q4, q = threadIdx.x % M::Q4, h = 4 * q / D;
+    float m = kMinRef, l = 0.f;
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 4
+    for (int64_t c = c0 + g * step; c < c1; c += M::NG * step) {
+        const float* pc = part + c * kF;
+        const float4 v = *reinterpret_cast<const float4*>(pc + 4 * q);
+        const float pm = pc[H * D + h], pl = pc[H * D + H + h];
+        const float mn = fmaxf(m, pm), wa = ex2(m - mn), wb = ex2(pm - mn);
+        o = mix4(o, wa, v, wb);
+        l = fmaf(pl, wb, l * wa);
+        m = mn;
     }
+    s_o[g][q] = o;
+    s_m[g][q] = m;
+    s_l[g][q] = l;
+    __syncthreads();
+    if (g != 0) return;
+    const int64_t at = i * H * D + 4 * q;
+    if (tp.has_row(i)) {
+        m = fmaxf(tp.m[i * H + h], kMinRef);
+        l = tp.l[i * H + h];
+        o = *reinterpret_cast<const float4*>(tp.acc + at);
+    } else {
+        m = kMinRef;
+        l = 0.f;
+        o = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    for (int k = 0; k < M::NG; ++k) {
+        const float pm = s_m[k][q], mn = fmaxf(m, pm), wa = ex2(m - mn), wb = ex2(pm - mn);
+        o = mix4(o, wa, s_o[k][q], wb);
+        l = fmaf(s_l[k][q], wb, l * wa);
+        m = mn;
+    }
+    const float inv = l > 0.f ? 1.f / l : 0.f;
+    store4(O + at, make_float4(o.x * inv, o.y * inv, o.z * inv, o.w * inv));
+    if (4 * q % D == 0) LSE[i * H + h] = l > 0.f ? (m + __log2f(l)) * kLn2 : kNegInf;
 }
 
-template <typename T, int D, int H, bool kBias>
-__global__ __launch_bounds__(kThreads) void k_bwd_rows_long(const int32_t* __restrict__ list, int64_t n_long,
-                                                            const int64_t* __restrict__ chunk_off,
-                                                            const int64_t* __restrict__ rp,
-                                                            const int32_t* __restrict__ cl, const T* __restrict__ Q,
-                                                            const T* __restrict__ K, const T* __restrict__ V,
-                                                            const T* __restrict__ dO, const float* __restrict__ LSE,
-                                                            float sl2, float* __restrict__ part, EdgeBias eb) {
-    using C = EdgeCfg<T, D, H>;
-    constexpr int S = kThreads / C::G;
-    __shared__ float s_a[S][H * D];
-    __shared__ float s_b[S][H * D];
-    __shared__ float s_d[S][H];
-    int64_t r;
-    int e0;
-    if (!chunk_of(chunk_off, n_long, blockIdx.x, r, e0)) return;
-    const Lanes<T, D, H> ln(threadIdx.x);
-    const int64_t i = list[r];
-    const int64_t a = rp[i];
-    const int deg = int(rp[i + 1] - a);
-    const int e1 = e0 + kChunk < deg ? e0 + kChunk : deg;
-    const int64_t off = ln.off(i);
-    SliceOf<T, D, H> q, g;
-    q.load(Q + off);
-    g.load(dO + off);
-    const float lse2 = LSE[i * H + ln.h] * kLog2e;
-    RowSums<C::F> rs;
-    // each lane group walks its own run of the chunk's edges
-    const int run = int(cdiv(e1 - e0, S)), g0 = e0 + ln.slot * run;
-    const int gdeg = g0 < e1 ? (g0 + run < e1 ? run : e1 - g0) : 0;
-    const EdgeList<C::G> el(cl, a + deg, a + g0, gdeg, lane_id());
-    el.template walk_ahead<kAheadRows, Rows<T, D, H>>(
-        run, [&](Rows<T, D, H>& x, int64_t jj) { x.load(K, V, ln.off(jj)); },
-        [&](const Rows<T, D, H>& x, int t, int k) {
-            const bool ok = t < el.deg;
-            float b = 0.f;
-            if constexpr (kBias) b = bias_one(eb, a + g0, t, ok, H, ln);
-            dq_step<T, D, H>(rs, q, g, lse2, x, ok, k & 1, sl2, b);
-        });
-    if (gdeg == 0) rs = RowSums<C::F>();  // no edges: whatever the stand-in row held
-#pragma unroll
-    for (int f = 0; f < C::F; ++f) {
-        s_a[ln.slot][ln.h * D + C::feat(ln.part, f)] = rs.a.v[f];
-        s_b[ln.slot][ln.h * D + C::feat(ln.part, f)] = rs.b.v[f];
+template <typename T, int D, int H>
+__global__ __launch_bounds__(kThreads) void k_bwd_rows_long_merge(LongRows lr, int parts, const float* __restrict__ part,
+                                                            TilePartials tp, const float* __restrict__ LSE,
+                                                            float scale, T* __restrict__ dQ, float* __restrict__ Dv,
+                                                            float2* __restrict__ stat) {
+    using M = MergeCfg<H, D>;
+    constexpr int64_t kF = row_run_floats(H, D);
+    __shared__ float4 s_a[M::NG][M::Q4], s_b[M::NG][M::Q4];
+    __shared__ float s_d[M::NG][M::Q4];
+    const int64_t i = lr.list[blockIdx.x];
+    int64_t c0, c1;
+    run_range(lr, blockIdx.x, c0, c1);
+    const int64_t step = fold_share(c1 - c0, parts);
+    const int g = threadIdx.x / M::Q4, q = threadIdx.x % M::Q4, h = 4 * q / D;
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
+    float d = 0.f;
+#pragma unroll 4
+    for (int64_t c = c0 + g * step; c < c1; c += M::NG * step) {
+        const float* pc = part + c * kF;
+        a = add4(a, *reinterpret_cast<const float4*>(pc + 4 * q));
+        b = add4(b, *reinterpret_cast<const float4*>(pc + H * D + 4 * q));
+        d += pc[2 * H * D + h];
     }
-    if (ln.part == 0) s_d[ln.slot][ln.h] = rs.d[0] + rs.d[1];
+    s_a[g][q] = a;
+    s_b[g][q] = b;
+    s_d[g][q] = d;
     __syncthreads();
-    float* out = part + blockIdx.x * RowLongF<H, D>;
-    for (int idx = threadIdx.x; idx < H * D; idx += kThreads) {
-        const int h = idx / D;
-        float sa = 0.f, sb = 0.f, sd = 0.f;
-        for (int gi = 0; gi < S; ++gi) {
-            sa += s_a[gi][idx];
-            sb += s_b[gi][idx];
-            sd += s_d[gi][h];
-        }
-        out[idx] = sa;
-        out[H * D + idx] = sb;
-        if (idx % D == 0) out[2 * H * D + h] = sd;
+    if (g != 0) return;
+    const int64_t at = i * H * D + 4 * q;
+    if (tp.has_row(i)) {
+        a = add4(a, *reinterpret_cast<const float4*>(tp.acc + at));
+        b = add4(b, *reinterpret_cast<const float4*>(tp.acc2 + at));
+        d += tp.m[i * H + h];
+    }
+    for (int k = 1; k < M::NG; ++k) {
+        a = add4(a, s_a[k][q]);
+        b = add4(b, s_b[k][q]);
+        d += s_d[k][q];
+    }
+    store4(dQ + at, make_float4(fmaf(-d, b.x, a.x) * scale, fmaf(-d, b.y, a.y) * scale, fmaf(-d, b.z, a.z) * scale,
+                                fmaf(-d, b.w, a.w) * scale));
+    if (4 * q % D == 0) {
+        if (Dv) Dv[i * H + h] = d;
+        if (stat) stat[i * H + h] = make_float2(LSE[i * H + h] * kLog2e, d);
     }
 }
 
 template <typename T, int D, int H>
-__global__ __launch_bounds__(kThreads) void k_bwd_rows_long_merge(const int32_t* __restrict__ list,
-                                                                  const int64_t* __restrict__ chunk_off,
-                                                                  const float* __restrict__ part, TilePartials tp,
-                                                                  float scale, T* __restrict__ dQ,
-                                                                  float* __restrict__ Dv) {
-    const int64_t i = list[blockIdx.x];
-    const int64_t c0 = chunk_off[blockIdx.x], c1 = chunk_off[blockIdx.x + 1];
-    const bool tile = tp.has_row(i);
-    for (int idx = threadIdx.x; idx < H * D; idx += kThreads) {
-        const int h = idx / D;
-        float sa = tile ? tp.acc[i * H * D + idx] : 0.f;
-        float sb = tile ? tp.acc2[i * H * D + idx] : 0.f;
-        float sd = tile ? tp.m[i * H + h] : 0.f;
-        for (int64_t c = c0; c < c1; ++c) {
-            const float* pc = part + c * RowLongF<H, D>;
-            sa += pc[idx];
-            sb += pc[H * D + idx];
-            sd += pc[2 * H * D + h];
-        }
-        const float v = fmaf(-sd, sb, sa) * scale;
-        if (sizeof(T) == 2)
-            reinterpret_cast<uint16_t*>(dQ)[i * H * D + idx] = f32_to_bf16(v);
-        else
-            reinterpret_cast<float*>(dQ)[i * H * D + idx] = v;
-        if (idx % D == 0) Dv[i * H + h] = sd;
+__global__ __launch_bounds__(kThreads) void k_bwd_cols_long_merge(LongRows lr, int parts, const float* __restrict__ part,
+                                                            TilePartials tpk, TilePartials tpv, float scale,
+                                                            T* __restrict__ dK, T* __restrict__ dV) {
+    using M = MergeCfg<H, D>;
+    constexpr int64_t kF = col_run_floats(H, D);
+    __shared__ float4 s_k[M::NG][M::Q4], s_v[M::NG][M::Q4];
+    const int64_t j = lr.list[blockIdx.x];
+    int64_t c0, c1;
+    run_range(lr, blockIdx.x, c0, c1);
+    const int64_t step = fold_share(c1 - c0, parts);
+    const int g = threadIdx.x / M::Q4, q = threadIdx.x % M::Q4;
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
+#pragma unroll 4
+    for (int64_t c = c0 + g * step; c < c1; c += M::NG * step) {
+        const float* pc = part + c * kF;
+        a = add4(a, *reinterpret_cast<const float4*>(pc + 4 * q));
+        b = add4(b, *reinterpret_cast<const float4*>(pc + H * D + 4 * q));
     }
-}
-
-template <typename T, int D, int H, bool kBias>
-__global__ __launch_bounds__(kThreads) void k_bwd_cols_long(const int32_t* __restrict__ list, int64_t n_long,
-                                                            const int64_t* __restrict__ chunk_off,
-                                                            const int64_t* __restrict__ cp,
-                                                            const int32_t* __restrict__ rw, const T* __restrict__ Q,
-                                                            const T* __restrict__ K, const T* __restrict__ V,
-                                                            const T* __restrict__ dO,
-                                                            const float2* __restrict__ stat, float sl2,
-                                                            float* __restrict__ part, EdgeBias eb) {
-    using C = EdgeCfg<T, D, H>;
-    constexpr int S = kThreads / C::G;
-    __shared__ float s_k[S][H * D];
-    __shared__ float s_v[S][H * D];
-    int64_t r;
-    int e0;
-    if (!chunk_of(chunk_off, n_long, blockIdx.x, r, e0)) return;
-    const Lanes<T, D, H> ln(threadIdx.x);
-    const int64_t j = list[r];
-    const int64_t a = cp[j];
-    const int deg = int(cp[j + 1] - a);
-    const int e1 = e0 + kChunk < deg ? e0 + kChunk : deg;
-    const int64_t off = ln.off(j);
-    SliceOf<T, D, H> k, v;
-    k.load(K + off);
-    v.load(V + off);
-    Acc<C::F> dk, dv;
-    // each lane group walks its own run of the chunk's edges
-    const int run = int(cdiv(e1 - e0, S)), g0 = e0 + ln.slot * run;
-    const int gdeg = g0 < e1 ? (g0 + run < e1 ? run : e1 - g0) : 0;
-    const EdgeList<C::G> el(rw, a + deg, a + g0, gdeg, lane_id());
-    el.walk(run, [&](int64_t i0, int64_t i1, int t, bool ok0, bool ok1) {
-        dkv_step<T, D, H, kBias>(dk, dv, k, v, Q, dO, stat, i0, i1, ok0, ok1, ln, sl2, eb, a + g0 + t,
-                                 a + g0 + t + 1);
-    });
-    if (gdeg == 0) dk = dv = Acc<C::F>();  // no edges: whatever the stand-in row held
-#pragma unroll
-    for (int f = 0; f < C::F; ++f) {
-        s_k[ln.slot][ln.h * D + C::feat(ln.part, f)] = dk.v[f];
-        s_v[ln.slot][ln.h * D + C::feat(ln.part, f)] = dv.v[f];
-    }
+    s_k[g][q] = a;
+    s_v[g][q] = b;
     __syncthreads();
-    float* out = part + blockIdx.x * ColLongF<H, D>;
-    for (int idx = threadIdx.x; idx < H * D; idx += kThreads) {
-        float ak = 0.f, av = 0.f;
-        for (int g = 0; g < S; ++g) {
-            ak += s_k[g][idx];
-            av += s_v[g][idx];
-        }
-        out[idx] = ak;
-        out[H * D + idx] = av;
+    if (g != 0) return;
+    const int64_t at = j * H * D + 4 * q;
+    if (tpk.has_col(j)) {
+        a = add4(a, *reinterpret_cast<const float4*>(tpk.acc + at));
+        b = add4(b, *reinterpret_cast<const float4*>(tpv.acc + at));
     }
-}
-
-template <typename T, int D, int H>
-__global__ __launch_bounds__(kThreads) void k_bwd_cols_long_merge(const int32_t* __restrict__ list,
-                                                                  const int64_t* __restrict__ chunk_off,
-                                                                  const float* __restrict__ part, TilePartials tpk,
-                                                                  TilePartials tpv, float scale,
-                                                                  T* __restrict__ dK, T* __restrict__ dV) {
-    const int64_t j = list[blockIdx.x];
-    const int64_t c0 = chunk_off[blockIdx.x], c1 = chunk_off[blockIdx.x + 1];
-    const bool tile = tpk.has_col(j);
-    for (int idx = threadIdx.x; idx < H * D; idx += kThreads) {
-        float ak = tile ? tpk.acc[j * H * D + idx] : 0.f;
-        float av = tile ? tpv.acc[j * H * D + idx] : 0.f;
-        for (int64_t c = c0; c < c1; ++c) {
-            const float* pc = part + c * ColLongF<H, D>;
-            ak += pc[idx];
-            av += pc[H * D + idx];
-        }
-        ak *= scale;
-        if (sizeof(T) == 2) {
-            reinterpret_cast<uint16_t*>(dK)[j * H * D + idx] = f32_to_bf16(ak);
-            reinterpret_cast<uint16_t*>(dV)[j * H * D + idx] = f32_to_bf16(av);
-        } else {
-            reinterpret_cast<float*>(dK)[j * H * D + idx] = ak;
-            reinterpret_cast<float*>(dV)[j * H * D + idx] = av;
-        }
+    for (int k = 1; k < M::NG; ++k) {
+        a = add4(a, s_k[k][q]);
+        b = add4(b, s_v[k][q]);
     }
+    store4(dK + at, make_float4(a.x * scale, a.y * scale, a.z * scale, a.w * scale));
+    store4(dV + at, b);
 }
 
 // The column pass reads each in-edge's row statistics as one (LSE log2 e, D)
@@ -1159,10 +1287,10 @@ template <typename T, int D, int H>
 __global__ __launch_bounds__(kThreads) void k_gather_probe(int64_t n, const int64_t* __restrict__ rp,
                                                            const int32_t* __restrict__ cl, int64_t len,
                                                            const T* __restrict__ A, const T* __restrict__ B,
-                                                           uint32_t* __restrict__ sink) {
+                                                           uint32_t* __restrict__ sink, unsigned run) {
     using C = EdgeCfg<T, D, H>;
     const Lanes<T, D, H> ln(lane_id());
-    const int64_t wave = xcd_block(blockIdx.x, gridDim.x) * (kThreads / kWave) + threadIdx.x / kWave;
+    const int64_t wave = row_block(blockIdx.x, run) * (kThreads / kWave) + threadIdx.x / kWave;
     const int64_t i = wave * C::NPW + ln.slot;
     const bool live = i < n;
     const int64_t self = live ? i : 0;
@@ -1189,9 +1317,10 @@ template <typename T, int D, int H>
 gt_status run_probe(const gt_tiles* p, const void* A, const void* B, uint32_t* sink, hipStream_t s) {
     using C = EdgeCfg<T, D, H>;
     if (p->n == 0) return GT_OK;
-    const unsigned grid = xcd_grid(cdiv(cdiv(p->n, C::NPW), kThreads / kWave));
-    k_gather_probe<T, D, H><<<grid, kThreads, 0, s>>>(p->n, p->sp_rowptr, p->sp_col, p->nnz_sparse,
-                                                      static_cast<const T*>(A), static_cast<const T*>(B), sink);
+    const RowGrid rg = row_grid(p->n, C::NPW * (kThreads / kWave));
+    k_gather_probe<T, D, H><<<rg.grid, kThreads, 0, s>>>(p->n, p->sp_rowptr, p->sp_col, p->nnz_sparse,
+                                                         static_cast<const T*>(A), static_cast<const T*>(B), sink,
+                                                         rg.run);
     GT_LAUNCH_CHECK("gather_probe");
     return GT_OK;
 }
@@ -1211,7 +1340,7 @@ gt_status run_fwd_t(const gt_tiles* p, const void* Q, const void* K, const void*
     Ws ws(ws_ptr);
     ws.take<char>(256);
     TilePartials tp = tile_partials_fwd(ws, p, H, D);
-    LongPlan lp = long_plan_take(ws, p->n_long_rows, p->nnz_sparse, FwdLongF<H, D>);
+    LongPlan lp = long_plan_take(ws, p->n_long_rows, p->nnz_sparse, fwd_run_floats(H, D));
     const float sl2 = scale * kLog2e;
     gt_status st;
     if (p->n_dense > 0) {
@@ -1221,19 +1350,21 @@ gt_status run_fwd_t(const gt_tiles* p, const void* Q, const void* K, const void*
     } else {
         tp = TilePartials{};
     }
-    const int64_t waves = cdiv(n, C::NPW);
-    k_fwd_rows<T, D, H, kBias><<<xcd_grid(cdiv(waves, kThreads / kWave)), kThreads, 0, s>>>(
+    LongRows lr;
+    if ((st = long_rows(p->long_rows, p->n_long_rows, p->sp_rowptr, lp, lr, s)) != GT_OK) return st;
+    const RowGrid rg = row_grid(n, C::NPW * (kThreads / kWave));
+    const unsigned runs = lp.blocks(C::NPW * (kThreads / kWave));
+    k_fwd_rows<T, D, H, kBias><<<runs + rg.grid, kThreads, 0, s>>>(
         n, p->sp_rowptr, p->sp_col, p->nnz_sparse, static_cast<const T*>(Q), static_cast<const T*>(K),
-        static_cast<const T*>(V), sl2, static_cast<T*>(O), LSE, tp, eb);
+        static_cast<const T*>(V), sl2, static_cast<T*>(O), LSE, tp, eb, rg.run, lr, runs, lp.part);
     GT_LAUNCH_CHECK("sparse_fwd_rows");
     if (p->n_long_rows > 0) {
-        if ((st = long_chunks(p->long_rows, p->n_long_rows, p->sp_rowptr, lp, s)) != GT_OK) return st;
-        k_fwd_long<T, D, H, kBias><<<unsigned(lp.max_chunks), kThreads, 0, s>>>(
-            p->long_rows, p->n_long_rows, lp.chunk_off, p->sp_rowptr, p->sp_col, static_cast<const T*>(Q),
-            static_cast<const T*>(K), static_cast<const T*>(V), sl2, lp.part, eb);
-        GT_LAUNCH_CHECK("sparse_fwd_long");
-        k_fwd_long_merge<T, D, H><<<unsigned(p->n_long_rows), kThreads, 0, s>>>(
-            p->long_rows, lp.chunk_off, lp.part, tp, static_cast<T*>(O), LSE);
+        if (lp.fold > 1) {
+            k_fwd_fold<D, H><<<unsigned(p->n_long_rows) * lp.fold, kThreads, 0, s>>>(lr, lp.fold, lp.part);
+            GT_LAUNCH_CHECK("sparse_fwd_fold");
+        }
+        k_fwd_long_merge<T, D, H><<<unsigned(p->n_long_rows), kThreads, 0, s>>>(lr, lp.fold, lp.part, tp,
+                                                                               static_cast<T*>(O), LSE);
         GT_LAUNCH_CHECK("sparse_fwd_long_merge");
     }
     return GT_OK;
@@ -1248,15 +1379,15 @@ gt_status run_fwd(const gt_tiles* p, const void* Q, const void* K, const void* V
 
 template <typename T, int D, int H, bool kBias>
 gt_status run_bwd_rows_t(const gt_tiles* p, const void* Q, const void* K, const void* V, const void* dO,
-                         const float* LSE, float scale, void* dQ, float* Dv, void* ws_ptr, EdgeBias eb,
-                         hipStream_t s) {
+                         const float* LSE, float scale, void* dQ, float* Dv, float2* stat, void* ws_ptr,
+                         EdgeBias eb, hipStream_t s) {
     using C = EdgeCfg<T, D, H>;
     const int64_t n = p->n;
     if (n == 0) return GT_OK;
     Ws ws(ws_ptr);
     ws.take<char>(256);
     TileBwdPartials tb = tile_partials_bwd(ws, p, H, D, true, false);
-    LongPlan lp = long_plan_take(ws, p->n_long_rows, p->nnz_sparse, RowLongF<H, D>);
+    LongPlan lp = long_plan_take(ws, p->n_long_rows, p->nnz_sparse, row_run_floats(H, D));
     const float sl2 = scale * kLog2e;
     const T *q = static_cast<const T*>(Q), *k = static_cast<const T*>(K), *v = static_cast<const T*>(V);
     const T* g = static_cast<const T*>(dO);
@@ -1264,17 +1395,22 @@ gt_status run_bwd_rows_t(const gt_tiles* p, const void* Q, const void* K, const 
     if (p->n_dense > 0) {
         if ((st = tile_bwd_dq<T, D, H>(p, q, k, v, g, LSE, sl2, tb.dq, eb.tile, s)) != GT_OK) return st;
     }
-    const unsigned grid = xcd_grid(cdiv(cdiv(n, C::NPW), kThreads / kWave));
-    k_bwd_rows<T, D, H, kBias><<<grid, kThreads, 0, s>>>(n, p->sp_rowptr, p->sp_col, p->nnz_sparse, q, k, v, g,
-                                                         LSE, Dv, sl2, scale, static_cast<T*>(dQ), tb.dq, eb);
+    LongRows lr;
+    if ((st = long_rows(p->long_rows, p->n_long_rows, p->sp_rowptr, lp, lr, s)) != GT_OK) return st;
+    const RowGrid rg = row_grid(n, C::NPW * (kThreads / kWave));
+    const unsigned runs = lp.blocks(C::NPW * (kThreads / kWave));
+    k_bwd_rows<T, D, H, kBias><<<runs + rg.grid, kThreads, 0, s>>>(
+        n, p->sp_rowptr, p->sp_col, p->nnz_sparse, q, k, v, g, LSE, Dv, stat, sl2, scale, static_cast<T*>(dQ), tb.dq,
+        eb, rg.run, lr, runs, lp.part);
     GT_LAUNCH_CHECK("sparse_bwd_rows");
     if (p->n_long_rows > 0) {
-        if ((st = long_chunks(p->long_rows, p->n_long_rows, p->sp_rowptr, lp, s)) != GT_OK) return st;
-        k_bwd_rows_long<T, D, H, kBias><<<unsigned(lp.max_chunks), kThreads, 0, s>>>(
-            p->long_rows, p->n_long_rows, lp.chunk_off, p->sp_rowptr, p->sp_col, q, k, v, g, LSE, sl2, lp.part, eb);
-        GT_LAUNCH_CHECK("sparse_bwd_rows_long");
+        if (lp.fold > 1) {
+            k_sum_fold<row_run_floats(H, D)>
+                <<<unsigned(p->n_long_rows) * lp.fold, kThreads, 0, s>>>(lr, lp.fold, lp.part);
+            GT_LAUNCH_CHECK("sparse_bwd_rows_fold");
+        }
         k_bwd_rows_long_merge<T, D, H><<<unsigned(p->n_long_rows), kThreads, 0, s>>>(
-            p->long_rows, lp.chunk_off, lp.part, tb.dq, scale, static_cast<T*>(dQ), Dv);
+            lr, lp.fold, lp.part, tb.dq, LSE, scale, static_cast<T*>(dQ), Dv, stat);
         GT_LAUNCH_CHECK("sparse_bwd_rows_long_merge");
     }
     return GT_OK;
@@ -1282,23 +1418,24 @@ gt_status run_bwd_rows_t(const gt_tiles* p, const void* Q, const void* K, const 
 
 template <typename T, int D, int H>
 gt_status run_bwd_rows(const gt_tiles* p, const void* Q, const void* K, const void* V, const void* dO,
-                       const float* LSE, float scale, void* dQ, float* Dv, void* ws_ptr, EdgeBias eb, hipStream_t s) {
-    return eb.b ? run_bwd_rows_t<T, D, H, true>(p, Q, K, V, dO, LSE, scale, dQ, Dv, ws_ptr, eb, s)
-                : run_bwd_rows_t<T, D, H, false>(p, Q, K, V, dO, LSE, scale, dQ, Dv, ws_ptr, eb, s);
+                       const float* LSE, float scale, void* dQ, float* Dv, float2* stat, void* ws_ptr, EdgeBias eb,
+                       hipStream_t s) {
+    return eb.b ? run_bwd_rows_t<T, D, H, true>(p, Q, K, V, dO, LSE, scale, dQ, Dv, stat, ws_ptr, eb, s)
+                : run_bwd_rows_t<T, D, H, false>(p, Q, K, V, dO, LSE, scale, dQ, Dv, stat, ws_ptr, eb, s);
 }
 
 template <typename T, int D, int H, bool kBias>
 gt_status run_bwd_cols_t(const gt_tiles* p, const void* Q, const void* K, const void* V, const void* dO,
-                         const float* LSE, const float* Dv, float scale, void* dK, void* dV, void* ws_ptr,
-                         EdgeBias eb, hipStream_t s) {
+                         const float* LSE, const float* Dv, const float2* packed, float scale, void* dK, void* dV,
+                         void* ws_ptr, EdgeBias eb, hipStream_t s) {
     using C = EdgeCfg<T, D, H>;
     const int64_t n = p->n;
     if (n == 0) return GT_OK;
     Ws ws(ws_ptr);
     ws.take<char>(256);
     TileBwdPartials tb = tile_partials_bwd(ws, p, H, D, false, true);
-    LongPlan lp = long_plan_take(ws, p->n_long_cols, p->nnz_sparse, ColLongF<H, D>);
-    float2* stat = ws.take<float2>(size_t(n) * H);
+    LongPlan lp = long_plan_take(ws, p->n_long_cols, p->nnz_sparse, col_run_floats(H, D));
+    float2* stat = packed ? nullptr : ws.take<float2>(size_t(n) * H);
     const float sl2 = scale * kLog2e;
     const T *q = static_cast<const T*>(Q), *k = static_cast<const T*>(K), *v = static_cast<const T*>(V);
     const T* g = static_cast<const T*>(dO);
@@ -1307,21 +1444,26 @@ gt_status run_bwd_cols_t(const gt_tiles* p, const void* Q, const void* K, const 
         if ((st = tile_bwd_dkdv<T, D, H>(p, q, k, v, g, LSE, Dv, sl2, tb.dk, tb.dv, eb.tile, s)) != GT_OK)
             return st;
     }
-    k_pack_stats<<<grid_for(n * H, 256, 8192), 256, 0, s>>>(n * H, LSE, Dv, stat);
-    GT_LAUNCH_CHECK("sparse_bwd_pack_stats");
-    const unsigned grid = xcd_grid(cdiv(cdiv(n, C::NPW), kThreads / kWave));
-    k_bwd_cols<T, D, H, kBias><<<grid, kThreads, 0, s>>>(n, p->sp_colptr, p->sp_row, p->nnz_sparse, q, k, v, g,
-                                                         stat, sl2, scale, static_cast<T*>(dK),
-                                                         static_cast<T*>(dV), tb.dk, tb.dv, eb);
+    if (!packed) {
+        k_pack_stats<<<grid_for(n * H, 256, 8192), 256, 0, s>>>(n * H, LSE, Dv, stat);
+        GT_LAUNCH_CHECK("sparse_bwd_pack_stats");
+    }
+    LongRows lr;
+    if ((st = long_rows(p->long_cols, p->n_long_cols, p->sp_colptr, lp, lr, s)) != GT_OK) return st;
+    const RowGrid rg = row_grid(n, C::NPW * (kThreads / kWave));
+    const unsigned runs = lp.blocks(C::NPW * (kThreads / kWave));
+    k_bwd_cols<T, D, H, kBias><<<runs + rg.grid, kThreads, 0, s>>>(
+        n, p->sp_colptr, p->sp_row, p->nnz_sparse, q, k, v, g, packed ? packed : stat, sl2, scale,
+        static_cast<T*>(dK), static_cast<T*>(dV), tb.dk, tb.dv, eb, rg.run, lr, runs, lp.part);
     GT_LAUNCH_CHECK("sparse_bwd_cols");
     if (p->n_long_cols > 0) {
-        if ((st = long_chunks(p->long_cols, p->n_long_cols, p->sp_colptr, lp, s)) != GT_OK) return st;
-        k_bwd_cols_long<T, D, H, kBias><<<unsigned(lp.max_chunks), kThreads, 0, s>>>(
-            p->long_cols, p->n_long_cols, lp.chunk_off, p->sp_colptr, p->sp_row, q, k, v, g, stat, sl2, lp.part,
-            eb);
-        GT_LAUNCH_CHECK("sparse_bwd_cols_long");
+        if (lp.fold > 1) {
+            k_sum_fold<col_run_floats(H, D)>
+                <<<unsigned(p->n_long_cols) * lp.fold, kThreads, 0, s>>>(lr, lp.fold, lp.part);
+            GT_LAUNCH_CHECK("sparse_bwd_cols_fold");
+        }
         k_bwd_cols_long_merge<T, D, H><<<unsigned(p->n_long_cols), kThreads, 0, s>>>(
-            p->long_cols, lp.chunk_off, lp.part, tb.dk, tb.dv, scale, static_cast<T*>(dK), static_cast<T*>(dV));
+            lr, lp.fold, lp.part, tb.dk, tb.dv, scale, static_cast<T*>(dK), static_cast<T*>(dV));
         GT_LAUNCH_CHECK("sparse_bwd_cols_long_merge");
     }
     return GT_OK;
@@ -1329,22 +1471,25 @@ gt_status run_bwd_cols_t(const gt_tiles* p, const void* Q, const void* K, const 
 
 template <typename T, int D, int H>
 gt_status run_bwd_cols(const gt_tiles* p, const void* Q, const void* K, const void* V, const void* dO,
-                       const float* LSE, const float* Dv, float scale, void* dK, void* dV, void* ws_ptr, EdgeBias eb,
-                       hipStream_t s) {
-    return eb.b ? run_bwd_cols_t<T, D, H, true>(p, Q, K, V, dO, LSE, Dv, scale, dK, dV, ws_ptr, eb, s)
-                : run_bwd_cols_t<T, D, H, false>(p, Q, K, V, dO, LSE, Dv, scale, dK, dV, ws_ptr, eb, s);
+                       const float* LSE, const float* Dv, const float2* packed, float scale, void* dK, void* dV,
+                       void* ws_ptr, EdgeBias eb, hipStream_t s) {
+    return eb.b ? run_bwd_cols_t<T, D, H, true>(p, Q, K, V, dO, LSE, Dv, packed, scale, dK, dV, ws_ptr, eb, s)
+                : run_bwd_cols_t<T, D, H, false>(p, Q, K, V, dO, LSE, Dv, packed, scale, dK, dV, ws_ptr, eb, s);
 }
 
 template <typename T, int D, int H>
 gt_status run_bwd(const gt_tiles* p, const void* Q, const void* K, const void* V, const void* dO, const float* LSE,
                   float scale, void* dQ, void* dK, void* dV, void* ws_ptr, EdgeBias eb, hipStream_t s) {
     if (p->n == 0) return GT_OK;
+    // the row pass leaves the packed statistics the column pass reads; D alone
+    // only where the tile kernels read it
     Ws ws(ws_ptr);
-    float* Dv = ws.take<float>(size_t(p->n) * H);
+    float2* stat = ws.take<float2>(size_t(p->n) * H);
+    float* Dv = p->n_dense > 0 ? ws.take<float>(size_t(p->n) * H) : nullptr;
     char* rest = ws.take<char>(1);
-    gt_status st = run_bwd_rows<T, D, H>(p, Q, K, V, dO, LSE, scale, dQ, Dv, rest, eb, s);
+    gt_status st = run_bwd_rows<T, D, H>(p, Q, K, V, dO, LSE, scale, dQ, Dv, stat, rest, eb, s);
     if (st != GT_OK) return st;
-    return run_bwd_cols<T, D, H>(p, Q, K, V, dO, LSE, Dv, scale, dK, dV, rest, eb, s);
+    return run_bwd_cols<T, D, H>(p, Q, K, V, dO, LSE, Dv, stat, scale, dK, dV, rest, eb, s);
 }
 
 bool supported(int32_t H, int32_t d, gt_dtype dt) {
@@ -1368,24 +1513,25 @@ size_t fwd_ws(const gt_tiles* p, int32_t H, int32_t d) {
     Ws ws(nullptr);
     ws.take<char>(256);
     tile_partials_fwd(ws, p, H, d);
-    long_plan_take(ws, p->n_long_rows, p->nnz_sparse, int64_t(H) * d + 2 * H);
+    long_plan_take(ws, p->n_long_rows, p->nnz_sparse, fwd_run_floats(H, d));
     return ws.size();
 }
-size_t bwd_part_ws(const gt_tiles* p, int32_t H, int32_t d, bool rows, bool cols) {
+size_t bwd_part_ws(const gt_tiles* p, int32_t H, int32_t d, bool rows, bool cols, bool with_stat = true) {
     Ws ws(nullptr);
     ws.take<char>(256);
     tile_partials_bwd(ws, p, H, d, rows, cols);
-    if (rows) long_plan_take(ws, p->n_long_rows, p->nnz_sparse, 2 * int64_t(H) * d + H);
+    if (rows) long_plan_take(ws, p->n_long_rows, p->nnz_sparse, row_run_floats(H, d));
     if (cols) {
-        long_plan_take(ws, p->n_long_cols, p->nnz_sparse, 2 * int64_t(H) * d);
-        ws.take<float2>(size_t(p->n > 0 ? p->n : 1) * H);
+        long_plan_take(ws, p->n_long_cols, p->nnz_sparse, col_run_floats(H, d));
+        if (with_stat) ws.take<float2>(size_t(p->n > 0 ? p->n : 1) * H);
     }
     return ws.size();
 }
 size_t bwd_ws(const gt_tiles* p, int32_t H, int32_t d) {
     Ws ws(nullptr);
-    ws.take<float>(size_t(p->n > 0 ? p->n : 1) * H);
-    const size_t a = bwd_part_ws(p, H, d, true, false), b = bwd_part_ws(p, H, d, false, true);
+    ws.take<float2>(size_t(p->n > 0 ? p->n : 1) * H);
+    if (p->n_dense > 0) ws.take<float>(size_t(p->n > 0 ? p->n : 1) * H);
+    const size_t a = bwd_part_ws(p, H, d, true, false), b = bwd_part_ws(p, H, d, false, true, false);
     ws.take<char>(a > b ? a : b);
     return ws.size();
 }
@@ -1434,8 +1580,8 @@ extern "C" gt_status gt_sparse_attn_bwd_rows(const gt_tiles* plan, int32_t H, in
         return fail(GT_ERR_INVALID_ARG, "gt_sparse_attn_bwd_rows: null pointer");
     if (ws_bytes < bwd_part_ws(plan, H, d, true, false))
         return fail(GT_ERR_WORKSPACE, "gt_sparse_attn_bwd_rows: workspace too small");
-    return GT_DISPATCH_ATTN(dtype, d, H, run_bwd_rows, plan, Q, K, V, dO, LSE, scale, dQ, Dstat, ws, EdgeBias{},
-                            stream);
+    return GT_DISPATCH_ATTN(dtype, d, H, run_bwd_rows, plan, Q, K, V, dO, LSE, scale, dQ, Dstat,
+                            static_cast<float2*>(nullptr), ws, EdgeBias{}, stream);
 }
 
 extern "C" size_t gt_sparse_attn_bwd_cols_workspace_size(const gt_tiles* plan, int32_t H, int32_t d,
@@ -1455,8 +1601,8 @@ extern "C" gt_status gt_sparse_attn_bwd_cols(const gt_tiles* plan, int32_t H, in
         return fail(GT_ERR_INVALID_ARG, "gt_sparse_attn_bwd_cols: null pointer");
     if (ws_bytes < bwd_part_ws(plan, H, d, false, true))
         return fail(GT_ERR_WORKSPACE, "gt_sparse_attn_bwd_cols: workspace too small");
-    return GT_DISPATCH_ATTN(dtype, d, H, run_bwd_cols, plan, Q, K, V, dO, LSE, Dstat, scale, dK, dV, ws,
-                            EdgeBias{}, stream);
+    return GT_DISPATCH_ATTN(dtype, d, H, run_bwd_cols, plan, Q, K, V, dO, LSE, Dstat,
+                            static_cast<const float2*>(nullptr), scale, dK, dV, ws, EdgeBias{}, stream);
 }
 
 extern "C" gt_status gt_sparse_attn_bwd(const gt_tiles* plan, int32_t H, int32_t d, gt_dtype dtype, const void* Q,

@@ -4,27 +4,31 @@
 // n x n buffer.
 //
 // Design (CDNA4, wave64, v_mfma_f32_32x32x16_bf16):
-//   - A workgroup owns 256 rows of one head.  In the forward each wavefront
-//     owns 64 of them (two 32-row MFMA blocks), so every operand fragment read
-//     from LDS feeds two products; the backward passes give each wavefront one
-//     block (8 wavefronts), which halves their registers and leaves 2-3
-//     wavefronts per SIMD.  The partner rows stream through LDS in 64-row stages,
-//     double buffered: the next stage is loaded into registers while the
-//     current one is multiplied, then written to the other buffer, with one
+//   - A workgroup owns the rows of 2 to 8 wavefronts of one head, 32 or (large
+//     forwards) 64 rows each, so every operand fragment read from LDS feeds one
+//     or two products; where a layer has few such blocks for the chip, a second
+//     set of wavefronts takes half of the partners (FullShape).  The partner rows
+//     stream through LDS in 64-row stages, double buffered: the next stage is
+//     loaded straight into LDS while the current one is multiplied, with one
 //     barrier per stage.
 //   - Scores are formed transposed (partners x owned rows), so each lane holds
 //     one owned row and 16 of its partners; per-row statistics need one
 //     v_permlane32_swap between the half-waves.  The probabilities (or dS)
 //     become the next product's B operand straight from the accumulators; the
-//     A operand of that product (V^T, K^T, dO^T, Q^T) is read from a
-//     transposed LDS copy written as 4-partner x 4-feature blocks.
-//   - The forward's running maximum is lazy: the accumulators are rescaled
-//     only when some row's block maximum exceeds it by 2^8 (exp2 domain), so
-//     weights stay below 256 and the result is unchanged.
+//     A operand of that product (V^T, K^T, dO^T, Q^T) is read from the
+//     row-major copy by transposing LDS reads (the dense tiles: from a transposed
+//     LDS copy written as 4-partner x 4-feature blocks).
+//   - The forward's running maximum is lazy: the accumulators are rescaled only
+//     when weights reach 2^8, so weights stay below 256 and the result is
+//     unchanged.
 //   - D_i = <dO_i, O_i> from the given O: every full-layer weight is O(1/n),
 //     so no cancellation-prone sum over partners is needed.
 //   - Workgroups are remapped so that each XCD works on one range of
 //     (head, row block) pairs and shares that head's K and V in its L2.
+//   - Measured at 65,536 x 8 x 64: forward 10.5 -> 8.6 ms (1,020 TFLOP/s, a large
+//     bf16 matrix product reaches about 1,130 here), backward 34.0 -> 28.6 ms (the
+//     seven products it forms run at 1,080 TFLOP/s); at 3,001 x 8 x 64 86 -> 41 and
+//     205 -> 110 us.
 #include "tile_attn.h"
 
 namespace gt {
@@ -33,7 +37,6 @@ namespace {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
-constexpr int kRowsWg = 256;             // owned rows per workgroup of the full layer
 constexpr int kStage = 64;               // partner rows per LDS stage
 constexpr int kTS = kStage + 4;          // transposed LDS row stride (elements)
 constexpr float kNegInf = -__builtin_huge_valf();
@@ -153,25 +156,6 @@ struct Stager {
             }
         }
     }
-    // A stage whose 64 rows are all below n: one uniform base address, per-lane
-    // 32-bit offsets that do not change from stage to stage, no clamping.
-    __device__ __forceinline__ void load_in(const uint16_t* __restrict__ X, int64_t base, int H, int h) {
-        const uint16_t* xb = X + (base * H + h) * D;
-        const int rs = H * D;
-        valid = ~0u;
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int it = item(k), rg = it / FG, fg = it % FG;
-            const uint16_t* p = xb + 4 * rg * rs + 4 * fg;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) r[k][j] = *reinterpret_cast<const uint2*>(p + j * rs);
-        }
-    }
-    // Either form, by where the stage ends.
-    __device__ __forceinline__ void load_any(const uint16_t* __restrict__ X, int64_t base, int64_t n, int H, int h) {
-        if (base + kStage <= n) load_in(X, base, H, h);
-        else load(X, base, n, H, h);
-    }
     __device__ __forceinline__ uint2 row(int k, int j) const {
         return (valid >> (4 * k + j)) & 1u ? r[k][j] : make_uint2(0, 0);
     }
@@ -206,42 +190,149 @@ struct Stager {
 // compiler's wait counting starts the streaming loop from a clean state).
 __device__ __forceinline__ void drain() { __builtin_amdgcn_s_waitcnt(0); }
 
+// ------------------------------------------------------------- full layer
+// Partner rows are staged 64 at a time by loads that write LDS directly (no
+// registers, no stores), one row-major copy of each operand, double buffered:
+// the next stage's loads are issued before the current one is multiplied.  A
+// row's 16-byte pieces are permuted by the row number (the loads place lane i
+// at byte 16 i, so a lane picks the piece it fetches), which spreads the same
+// piece of neighbouring rows over all LDS banks.  The row operand of a product
+// is read as it lies; the transposed operand (features x partners) by
+// ds_read_b64_tr_b16, which turns a 4 partners x 16 features block round.
+template <int D>
+struct Tile {
+    static constexpr int kPieces = D / 8;                  // 16-byte pieces per row
+    static constexpr int kElems = kStage * D;              // one staged operand
+    static constexpr int kLoads = kElems * 2 / 1024;       // 1 KiB wavefront loads per operand
+    __device__ __forceinline__ static int turn(int r) { return D == 64 ? r & 7 : (r >> 1) & 3; }
+
+    // This wavefront's share of a stage of X[:, h, :], rows base .. base + 63
+    // (rows past the end repeat the last one).
+    template <int WAVES>
+    __device__ __forceinline__ static void fetch(uint16_t* s, const uint16_t* __restrict__ X, int64_t base, int64_t n,
+                                                 int H, int h, int wave, int lane) {
+#pragma unroll
+        for (int q0 = 0; q0 < kLoads; q0 += WAVES) {
+            const int q = q0 + wave;
+            if (q >= kLoads) break;  // uniform
+            const int at = q * 64 + lane, r = at / kPieces, c = (at % kPieces) ^ turn(r);
+            const int64_t left = n - 1 - base;
+            const int row = r < left ? r : int(left);
+            const uint16_t* src = X + (base * H + h) * D + int64_t(row * H) * D + 8 * c;
+            __builtin_amdgcn_global_load_lds(
+                reinterpret_cast<const __attribute__((address_space(1))) uint32_t*>(reinterpret_cast<uintptr_t>(src)),
+                reinterpret_cast<__attribute__((address_space(3))) uint32_t*>(
+                    reinterpret_cast<uintptr_t>(s + q * 512)),
+                16, 0, 0);
+        }
+    }
+    // Row operand: row r, features 16 c + 8 (lane / 32) .. + 7.
+    __device__ __forceinline__ static bf16x8_t rows(const uint16_t* s, int r, int c, int lane) {
+        return __builtin_bit_cast(
+            bf16x8_t, *reinterpret_cast<const uint4*>(s + r * D + 8 * ((2 * c + (lane >> 5)) ^ turn(r))));
+    }
+    // Transposed operand: feature 32 db + lane % 32; partners base + 4 (lane / 32) + {0..3} and base + 8 + 4 (lane
+    // / 32) + {0..3}, the partner order of an accumulator-layout B operand (acc_b16).
+    __device__ __forceinline__ static bf16x8_t cols(const uint16_t* s, int db, int base, int lane) {
+        typedef short s16x4_t __attribute__((ext_vector_type(4)));
+        const int k = 4 * (lane >> 5) + ((lane & 15) >> 2);
+        const int c = (4 * db + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ turn(k);
+        const uint16_t* p = s + (base + k) * D + 8 * c + 4 * (lane & 1);
+        // turn(k + 8) = turn(k)
+        const s16x4_t x = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            reinterpret_cast<__attribute__((address_space(3))) s16x4_t*>(reinterpret_cast<uintptr_t>(p)));
+        const s16x4_t y = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            reinterpret_cast<__attribute__((address_space(3))) s16x4_t*>(reinterpret_cast<uintptr_t>(p + 8 * D)));
+        typedef short s16x8_t __attribute__((ext_vector_type(8)));
+        return __builtin_bit_cast(bf16x8_t, s16x8_t{x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]});
+    }
+};
+
+// The stage fetched last is in LDS for every wavefront, and every wavefront is done with the one before.
+__device__ __forceinline__ void stage_done() {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+}
+
 // Workgroup -> (head, first owned row); false for the padding of the grid.
+template <int ROWS>
 __device__ __forceinline__ bool wg_coords(int64_t n, int H, int& h, int64_t& row0) {
-    const int64_t blocks = cdiv(n, kRowsWg);
+    const int64_t blocks = cdiv(n, ROWS);
     const int64_t b = xcd_block(blockIdx.x, gridDim.x);
     if (b >= blocks * H) return false;
     h = int(b / blocks);
-    row0 = (b % blocks) * kRowsWg;
+    row0 = (b % blocks) * ROWS;
     return true;
 }
+template <int ROWS>
+inline unsigned full_grid(int64_t n, int H) { return xcd_grid(cdiv(n, ROWS) * H); }
 
-inline unsigned full_grid(int64_t n, int H) { return xcd_grid(cdiv(n, kRowsWg) * H); }
+__device__ __forceinline__ f32x16_t splat16(float x) {
+    f32x16_t z;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) z[i] = x;
+    return z;
+}
 
-// 32-row MFMA blocks per wavefront in the full layer (the kernels are
-// templated on it) and the threads per workgroup that hold kRowsWg rows.  The
-// forward keeps two blocks (every K and V fragment read from LDS feeds two
-// products; measured faster: 10.9 against 13.7 ms at 65,536 x 8 x 64); the
-// backward passes take one, which leaves them 2-3 wavefronts per SIMD instead
-// of one (44.1 -> 35.3 ms).
-constexpr int kFullFwdNB = 2, kFullBwdNB = 1;
-constexpr int kFullFwdThr = kRowsWg / (32 * kFullFwdNB) * kWave;
-constexpr int kFullBwdThr = kRowsWg / (32 * kFullBwdNB) * kWave;
+// Accumulators (features x owned rows) times `f` as bf16, one owned row's 8-byte pieces per lane.
+template <int D>
+__device__ __forceinline__ void store_acc(uint16_t* o, const f32x16_t (&a)[D / 32], float f, int lane) {
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            *reinterpret_cast<uint2*>(o + 32 * db + 8 * j + 4 * (lane >> 5)) =
+                make_uint2(pack_bf16x2(a[db][4 * j] * f, a[db][4 * j + 1] * f),
+                           pack_bf16x2(a[db][4 * j + 2] * f, a[db][4 * j + 3] * f));
+}
+
+// Where the partners of a stage are shared by KS = 2 sets of wavefronts: add
+// the second set's accumulators to the first's (false for the second set).
+template <int KS, int WAVES, int N>
+__device__ __forceinline__ bool add_shares(f32x16_t* a, int part) {
+    if constexpr (KS == 2) {
+        __shared__ float s_x[N * 16][WAVES * kWave];
+        const int at = int(threadIdx.x) % (WAVES * kWave);
+        if (part == 1)
+#pragma unroll
+            for (int k = 0; k < N; ++k)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) s_x[16 * k + i][at] = a[k][i];
+        __syncthreads();
+        if (part == 0)
+#pragma unroll
+            for (int k = 0; k < N; ++k)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) a[k][i] += s_x[16 * k + i][at];
+    }
+    return part == 0;
+}
 
 // ------------------------------------------------------------------ forward
+// The running reference m of a row is checked after the fact: a block's weights
+// exp2(s - m) are summed anyway, and only where a lane's sum of 16 exceeds 2^8 (or is
+// not a number, as from the first block's m = -inf) are the block's scores
+// formed again, the true maximum taken and the accumulators rescaled.  Weights
+// stay below 2^8 as with a maximum taken first, without its 16 vector
+// operations a block.
 
-template <int D, int NB>
-__global__ __launch_bounds__(kRowsWg / (32 * NB) * kWave) __attribute__((amdgpu_waves_per_eu(NB == 1 ? 3 : 2))) void k_full_fwd(int64_t n, int H, const uint16_t* __restrict__ Q,
-                                                      const uint16_t* __restrict__ K,
-                                                      const uint16_t* __restrict__ V, float sl2,
-                                                      uint16_t* __restrict__ O, float* __restrict__ LSE) {
-    __shared__ __attribute__((aligned(16))) uint16_t sK[2][kStage * RS<D>::v];
-    __shared__ __attribute__((aligned(16))) uint16_t sVt[2][D * kTS];
+template <int D, int NB, int WAVES, int KS>
+__global__ __launch_bounds__(WAVES * KS * kWave) __attribute__((amdgpu_waves_per_eu(2))) void k_full_fwd(
+    int64_t n, int H, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
+    float sl2, uint16_t* __restrict__ O, float* __restrict__ LSE) {
+    using Tl = Tile<D>;
+    // one variable per buffer: the compiler then knows that a stage's reads do
+    // not touch the buffer being filled, and does not wait for its loads
+    __shared__ __attribute__((aligned(16))) uint16_t sK0[Tl::kElems], sK1[Tl::kElems];
+    __shared__ __attribute__((aligned(16))) uint16_t sV0[Tl::kElems], sV1[Tl::kElems];
     int h;
     int64_t row0;
-    if (!wg_coords(n, H, h, row0)) return;
-    const int lane = lane_id();
-    const int64_t q0 = row0 + (threadIdx.x / kWave) * 32 * NB;
+    if (!wg_coords<32 * NB * WAVES>(n, H, h, row0)) return;
+    const int lane = lane_id(), wave = uniform(int(threadIdx.x) / kWave);
+    const int part = KS == 1 ? 0 : wave / WAVES;  // which of a stage's KS shares of the partners
+    const int64_t q0 = row0 + (wave - part * WAVES) * 32 * NB;
+    Tl::template fetch<WAVES * KS>(sK0, K, 0, n, H, h, wave, lane);
+    Tl::template fetch<WAVES * KS>(sV0, V, 0, n, H, h, wave, lane);
     Frag<D> qf[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) qf[b].load(Q, q0 + 32 * b + (lane & 31), n, H, h, lane);
@@ -256,70 +347,81 @@ __global__ __launch_bounds__(kRowsWg / (32 * NB) * kWave) __attribute__((amdgpu_
                                                                          0x80008000u));
     }
     f32x16_t acc[NB][D / 32];
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int db = 0; db < D / 32; ++db) acc[b][db] = zero16();
     float m[NB], l[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
+#pragma unroll
+        for (int db = 0; db < D / 32; ++db) acc[b][db] = zero16();
         m[b] = kNegInf;
         l[b] = 0.f;
     }
-
-    Stager<D, kRowsWg / (32 * NB) * kWave> gk, gv;
-    gk.load(K, 0, n, H, h);
-    gv.load(V, 0, n, H, h);
-    gk.store_rm(sK[0]);
-    gv.store_tr(sVt[0]);
-    drain();
-    __syncthreads();
+    stage_done();
     const int64_t stages = cdiv(n, kStage);
-    for (int64_t t = 0; t < stages; ++t) {
-        const int buf = int(t & 1);
+    auto stage = [&](int64_t t, const uint16_t* cK, const uint16_t* cV, uint16_t* nK, uint16_t* nV) {
         const int64_t kbase = t * kStage;
         if (t + 1 < stages) {
-            gk.load_any(K, kbase + kStage, n, H, h);
-            gv.load_any(V, kbase + kStage, n, H, h);
+            Tl::template fetch<WAVES * KS>(nK, K, kbase + kStage, n, H, h, wave, lane);
+            Tl::template fetch<WAVES * KS>(nV, V, kbase + kStage, n, H, h, wave, lane);
         }
-        const uint16_t* k_s = sK[buf];
-        const uint16_t* v_s = sVt[buf];
 #pragma unroll
-        for (int kb = 0; kb < kStage / 32; ++kb) {
-            f32x16_t s[NB];
-            #pragma unroll
-            for (int b = 0; b < NB; ++b) s[b] = zero16();
-#pragma unroll
-            for (int c = 0; c < D / 16; ++c) {
-                const bf16x8_t a = lds_row8<D>(k_s, 32 * kb + (lane & 31), c, lane);
-                #pragma unroll
-                for (int b = 0; b < NB; ++b) s[b] = mma(a, qf[b].v[c], s[b]);
-            }
+        for (int kx = 0; kx < kStage / 32 / KS; ++kx) {
+            const int kb = kx + part * (kStage / 32 / KS);
             const int64_t key0 = kbase + 32 * kb;
-            if (__builtin_expect(key0 + 32 > n, 0)) {  // ragged last block: partners >= n take no weight
-                // kept as a branch (the empty asm stops the compiler from turning
-                // it into selects on every block)
-                asm volatile("" ::: "memory");
+            if (KS > 1 && key0 >= n) break;  // no partner left for this share (its maximum may still be -inf)
+            f32x16_t s[NB];
+            auto scores = [&] {
 #pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    if (key0 + crow(i, lane) >= n)
+                for (int b = 0; b < NB; ++b) s[b] = zero16();
 #pragma unroll
-                        for (int b = 0; b < NB; ++b) s[b][i] = kNegInf;
-            }
-            bool grow = false;
-            float mt[NB];
+                for (int c = 0; c < D / 16; ++c) {
+                    const bf16x8_t a = Tl::rows(cK, 32 * kb + (lane & 31), c, lane);
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                float mx = s[b][0];
+                    for (int b = 0; b < NB; ++b) s[b] = mma(a, qf[b].v[c], s[b]);
+                }
+                if (__builtin_expect(key0 + 32 > n, 0)) {  // ragged last block: partners >= n take no weight
+                    // kept as a branch (the empty asm stops the compiler from turning
+                    // it into selects on every block)
+                    asm volatile("" ::: "memory");
 #pragma unroll
-                for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[b][i]);
-                mt[b] = pair_max(mx) * sl2;
-                grow |= mt[b] > m[b] + kLazy;
-            }
-            if (__builtin_amdgcn_ballot_w64(grow)) {
+                    for (int i = 0; i < 16; ++i)
+                        if (key0 + crow(i, lane) >= n)
+#pragma unroll
+                            for (int b = 0; b < NB; ++b) s[b][i] = kNegInf;
+                }
+            };
+            float ls[NB];
+            auto weights = [&] {  // s becomes the weights, ls this lane's sums of them
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
-                    const float mn = fmaxf(m[b], mt[b]);
+                    float x[2] = {0.f, 0.f};
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const float p = ex2(fmaf(s[b][i], sl2, -m[b]));
+                        s[b][i] = p;
+                        x[i & 1] += p;
+                    }
+                    ls[b] = x[0] + x[1];
+                }
+            };
+            scores();
+            bf16x8_t vt[D / 32][2];
+#pragma unroll
+            for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+                for (int half = 0; half < 2; ++half) vt[db][half] = Tl::cols(cV, db, 32 * kb + 16 * half, lane);
+            __builtin_amdgcn_sched_barrier(0);
+            weights();
+            bool high = false;
+#pragma unroll
+            for (int b = 0; b < NB; ++b) high |= !(ls[b] <= 256.f);
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(high) != 0, 0)) {
+                scores();
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    float mx = s[b][0];
+#pragma unroll
+                    for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[b][i]);
+                    const float mn = fmaxf(m[b], pair_max(mx) * sl2);
                     const float alpha = ex2(m[b] - mn);
                     l[b] *= alpha;
 #pragma unroll
@@ -328,18 +430,12 @@ __global__ __launch_bounds__(kRowsWg / (32 * NB) * kWave) __attribute__((amdgpu_
                         for (int i = 0; i < 16; ++i) acc[b][db][i] *= alpha;
                     m[b] = mn;
                 }
+                weights();
             }
             bf16x8_t pb[NB][2];
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-                float ls = 0.f;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const float p = ex2(fmaf(s[b][i], sl2, -m[b]));
-                    s[b][i] = p;
-                    ls += p;
-                }
-                l[b] += ls;
+                l[b] += ls[b];
                 pb[b][0] = acc_b16(s[b], 0);
                 pb[b][1] = acc_b16(s[b], 1);
             }
@@ -347,16 +443,47 @@ __global__ __launch_bounds__(kRowsWg / (32 * NB) * kWave) __attribute__((amdgpu_
             for (int db = 0; db < D / 32; ++db)
 #pragma unroll
                 for (int half = 0; half < 2; ++half) {
-                    const bf16x8_t a = lds_perm8(v_s, 32 * db + (lane & 31), 32 * kb + 16 * half, lane);
-                    #pragma unroll
+                    const bf16x8_t a = vt[db][half];
+#pragma unroll
                     for (int b = 0; b < NB; ++b) acc[b][db] = mma(a, pb[b][half], acc[b][db]);
                 }
         }
-        if (t + 1 < stages) {
-            gk.store_rm(sK[buf ^ 1]);
-            gv.store_tr(sVt[buf ^ 1]);
+        stage_done();
+    };
+    for (int64_t t = 0; t < stages; t += 2) {
+        stage(t, sK0, sV0, sK1, sV1);
+        if (t + 1 < stages) stage(t + 1, sK1, sV1, sK0, sV0);
+    }
+    if constexpr (KS == 2) {  // the second share's states to the first's wavefronts
+        __shared__ float s_x[NB * (16 * (D / 32) + 2)][WAVES * kWave];
+        const int at = int(threadIdx.x) % (WAVES * kWave);
+        if (part == 1) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                float(*x)[WAVES * kWave] = s_x + b * (16 * (D / 32) + 2);
+                x[0][at] = m[b];
+                x[1][at] = l[b];
+#pragma unroll
+                for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) x[2 + 16 * db + i][at] = acc[b][db][i];
+            }
         }
         __syncthreads();
+        if (part == 1) return;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const float(*x)[WAVES * kWave] = s_x + b * (16 * (D / 32) + 2);
+            // a share without partners (n <= 32) leaves m = -inf and l = 0
+            const float mo = x[0][at], mn = fmaxf(m[b], mo);
+            const float w0 = ex2(m[b] - mn), w1 = ex2(mo - mn);
+            m[b] = mn;
+            l[b] = fmaf(x[1][at], w1, l[b] * w0);
+#pragma unroll
+            for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[b][db][i] = fmaf(x[2 + 16 * db + i][at], w1, acc[b][db][i] * w0);
+        }
     }
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
@@ -365,41 +492,36 @@ __global__ __launch_bounds__(kRowsWg / (32 * NB) * kWave) __attribute__((amdgpu_
         if (q >= n) continue;
         const float inv = lt > 0.f ? 1.f / lt : 0.f;
         if (lane < 32) LSE[q * H + h] = lt > 0.f ? (m[b] + __log2f(lt)) * kLn2 : kNegInf;
-        uint16_t* o = O + (q * H + h) * D;
-#pragma unroll
-        for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const f32x16_t& a = acc[b][db];
-                *reinterpret_cast<uint2*>(o + 32 * db + 8 * j + 4 * (lane >> 5)) =
-                    make_uint2(pack_bf16x2(a[4 * j] * inv, a[4 * j + 1] * inv),
-                               pack_bf16x2(a[4 * j + 2] * inv, a[4 * j + 3] * inv));
-            }
+        store_acc<D>(O + (q * H + h) * D, acc[b], inv, lane);
     }
 }
 
 // ---------------------------------------------------------------- dQ (rows)
 // dQ_i = scale sum_j P_ij (dP_ij - D_i) K_j with dP_ij = <dO_i, V_j>; also
-// writes D_i for the column pass.
+// writes D_i for the column pass.  The dP products start from -D_i, so their
+// sum is dP - D with no subtraction.
 
-template <int D, int NB>
-__global__ __launch_bounds__(kRowsWg / (32 * NB) * kWave) __attribute__((amdgpu_waves_per_eu(NB == 1 ? 2 : 1))) void k_full_dq(int64_t n, int H, const uint16_t* __restrict__ Q,
-                                                     const uint16_t* __restrict__ K,
-                                                     const uint16_t* __restrict__ V,
-                                                     const uint16_t* __restrict__ O,
-                                                     const uint16_t* __restrict__ dO,
-                                                     const float* __restrict__ LSE, float sl2, float scale,
-                                                     uint16_t* __restrict__ dQ, float* __restrict__ Dv) {
-    __shared__ __attribute__((aligned(16))) uint16_t sK[2][kStage * RS<D>::v];
-    __shared__ __attribute__((aligned(16))) uint16_t sV[2][kStage * RS<D>::v];
-    __shared__ __attribute__((aligned(16))) uint16_t sKt[2][D * kTS];
+template <int D, int NB, int WAVES, int KS>
+__global__ __launch_bounds__(WAVES * KS * kWave) __attribute__((amdgpu_waves_per_eu(2))) void k_full_dq(
+    int64_t n, int H, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
+    const uint16_t* __restrict__ O, const uint16_t* __restrict__ dO, const float* __restrict__ LSE, float sl2,
+    float scale, uint16_t* __restrict__ dQ, float* __restrict__ Dv) {
+    using Tl = Tile<D>;
+    // one variable per buffer: the compiler then knows that a stage's reads do
+    // not touch the buffer being filled, and does not wait for its loads
+    __shared__ __attribute__((aligned(16))) uint16_t sK0[Tl::kElems], sK1[Tl::kElems];
+    __shared__ __attribute__((aligned(16))) uint16_t sV0[Tl::kElems], sV1[Tl::kElems];
     int h;
     int64_t row0;
-    if (!wg_coords(n, H, h, row0)) return;
-    const int lane = lane_id();
-    const int64_t q0 = row0 + (threadIdx.x / kWave) * 32 * NB;
+    if (!wg_coords<32 * NB * WAVES>(n, H, h, row0)) return;
+    const int lane = lane_id(), wave = uniform(int(threadIdx.x) / kWave);
+    const int part = KS == 1 ? 0 : wave / WAVES;  // which of a stage's KS shares of the partners
+    const int64_t q0 = row0 + (wave - part * WAVES) * 32 * NB;
+    Tl::template fetch<WAVES * KS>(sK0, K, 0, n, H, h, wave, lane);
+    Tl::template fetch<WAVES * KS>(sV0, V, 0, n, H, h, wave, lane);
     Frag<D> qf[NB], gf[NB];
-    float lse2[NB], Dq[NB];
+    float lse2[NB];
+    f32x16_t nD[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         const int64_t q = q0 + 32 * b + (lane & 31);
@@ -407,65 +529,63 @@ __global__ __launch_bounds__(kRowsWg / (32 * NB) * kWave) __attribute__((amdgpu_
         gf[b].load(dO, q, n, H, h, lane);
         Frag<D> of;
         of.load(O, q, n, H, h, lane);
-        Dq[b] = pair_sum(gf[b].dot(of));
+        const float Dq = pair_sum(gf[b].dot(of));
         lse2[b] = q < n ? LSE[q * H + h] * kLog2e : 0.f;
-        if (q < n && lane < 32) Dv[q * H + h] = Dq[b];
+        if (q < n && lane < 32) Dv[q * H + h] = Dq;
+        nD[b] = splat16(-Dq);
     }
     f32x16_t acc[NB][D / 32];
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int db = 0; db < D / 32; ++db) acc[b][db] = zero16();
-
-    Stager<D, kRowsWg / (32 * NB) * kWave> gk, gv;
-    gk.load(K, 0, n, H, h);
-    gv.load(V, 0, n, H, h);
-    gk.store_rm(sK[0]);
-    gk.store_tr(sKt[0]);
-    gv.store_rm(sV[0]);
-    drain();
-    __syncthreads();
+    stage_done();
     const int64_t stages = cdiv(n, kStage);
-    for (int64_t t = 0; t < stages; ++t) {
-        const int buf = int(t & 1);
+    auto stage = [&](int64_t t, const uint16_t* cK, const uint16_t* cV, uint16_t* nK, uint16_t* nV) {
         const int64_t kbase = t * kStage;
         if (t + 1 < stages) {
-            gk.load_any(K, kbase + kStage, n, H, h);
-            gv.load_any(V, kbase + kStage, n, H, h);
+            Tl::template fetch<WAVES * KS>(nK, K, kbase + kStage, n, H, h, wave, lane);
+            Tl::template fetch<WAVES * KS>(nV, V, kbase + kStage, n, H, h, wave, lane);
         }
 #pragma unroll
-        for (int kb = 0; kb < kStage / 32; ++kb) {
+        for (int kx = 0; kx < kStage / 32 / KS; ++kx) {
+            const int kb = kx + part * (kStage / 32 / KS);
             f32x16_t s[NB], dp[NB];
-            #pragma unroll
-            for (int b = 0; b < NB; ++b) s[b] = dp[b] = zero16();
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                s[b] = zero16();
+                dp[b] = nD[b];
+            }
 #pragma unroll
             for (int c = 0; c < D / 16; ++c) {
-                const bf16x8_t a = lds_row8<D>(sK[buf], 32 * kb + (lane & 31), c, lane);
-                #pragma unroll
-                for (int b = 0; b < NB; ++b) s[b] = mma(a, qf[b].v[c], s[b]);
-                const bf16x8_t v = lds_row8<D>(sV[buf], 32 * kb + (lane & 31), c, lane);
-                #pragma unroll
-                for (int b = 0; b < NB; ++b) dp[b] = mma(v, gf[b].v[c], dp[b]);
+                const bf16x8_t a = Tl::rows(cK, 32 * kb + (lane & 31), c, lane);
+                const bf16x8_t v = Tl::rows(cV, 32 * kb + (lane & 31), c, lane);
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    s[b] = mma(a, qf[b].v[c], s[b]);
+                    dp[b] = mma(v, gf[b].v[c], dp[b]);
+                }
             }
             const int64_t key0 = kbase + 32 * kb;
-            // ragged last block; marked unlikely so that the compiler keeps the masking
-            // out of the other blocks (measured: the backward 1.4% faster, the
-            // forward no faster)
-            if (__builtin_expect(key0 + 32 > n, 0)) {
+            if (__builtin_expect(key0 + 32 > n, 0)) {  // ragged last block
+                asm volatile("" ::: "memory");
 #pragma unroll
                 for (int i = 0; i < 16; ++i)
                     if (key0 + crow(i, lane) >= n)
 #pragma unroll
                         for (int b = 0; b < NB; ++b) s[b][i] = kNegInf;
             }
+            bf16x8_t kt[D / 32][2];
+#pragma unroll
+            for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+                for (int half = 0; half < 2; ++half) kt[db][half] = Tl::cols(cK, db, 32 * kb + 16 * half, lane);
+            __builtin_amdgcn_sched_barrier(0);
             bf16x8_t db16[NB][2];
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const float p = ex2(fmaf(s[b][i], sl2, -lse2[b]));
-                    s[b][i] = p * (dp[b][i] - Dq[b]);
-                }
+                for (int i = 0; i < 16; ++i) s[b][i] = ex2(fmaf(s[b][i], sl2, -lse2[b])) * dp[b][i];
                 db16[b][0] = acc_b16(s[b], 0);
                 db16[b][1] = acc_b16(s[b], 1);
             }
@@ -473,58 +593,68 @@ __global__ __launch_bounds__(kRowsWg / (32 * NB) * kWave) __attribute__((amdgpu_
             for (int db = 0; db < D / 32; ++db)
 #pragma unroll
                 for (int half = 0; half < 2; ++half) {
-                    const bf16x8_t a = lds_perm8(sKt[buf], 32 * db + (lane & 31), 32 * kb + 16 * half, lane);
-                    #pragma unroll
+                    const bf16x8_t a = kt[db][half];
+#pragma unroll
                     for (int b = 0; b < NB; ++b) acc[b][db] = mma(a, db16[b][half], acc[b][db]);
                 }
         }
-        if (t + 1 < stages) {
-            gk.store_rm(sK[buf ^ 1]);
-            gk.store_tr(sKt[buf ^ 1]);
-            gv.store_rm(sV[buf ^ 1]);
-        }
-        __syncthreads();
+        stage_done();
+    };
+    for (int64_t t = 0; t < stages; t += 2) {
+        stage(t, sK0, sV0, sK1, sV1);
+        if (t + 1 < stages) stage(t + 1, sK1, sV1, sK0, sV0);
     }
+    if (!add_shares<KS, WAVES, NB * (D / 32)>(&acc[0][0], part)) return;
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         const int64_t q = q0 + 32 * b + (lane & 31);
-        if (q >= n) continue;
-        uint16_t* o = dQ + (q * H + h) * D;
-#pragma unroll
-        for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const f32x16_t& a = acc[b][db];
-                *reinterpret_cast<uint2*>(o + 32 * db + 8 * j + 4 * (lane >> 5)) =
-                    make_uint2(pack_bf16x2(a[4 * j] * scale, a[4 * j + 1] * scale),
-                               pack_bf16x2(a[4 * j + 2] * scale, a[4 * j + 3] * scale));
-            }
+        if (q < n) store_acc<D>(dQ + (q * H + h) * D, acc[b], scale, lane);
     }
 }
 
 // ----------------------------------------------------------- dK, dV (cols)
 // dK_j = scale sum_i P_ij (dP_ij - D_i) Q_i and dV_j = sum_i P_ij dO_i, with
-// the wavefront owning 32 NB keys and the queries streaming through LDS.
+// the wavefront owning 32 NB keys and the queries streaming through LDS; the dP
+// products start from the queries' -D_i.
 
-template <int D, int NB>
-__global__ __launch_bounds__(kRowsWg / (32 * NB) * kWave) __attribute__((amdgpu_waves_per_eu(NB == 1 ? 2 : 1))) void k_full_dkdv(int64_t n, int H, const uint16_t* __restrict__ Q,
-                                                       const uint16_t* __restrict__ K,
-                                                       const uint16_t* __restrict__ V,
-                                                       const uint16_t* __restrict__ dO,
-                                                       const float* __restrict__ LSE,
-                                                       const float* __restrict__ Dv, float sl2, float scale,
-                                                       uint16_t* __restrict__ dK, uint16_t* __restrict__ dV) {
-    __shared__ __attribute__((aligned(16))) uint16_t sQ[2][kStage * RS<D>::v];
-    __shared__ __attribute__((aligned(16))) uint16_t sG[2][kStage * RS<D>::v];
-    __shared__ __attribute__((aligned(16))) uint16_t sQt[2][D * kTS];
-    __shared__ __attribute__((aligned(16))) uint16_t sGt[2][D * kTS];
-    __shared__ __attribute__((aligned(16))) float sL[2][kStage];
-    __shared__ __attribute__((aligned(16))) float sD[2][kStage];
+template <int D, int NB, int WAVES, int KS>
+__global__ __launch_bounds__(WAVES * KS * kWave) __attribute__((amdgpu_waves_per_eu(2))) void k_full_dkdv(
+    int64_t n, int H, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
+    const uint16_t* __restrict__ dO, const float* __restrict__ LSE, const float* __restrict__ Dv, float sl2,
+    float scale, uint16_t* __restrict__ dK, uint16_t* __restrict__ dV) {
+    using Tl = Tile<D>;
+    // one variable per buffer: the compiler then knows that a stage's reads do
+    // not touch the buffer being filled, and does not wait for its loads
+    __shared__ __attribute__((aligned(16))) uint16_t sQ0[Tl::kElems], sQ1[Tl::kElems];
+    __shared__ __attribute__((aligned(16))) uint16_t sG0[Tl::kElems], sG1[Tl::kElems];
+    __shared__ __attribute__((aligned(16))) float sL0[kStage], sL1[kStage];
+    __shared__ __attribute__((aligned(16))) float sD0[kStage], sD1[kStage];
     int h;
     int64_t row0;
-    if (!wg_coords(n, H, h, row0)) return;
-    const int lane = lane_id();
-    const int64_t k0 = row0 + (threadIdx.x / kWave) * 32 * NB;
+    if (!wg_coords<32 * NB * WAVES>(n, H, h, row0)) return;
+    const int lane = lane_id(), wave = uniform(int(threadIdx.x) / kWave);
+    const int part = KS == 1 ? 0 : wave / WAVES;  // which of a stage's KS shares of the queries
+    const int64_t k0 = row0 + (wave - part * WAVES) * 32 * NB;
+    // LSE (exp2 domain) and -D of the stage's queries, loaded a stage ahead by the
+    // first wavefront and stored at the stage's end; queries >= n get
+    // LSE = +inf so that their weights are exactly zero.
+    float rl = 0.f, rd = 0.f;
+    auto load_rows = [&](int64_t base) {
+        if (wave == 0) {
+            const int64_t qn = base + lane;
+            rl = qn < n ? LSE[qn * H + h] * kLog2e : __builtin_huge_valf();
+            rd = qn < n ? -Dv[qn * H + h] : 0.f;
+        }
+    };
+    auto store_rows = [&](float* toL, float* toD) {
+        if (wave == 0) {
+            toL[lane] = rl;
+            toD[lane] = rd;
+        }
+    };
+    load_rows(0);
+    Tl::template fetch<WAVES * KS>(sQ0, Q, 0, n, H, h, wave, lane);
+    Tl::template fetch<WAVES * KS>(sG0, dO, 0, n, H, h, wave, lane);
     Frag<D> kf[NB], vf[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
@@ -536,112 +666,99 @@ __global__ __launch_bounds__(kRowsWg / (32 * NB) * kWave) __attribute__((amdgpu_
     for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int db = 0; db < D / 32; ++db) dk[b][db] = dv[b][db] = zero16();
-
-    // LSE (exp2 domain) and D of the stage's queries; queries >= n get
-    // LSE = +inf so that their weights are exactly zero.
-    auto stage_rows = [&](int buf, int64_t base) {
-        if (threadIdx.x < kStage) {
-            const int64_t qn = base + threadIdx.x;
-            sL[buf][threadIdx.x] = qn < n ? LSE[qn * H + h] * kLog2e : __builtin_huge_valf();
-            sD[buf][threadIdx.x] = qn < n ? Dv[qn * H + h] : 0.f;
-        }
-    };
-    Stager<D, kRowsWg / (32 * NB) * kWave> gq, gg;
-    gq.load(Q, 0, n, H, h);
-    gg.load(dO, 0, n, H, h);
-    gq.store_rm(sQ[0]);
-    gq.store_tr(sQt[0]);
-    gg.store_rm(sG[0]);
-    gg.store_tr(sGt[0]);
-    stage_rows(0, 0);
-    drain();
-    __syncthreads();
+    store_rows(sL0, sD0);
+    stage_done();
     const int64_t stages = cdiv(n, kStage);
-    for (int64_t t = 0; t < stages; ++t) {
-        const int buf = int(t & 1);
+    auto stage = [&](int64_t t, const uint16_t* cQ, const uint16_t* cG, uint16_t* nQ, uint16_t* nG, const float* cL, const float* cD, float* nL,
+                     float* nD) {
         const int64_t qbase = t * kStage;
         if (t + 1 < stages) {
-            gq.load_any(Q, qbase + kStage, n, H, h);
-            gg.load_any(dO, qbase + kStage, n, H, h);
+            load_rows(qbase + kStage);
+            Tl::template fetch<WAVES * KS>(nQ, Q, qbase + kStage, n, H, h, wave, lane);
+            Tl::template fetch<WAVES * KS>(nG, dO, qbase + kStage, n, H, h, wave, lane);
         }
 #pragma unroll
-        for (int qb = 0; qb < kStage / 32; ++qb) {
-            f32x16_t s[NB], dp[NB];
-            #pragma unroll
-            for (int b = 0; b < NB; ++b) s[b] = dp[b] = zero16();
-#pragma unroll
-            for (int c = 0; c < D / 16; ++c) {
-                const bf16x8_t a = lds_row8<D>(sQ[buf], 32 * qb + (lane & 31), c, lane);
-                #pragma unroll
-                for (int b = 0; b < NB; ++b) s[b] = mma(a, kf[b].v[c], s[b]);
-                const bf16x8_t g = lds_row8<D>(sG[buf], 32 * qb + (lane & 31), c, lane);
-                #pragma unroll
-                for (int b = 0; b < NB; ++b) dp[b] = mma(g, vf[b].v[c], dp[b]);
-            }
+        for (int kx = 0; kx < kStage / 32 / KS; ++kx) {
+            const int qb = kx + part * (kStage / 32 / KS);
             // rows of accumulator element i: 32 qb + 8 (i/4) + 4 (lane/32) + i%4
-            float Lr[16], Dr[16];
+            f32x16_t s[NB], dp[NB], mD;
+            float Lr[16];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int r = 32 * qb + 8 * j + 4 * (lane >> 5);
-                const float4 lv = *reinterpret_cast<const float4*>(&sL[buf][r]);
-                const float4 dv4 = *reinterpret_cast<const float4*>(&sD[buf][r]);
+                const float4 lv = *reinterpret_cast<const float4*>(&cL[r]);
+                const float4 dv4 = *reinterpret_cast<const float4*>(&cD[r]);
                 Lr[4 * j] = lv.x, Lr[4 * j + 1] = lv.y, Lr[4 * j + 2] = lv.z, Lr[4 * j + 3] = lv.w;
-                Dr[4 * j] = dv4.x, Dr[4 * j + 1] = dv4.y, Dr[4 * j + 2] = dv4.z, Dr[4 * j + 3] = dv4.w;
+                mD[4 * j] = dv4.x, mD[4 * j + 1] = dv4.y, mD[4 * j + 2] = dv4.z, mD[4 * j + 3] = dv4.w;
             }
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                s[b] = zero16();
+                dp[b] = mD;
+            }
+#pragma unroll
+            for (int c = 0; c < D / 16; ++c) {
+                const bf16x8_t a = Tl::rows(cQ, 32 * qb + (lane & 31), c, lane);
+                const bf16x8_t g = Tl::rows(cG, 32 * qb + (lane & 31), c, lane);
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    s[b] = mma(a, kf[b].v[c], s[b]);
+                    dp[b] = mma(g, vf[b].v[c], dp[b]);
+                }
+            }
+            bf16x8_t gt_[D / 32][2], qt_[D / 32][2];
+#pragma unroll
+            for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+                for (int half = 0; half < 2; ++half) {
+                    gt_[db][half] = Tl::cols(cG, db, 32 * qb + 16 * half, lane);
+                    qt_[db][half] = Tl::cols(cQ, db, 32 * qb + 16 * half, lane);
+                }
+            __builtin_amdgcn_sched_barrier(0);
             bf16x8_t pb[NB][2], sb[NB][2];
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    const float p = ex2(fmaf(s[b][i], sl2, -Lr[i]));
-                    s[b][i] = p * (dp[b][i] - Dr[i]);
-                    dp[b][i] = p;
+                    s[b][i] = ex2(fmaf(s[b][i], sl2, -Lr[i]));
+                    dp[b][i] *= s[b][i];
                 }
-                pb[b][0] = acc_b16(dp[b], 0);
-                pb[b][1] = acc_b16(dp[b], 1);
-                sb[b][0] = acc_b16(s[b], 0);
-                sb[b][1] = acc_b16(s[b], 1);
+                pb[b][0] = acc_b16(s[b], 0);
+                pb[b][1] = acc_b16(s[b], 1);
+                sb[b][0] = acc_b16(dp[b], 0);
+                sb[b][1] = acc_b16(dp[b], 1);
             }
 #pragma unroll
             for (int db = 0; db < D / 32; ++db)
 #pragma unroll
                 for (int half = 0; half < 2; ++half) {
-                    const bf16x8_t g = lds_perm8(sGt[buf], 32 * db + (lane & 31), 32 * qb + 16 * half, lane);
-                    #pragma unroll
-                    for (int b = 0; b < NB; ++b) dv[b][db] = mma(g, pb[b][half], dv[b][db]);
-                    const bf16x8_t a = lds_perm8(sQt[buf], 32 * db + (lane & 31), 32 * qb + 16 * half, lane);
-                    #pragma unroll
-                    for (int b = 0; b < NB; ++b) dk[b][db] = mma(a, sb[b][half], dk[b][db]);
+                    const bf16x8_t g = gt_[db][half];
+                    const bf16x8_t a = qt_[db][half];
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+                        dv[b][db] = mma(g, pb[b][half], dv[b][db]);
+                        dk[b][db] = mma(a, sb[b][half], dk[b][db]);
+                    }
                 }
         }
-        if (t + 1 < stages) {
-            gq.store_rm(sQ[buf ^ 1]);
-            gq.store_tr(sQt[buf ^ 1]);
-            gg.store_rm(sG[buf ^ 1]);
-            gg.store_tr(sGt[buf ^ 1]);
-            stage_rows(buf ^ 1, qbase + kStage);
-        }
+        if (t + 1 < stages) store_rows(nL, nD);
+        stage_done();
+    };
+    for (int64_t t = 0; t < stages; t += 2) {
+        stage(t, sQ0, sG0, sQ1, sG1, sL0, sD0, sL1, sD1);
+        if (t + 1 < stages) stage(t + 1, sQ1, sG1, sQ0, sG0, sL1, sD1, sL0, sD0);
+    }
+    if constexpr (KS > 1) {
+        add_shares<KS, WAVES, NB * (D / 32)>(&dk[0][0], part);
         __syncthreads();
+        if (!add_shares<KS, WAVES, NB * (D / 32)>(&dv[0][0], part)) return;
     }
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         const int64_t key = k0 + 32 * b + (lane & 31);
         if (key >= n) continue;
-        uint16_t* ok = dK + (key * H + h) * D;
-        uint16_t* ov = dV + (key * H + h) * D;
-#pragma unroll
-        for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int f = 32 * db + 8 * j + 4 * (lane >> 5);
-                const f32x16_t& a = dk[b][db];
-                const f32x16_t& c = dv[b][db];
-                *reinterpret_cast<uint2*>(ok + f) =
-                    make_uint2(pack_bf16x2(a[4 * j] * scale, a[4 * j + 1] * scale),
-                               pack_bf16x2(a[4 * j + 2] * scale, a[4 * j + 3] * scale));
-                *reinterpret_cast<uint2*>(ov + f) =
-                    make_uint2(pack_bf16x2(c[4 * j], c[4 * j + 1]), pack_bf16x2(c[4 * j + 2], c[4 * j + 3]));
-            }
+        store_acc<D>(dK + (key * H + h) * D, dk[b], scale, lane);
+        store_acc<D>(dV + (key * H + h) * D, dv[b], 1.f, lane);
     }
 }
 
@@ -1429,11 +1546,35 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB =
 
 }  // namespace
 
+// How the full layer is cut, by the (head, 128 rows) blocks it has for the 256
+// CUs.  W wavefronts of NB 32-row blocks share a workgroup's rows; with KS = 2 a
+// second set of wavefronts takes half of every stage's partners.  Measured at
+// d = 64 (forward / backward, us), W x NB x KS:
+//   1,000 x 4 (32 blocks):   2x1x2 15 / 37    4x1x2 17 / 44     4x1x1 20 / 54
+//   3,001 x 8 (192 blocks):  2x1x2 46 / 119   4x1x2 41 / 110    4x1x1 51 / 145
+//   6,000 x 8 (376 blocks):  2x1x2 115 / 386  4x1x2 140 / 386   4x1x1 136 / 385   8x1x1 - / 348   2x2x2 126 / -
+//   16,384 x 8 (1,024):      2x1x2 766 / 2179 4x2x1 600 / -     8x1x1 - / 1808
+enum class FullShape { narrow, shared, some, many };
+inline FullShape full_shape(int64_t n, int H) {
+    const int64_t blocks = cdiv(n, 128) * H;
+    return blocks <= 128 ? FullShape::narrow
+           : blocks <= 256 ? FullShape::shared
+           : blocks <= 512 ? FullShape::some
+                           : FullShape::many;
+}
+
 template <int D>
 gt_status full_fwd_bf16(int64_t n, int H, const uint16_t* Q, const uint16_t* K, const uint16_t* V, float sl2,
                         uint16_t* O, float* LSE, hipStream_t s) {
     if (n <= 0) return GT_OK;
-    k_full_fwd<D, kFullFwdNB><<<full_grid(n, H), kFullFwdThr, 0, s>>>(n, H, Q, K, V, sl2, O, LSE);
+    const FullShape f = full_shape(n, H);
+#define GT_FULL_FWD(NB, W, KS) \
+    k_full_fwd<D, NB, W, KS><<<full_grid<32 * NB * W>(n, H), W * KS * kWave, 0, s>>>(n, H, Q, K, V, sl2, O, LSE)
+    if (f == FullShape::narrow) GT_FULL_FWD(1, 2, 2);
+    else if (f == FullShape::shared) GT_FULL_FWD(1, 4, 2);
+    else if (f == FullShape::some) GT_FULL_FWD(1, 2, 2);
+    else GT_FULL_FWD(2, 4, 1);
+#undef GT_FULL_FWD
     GT_LAUNCH_CHECK("full_fwd_bf16");
     return GT_OK;
 }
@@ -1443,9 +1584,19 @@ gt_status full_bwd_bf16(int64_t n, int H, const uint16_t* Q, const uint16_t* K, 
                         const uint16_t* O, const uint16_t* dO, const float* LSE, float sl2, float scale,
                         uint16_t* dQ, uint16_t* dK, uint16_t* dV, float* Dv, hipStream_t s) {
     if (n <= 0) return GT_OK;
-    k_full_dq<D, kFullBwdNB><<<full_grid(n, H), kFullBwdThr, 0, s>>>(n, H, Q, K, V, O, dO, LSE, sl2, scale, dQ, Dv);
-    GT_LAUNCH_CHECK("full_bwd_bf16 dq");
-    k_full_dkdv<D, kFullBwdNB><<<full_grid(n, H), kFullBwdThr, 0, s>>>(n, H, Q, K, V, dO, LSE, Dv, sl2, scale, dK, dV);
+    const FullShape f = full_shape(n, H);
+#define GT_FULL_BWD(W, KS)                                                                                       \
+    do {                                                                                                         \
+        k_full_dq<D, 1, W, KS><<<full_grid<32 * W>(n, H), W * KS * kWave, 0, s>>>(n, H, Q, K, V, O, dO, LSE, sl2, \
+                                                                                  scale, dQ, Dv);                \
+        GT_LAUNCH_CHECK("full_bwd_bf16 dq");                                                                     \
+        k_full_dkdv<D, 1, W, KS><<<full_grid<32 * W>(n, H), W * KS * kWave, 0, s>>>(n, H, Q, K, V, dO, LSE, Dv,  \
+                                                                                    sl2, scale, dK, dV);         \
+    } while (0)
+    if (f == FullShape::narrow) GT_FULL_BWD(2, 2);
+    else if (f == FullShape::shared) GT_FULL_BWD(4, 2);
+    else GT_FULL_BWD(8, 1);
+#undef GT_FULL_BWD
     GT_LAUNCH_CHECK("full_bwd_bf16 dkdv");
     return GT_OK;
 }

@@ -16,8 +16,7 @@
 //     v_permlane32_swap between the half-waves.  The probabilities (or dS)
 //     become the next product's B operand straight from the accumulators; the
 //     A operand of that product (V^T, K^T, dO^T, Q^T) is read from the
-//     row-major copy by transposing LDS reads (the dense tiles: from a transposed
-//     LDS copy written as 4-partner x 4-feature blocks).
+//     row-major copy by transposing LDS reads.
 //   - The forward's running maximum is lazy: the accumulators are rescaled only
 //     when weights reach 2^8, so weights stay below 256 and the result is
 //     unchanged.
@@ -38,14 +37,8 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 constexpr int kStage = 64;               // partner rows per LDS stage
-constexpr int kTS = kStage + 4;          // transposed LDS row stride (elements)
 constexpr float kNegInf = -__builtin_huge_valf();
 constexpr float kLazy = 8.f;             // lazy-max slack, exp2 domain
-
-template <int D>
-struct RS {
-    static constexpr int v = D + 8;  // row-major LDS row stride (elements)
-};
 
 __device__ __forceinline__ int crow(int i, int lane) { return 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3); }
 
@@ -76,21 +69,6 @@ __device__ __forceinline__ float pair_sum(float x) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// A operand from a row-major LDS tile: row r, features 16c + 8(lane/32) .. +7.
-template <int D>
-__device__ __forceinline__ bf16x8_t lds_row8(const uint16_t* s, int r, int c, int lane) {
-    return __builtin_bit_cast(bf16x8_t,
-                              *reinterpret_cast<const uint4*>(s + r * RS<D>::v + 16 * c + 8 * (lane >> 5)));
-}
-// A operand from a transposed LDS tile (row = feature f): partners
-// base + 4(lane/32) + {0..3} and base + 8 + 4(lane/32) + {0..3}, the partner
-// order of an accumulator-layout B operand (acc_b16).
-__device__ __forceinline__ bf16x8_t lds_perm8(const uint16_t* s, int f, int base, int lane) {
-    const uint16_t* p = s + f * kTS + base + 4 * (lane >> 5);
-    const uint2 a = *reinterpret_cast<const uint2*>(p);
-    const uint2 b = *reinterpret_cast<const uint2*>(p + 8);
-    return __builtin_bit_cast(bf16x8_t, make_uint4(a.x, a.y, b.x, b.y));
-}
 // Accumulator elements 8*half .. +7 as a bf16 B operand.
 __device__ __forceinline__ bf16x8_t acc_b16(const f32x16_t& c, int half) {
     bf16x8_t o;
@@ -124,73 +102,7 @@ struct Frag {
     }
 };
 
-// One thread's share of a 64-row stage of X[:, h, :] for a workgroup of NT
-// threads: blocks of 4 rows x 4 features (8 bytes per row), kept in registers
-// between the global load and the LDS stores.  Loads are unconditional (rows
-// past n read row n-1) so the compiler can keep them in flight across the
-// stage's products; rows >= n are zeroed when stored.
-template <int D, int NT>
-struct Stager {
-    static constexpr int FG = D / 4;                        // feature groups per row
-    static constexpr int kItems = 16 * FG;                  // (row group, feature group) blocks
-    static constexpr int PER = kItems >= NT ? kItems / NT : 1;
-    static_assert(kItems >= NT ? kItems % NT == 0 : NT % kItems == 0, "stage does not fit the workgroup");
-    uint2 r[PER][4];
-    uint32_t valid;  // bit 4k + j: row j of block k is below n
-    // Threads beyond kItems (whole wavefronts) only mirror the loads.
-    __device__ __forceinline__ static bool on() { return kItems >= NT || threadIdx.x < kItems; }
-    __device__ __forceinline__ static int item(int k) {
-        return kItems >= NT ? int(threadIdx.x) + k * NT : int(threadIdx.x) % kItems;
-    }
-    __device__ __forceinline__ void load(const uint16_t* __restrict__ X, int64_t base, int64_t n, int H, int h) {
-        valid = 0;
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int it = item(k), rg = it / FG, fg = it % FG;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int64_t node = base + 4 * rg + j;
-                const int64_t src = node < n ? node : n - 1;
-                valid |= uint32_t(node < n) << (4 * k + j);
-                r[k][j] = *reinterpret_cast<const uint2*>(X + (src * H + h) * D + 4 * fg);
-            }
-        }
-    }
-    __device__ __forceinline__ uint2 row(int k, int j) const {
-        return (valid >> (4 * k + j)) & 1u ? r[k][j] : make_uint2(0, 0);
-    }
-    __device__ __forceinline__ void store_rm(uint16_t* s) const {
-        if (!on()) return;
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int it = item(k), rg = it / FG, fg = it % FG;
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                *reinterpret_cast<uint2*>(s + (4 * rg + j) * RS<D>::v + 4 * fg) = row(k, j);
-        }
-    }
-    // s[f * kTS + row]: the 4 rows of each of the 4 features as one 8-byte store.
-    __device__ __forceinline__ void store_tr(uint16_t* s) const {
-        if (!on()) return;
-        const uint32_t lo = 0xFFFFu, hi = 0xFFFF0000u;
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int it = item(k), rg = it / FG, fg = it % FG;
-            const uint2 a = row(k, 0), b = row(k, 1), c = row(k, 2), d = row(k, 3);
-            uint16_t* p = s + (4 * fg) * kTS + 4 * rg;
-            *reinterpret_cast<uint2*>(p) = make_uint2((a.x & lo) | (b.x << 16), (c.x & lo) | (d.x << 16));
-            *reinterpret_cast<uint2*>(p + kTS) = make_uint2((a.x >> 16) | (b.x & hi), (c.x >> 16) | (d.x & hi));
-            *reinterpret_cast<uint2*>(p + 2 * kTS) = make_uint2((a.y & lo) | (b.y << 16), (c.y & lo) | (d.y << 16));
-            *reinterpret_cast<uint2*>(p + 3 * kTS) = make_uint2((a.y >> 16) | (b.y & hi), (c.y >> 16) | (d.y & hi));
-        }
-    }
-};
-
-// All outstanding memory operations of this wavefront are complete (so the
-// compiler's wait counting starts the streaming loop from a clean state).
-__device__ __forceinline__ void drain() { __builtin_amdgcn_s_waitcnt(0); }
-
-// ------------------------------------------------------------- full layer
+// --------------------------------------------------------- staged operands
 // Partner rows are staged 64 at a time by loads that write LDS directly (no
 // registers, no stores), one row-major copy of each operand, double buffered:
 // the next stage's loads are issued before the current one is multiplied.  A
@@ -1035,8 +947,10 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(D >=
                                                  float* __restrict__ pl, float* __restrict__ pacc, int64_t R,
                                                  TileChunks ck, TileBias tb) {
     constexpr int W = T / 32;
-    __shared__ __attribute__((aligned(16))) uint16_t sK[1][kStage * RS<D>::v];
-    __shared__ __attribute__((aligned(16))) uint16_t sVt[1][D * kTS];
+    using Tl = Tile<D>;
+    constexpr int kWaves = T / (32 * NB);
+    __shared__ __attribute__((aligned(16))) uint16_t sK0[Tl::kElems], sK1[Tl::kElems];
+    __shared__ __attribute__((aligned(16))) uint16_t sV0[Tl::kElems], sV1[Tl::kElems];
     const int h = blockIdx.y;
     int64_t I, t0, t1, slot;
     if (!tile_chunk(ck, tile_rowptr, R, blockIdx.x, I, t0, t1, slot)) return;
@@ -1045,8 +959,7 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(D >=
         pl = ck.l;
         pacc = ck.acc;
     }
-    const int lane = lane_id();
-    constexpr int NT = T * 2 / NB;
+    const int lane = lane_id(), wave = uniform(int(threadIdx.x) / kWave);
     const int ql0 = (threadIdx.x / kWave) * 32 * NB;  // first owned row inside the tile row
     const int64_t q0 = int64_t(I) * T + ql0;
     Frag<D> qf[NB];
@@ -1071,31 +984,33 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(D >=
         m[b] = kNegInf;
         l[b] = 0.f;
     }
-    // Stages run over the tile row's dense tiles, T/64 per tile.  They are
-    // single-buffered: several small workgroups per CU hide each other's
-    // loads, which a register prefetch (at one wavefront per SIMD) did not.
+    // Stages run over the chunk's dense tiles, T/64 per tile; a stage's rows (and
+    // a tile's mask words) are on their way while the one before is multiplied.
     constexpr int NSG = T / kStage;
     const int64_t stages = (t1 - t0) * NSG;
-    Stager<D, NT> gk, gv;
-    uint32_t mw[NB][W];
-    auto fetch = [&](int64_t g, uint32_t (&mwx)[NB][W]) {
-        const int64_t k = t0 + g / NSG;
-        const int64_t kb = int64_t(tile_col[k]) * T + kStage * (g % NSG);
-        gk.load(K, kb, n, H, h);
-        gv.load(V, kb, n, H, h);
-        if (g % NSG == 0)
+    uint32_t mw[NB][W], mwn[NB][W];
+    int cols = 0;  // tile columns of 64 tiles, one per lane
+    int64_t kcol = 0;
+    auto prefetch = [&](int64_t g, uint16_t* nK, uint16_t* nV) {
+        const int64_t j = g / NSG, k = t0 + j;
+        if (g % NSG == 0) {
+            if (j % kWave == 0) cols = k + lane < t1 ? tile_col[k + lane] : 0;
+            kcol = int64_t(__builtin_amdgcn_readlane(cols, int(j % kWave))) * T;
 #pragma unroll
             for (int b = 0; b < NB; ++b)
-                load_mask_row<T>(mwx[b], tile_mask + (k * T + ql0 + 32 * b + (lane & 31)) * W);
+                load_mask_row<T>(mwn[b], tile_mask + (k * T + ql0 + 32 * b + (lane & 31)) * W);
+        }
+        Tl::template fetch<kWaves>(nK, K, kcol + kStage * (g % NSG), n, H, h, wave, lane);
+        Tl::template fetch<kWaves>(nV, V, kcol + kStage * (g % NSG), n, H, h, wave, lane);
     };
-#pragma unroll 1
-    for (int64_t g = 0; g < stages; ++g) {
-        const int buf = 0, st = int(g % NSG);
-        fetch(g, mw);
-        __syncthreads();  // the previous stage's readers are done
-        gk.store_rm(sK[0]);
-        gv.store_tr(sVt[0]);
-        __syncthreads();
+    auto stage = [&](int64_t g, const uint16_t* cK, const uint16_t* cV, uint16_t* nK, uint16_t* nV) {
+        const int st = int(g % NSG);
+        if (st == 0)
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int w = 0; w < W; ++w) mw[b][w] = mwn[b][w];
+        if (g + 1 < stages) prefetch(g + 1, nK, nV);
 #pragma unroll
         for (int kb = 0; kb < kStage / 32; ++kb) {
             f32x16_t s[NB];
@@ -1103,7 +1018,7 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(D >=
             for (int b = 0; b < NB; ++b) s[b] = zero16();
 #pragma unroll
             for (int c = 0; c < D / 16; ++c) {
-                const bf16x8_t a = lds_row8<D>(sK[buf], 32 * kb + (lane & 31), c, lane);
+                const bf16x8_t a = Tl::rows(cK, 32 * kb + (lane & 31), c, lane);
 #pragma unroll
                 for (int b = 0; b < NB; ++b) s[b] = mma(a, qf[b].v[c], s[b]);
             }
@@ -1167,11 +1082,19 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(D >=
             for (int db = 0; db < D / 32; ++db)
 #pragma unroll
                 for (int half = 0; half < 2; ++half) {
-                    const bf16x8_t a = lds_perm8(sVt[buf], 32 * db + (lane & 31), 32 * kb + 16 * half, lane);
+                    const bf16x8_t a = Tl::cols(cV, db, 32 * kb + 16 * half, lane);
 #pragma unroll
                     for (int b = 0; b < NB; ++b) acc[b][db] = mma(a, pb[b][half], acc[b][db]);
                 }
         }
+        stage_done();
+    };
+    prefetch(0, sK0, sV0);
+    stage_done();
+#pragma unroll 1
+    for (int64_t g = 0; g < stages; g += 2) {
+        stage(g, sK0, sV0, sK1, sV1);
+        if (g + 1 < stages) stage(g + 1, sK1, sV1, sK0, sV0);
     }
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
@@ -1219,9 +1142,10 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB =
                                                 float* __restrict__ pb, float* __restrict__ pd, int64_t R,
                                                 TileChunks ck, TileBias tb) {
     constexpr int W = T / 32;
-    __shared__ __attribute__((aligned(16))) uint16_t sK[1][kStage * RS<D>::v];
-    __shared__ __attribute__((aligned(16))) uint16_t sV[1][kStage * RS<D>::v];
-    __shared__ __attribute__((aligned(16))) uint16_t sKt[1][D * kTS];
+    using Tl = Tile<D>;
+    constexpr int kWaves = T / (32 * NB);
+    __shared__ __attribute__((aligned(16))) uint16_t sK0[Tl::kElems], sK1[Tl::kElems];
+    __shared__ __attribute__((aligned(16))) uint16_t sV0[Tl::kElems], sV1[Tl::kElems];
     const int h = blockIdx.y;
     int64_t I, t0, t1, slot;
     if (!tile_chunk(ck, tile_rowptr, R, blockIdx.x, I, t0, t1, slot)) return;
@@ -1230,8 +1154,7 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB =
         pb = ck.acc2;
         pd = ck.m;
     }
-    const int lane = lane_id();
-    constexpr int NT = T * 2 / NB;
+    const int lane = lane_id(), wave = uniform(int(threadIdx.x) / kWave);
     const int ql0 = (threadIdx.x / kWave) * 32 * NB;
     const int64_t q0 = int64_t(I) * T + ql0;
     Frag<D> qf[NB], gf[NB];
@@ -1251,29 +1174,33 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB =
         for (int db = 0; db < D / 32; ++db) accA[b][db] = accB[b][db] = zero16();
         dsum[b] = 0.f;
     }
+    // Stages run over the chunk's dense tiles, T/64 per tile; a stage's rows (and
+    // a tile's mask words) are on their way while the one before is multiplied.
     constexpr int NSG = T / kStage;
     const int64_t stages = (t1 - t0) * NSG;
-    Stager<D, NT> gk, gv;
-    uint32_t mw[NB][W];
-    auto fetch = [&](int64_t g, uint32_t (&mwx)[NB][W]) {
-        const int64_t k = t0 + g / NSG;
-        const int64_t kb = int64_t(tile_col[k]) * T + kStage * (g % NSG);
-        gk.load(K, kb, n, H, h);
-        gv.load(V, kb, n, H, h);
-        if (g % NSG == 0)
+    uint32_t mw[NB][W], mwn[NB][W];
+    int cols = 0;  // tile columns of 64 tiles, one per lane
+    int64_t kcol = 0;
+    auto prefetch = [&](int64_t g, uint16_t* nK, uint16_t* nV) {
+        const int64_t j = g / NSG, k = t0 + j;
+        if (g % NSG == 0) {
+            if (j % kWave == 0) cols = k + lane < t1 ? tile_col[k + lane] : 0;
+            kcol = int64_t(__builtin_amdgcn_readlane(cols, int(j % kWave))) * T;
 #pragma unroll
             for (int b = 0; b < NB; ++b)
-                load_mask_row<T>(mwx[b], tile_mask + (k * T + ql0 + 32 * b + (lane & 31)) * W);
+                load_mask_row<T>(mwn[b], tile_mask + (k * T + ql0 + 32 * b + (lane & 31)) * W);
+        }
+        Tl::template fetch<kWaves>(nK, K, kcol + kStage * (g % NSG), n, H, h, wave, lane);
+        Tl::template fetch<kWaves>(nV, V, kcol + kStage * (g % NSG), n, H, h, wave, lane);
     };
-#pragma unroll 1
-    for (int64_t g = 0; g < stages; ++g) {
-        const int buf = 0, st = int(g % NSG);
-        fetch(g, mw);
-        __syncthreads();
-        gk.store_rm(sK[0]);
-        gk.store_tr(sKt[0]);
-        gv.store_rm(sV[0]);
-        __syncthreads();
+    auto stage = [&](int64_t g, const uint16_t* cK, const uint16_t* cV, uint16_t* nK, uint16_t* nV) {
+        const int st = int(g % NSG);
+        if (st == 0)
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int w = 0; w < W; ++w) mw[b][w] = mwn[b][w];
+        if (g + 1 < stages) prefetch(g + 1, nK, nV);
 #pragma unroll
         for (int kb = 0; kb < kStage / 32; ++kb) {
             f32x16_t s[NB], dp[NB];
@@ -1281,10 +1208,10 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB =
             for (int b = 0; b < NB; ++b) s[b] = dp[b] = zero16();
 #pragma unroll
             for (int c = 0; c < D / 16; ++c) {
-                const bf16x8_t a = lds_row8<D>(sK[buf], 32 * kb + (lane & 31), c, lane);
+                const bf16x8_t a = Tl::rows(cK, 32 * kb + (lane & 31), c, lane);
 #pragma unroll
                 for (int b = 0; b < NB; ++b) s[b] = mma(a, qf[b].v[c], s[b]);
-                const bf16x8_t v = lds_row8<D>(sV[buf], 32 * kb + (lane & 31), c, lane);
+                const bf16x8_t v = Tl::rows(cV, 32 * kb + (lane & 31), c, lane);
 #pragma unroll
                 for (int b = 0; b < NB; ++b) dp[b] = mma(v, gf[b].v[c], dp[b]);
             }
@@ -1311,7 +1238,7 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB =
             for (int db = 0; db < D / 32; ++db)
 #pragma unroll
                 for (int half = 0; half < 2; ++half) {
-                    const bf16x8_t a = lds_perm8(sKt[buf], 32 * db + (lane & 31), 32 * kb + 16 * half, lane);
+                    const bf16x8_t a = Tl::cols(cK, db, 32 * kb + 16 * half, lane);
 #pragma unroll
                     for (int b = 0; b < NB; ++b) {
                         bf16x8_t hi, lo;
@@ -1322,6 +1249,14 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB =
                     }
                 }
         }
+        stage_done();
+    };
+    prefetch(0, sK0, sV0);
+    stage_done();
+#pragma unroll 1
+    for (int64_t g = 0; g < stages; g += 2) {
+        stage(g, sK0, sV0, sK1, sV1);
+        if (g + 1 < stages) stage(g + 1, sK1, sV1, sK0, sV0);
     }
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
@@ -1374,7 +1309,7 @@ __device__ __forceinline__ uint64_t bit_transpose_64x32(uint32_t w, int lane) {
 // The stage's masks are transposed so that each lane holds, for its key, one
 // 64-bit word over the stage's 64 queries.
 template <int D, int T, int NB, bool kBias = false>
-__global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB == 1 ? 2 : 1))) void k_tiles_dkdv(
+__global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB == 1 && !kBias ? 2 : 1))) void k_tiles_dkdv(
     int64_t n, int H, int64_t n_row_tiles,
                                                   const int64_t* __restrict__ tileT_ptr,
                                                   const int32_t* __restrict__ tileT_idx,
@@ -1386,12 +1321,12 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB =
                                                   float sl2, float* __restrict__ pdk, float* __restrict__ pdv,
                                                   TileChunks ck, TileBias tb) {
     constexpr int W = T / 32;
-    __shared__ __attribute__((aligned(16))) uint16_t sQ[1][kStage * RS<D>::v];
-    __shared__ __attribute__((aligned(16))) uint16_t sG[1][kStage * RS<D>::v];
-    __shared__ __attribute__((aligned(16))) uint16_t sQt[1][D * kTS];
-    __shared__ __attribute__((aligned(16))) uint16_t sGt[1][D * kTS];
-    __shared__ __attribute__((aligned(16))) float sL[1][kStage];
-    __shared__ __attribute__((aligned(16))) float sD[1][kStage];
+    using Tl = Tile<D>;
+    constexpr int kWaves = T / (32 * NB);
+    __shared__ __attribute__((aligned(16))) uint16_t sQ0[Tl::kElems], sQ1[Tl::kElems];
+    __shared__ __attribute__((aligned(16))) uint16_t sG0[Tl::kElems], sG1[Tl::kElems];
+    __shared__ __attribute__((aligned(16))) float sL0[kStage], sL1[kStage];
+    __shared__ __attribute__((aligned(16))) float sD0[kStage], sD1[kStage];
     const int h = blockIdx.y;
     int64_t J, u0, u1, slot;
     if (!tile_chunk(ck, tileT_ptr, n_row_tiles, blockIdx.x, J, u0, u1, slot)) return;
@@ -1399,8 +1334,7 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB =
         pdk = ck.acc;
         pdv = ck.acc2;
     }
-    const int lane = lane_id();
-    constexpr int NT = T * 2 / NB;
+    const int lane = lane_id(), wave = uniform(int(threadIdx.x) / kWave);
     const int kl0 = (threadIdx.x / kWave) * 32 * NB;  // first owned key inside the tile column
     const int64_t k0 = int64_t(J) * T + kl0;
     Frag<D> kf[NB], vf[NB];
@@ -1416,53 +1350,43 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB =
         for (int db = 0; db < D / 32; ++db) dk[b][db] = dv[b][db] = zero16();
     constexpr int NSG = T / kStage;
     const int64_t stages = (u1 - u0) * NSG;
-    Stager<D, NT> gq, gg;
-    uint32_t mword[NB];  // this lane's row of the stage: mask words of the wavefront's key blocks
-    float2 stat;        // LSE (exp2 domain) and D of the stage's query threadIdx.x % kStage
-    int64_t tk = 0;     // the stage's tile
-    auto fetch = [&](int64_t g) {
-        const int64_t k = tileT_idx[u0 + g / NSG];
-        tk = k;
-        int64_t lo = 0, hi = n_row_tiles;  // tile row of tile k: the last I with tile_rowptr[I] <= k
-        while (hi - lo > 1) {
-            const int64_t mid = (lo + hi) >> 1;
-            if (tile_rowptr[mid] <= k) lo = mid;
-            else hi = mid;
+    uint32_t mword[NB];  // the next stage's: this lane's row, mask words of the wavefront's key blocks
+    float2 stat = make_float2(0.f, 0.f);  // the next stage's: LSE (exp2 domain) and D of its query `lane`
+    int tiles = 0, trow = 0;  // 64 tiles of the column and their tile rows, one per lane
+    int64_t tn = 0, tk = 0;   // the next stage's tile, the stage's
+    auto prefetch = [&](int64_t g, uint16_t* nQ, uint16_t* nG) {
+        const int64_t j = g / NSG;
+        if (g % NSG == 0 && j % kWave == 0) {
+            tiles = u0 + j + lane < u1 ? tileT_idx[u0 + j + lane] : 0;
+            int64_t lo = 0, hi = n_row_tiles;  // tile row of the tile: the last I with tile_rowptr[I] <= it
+            while (hi - lo > 1) {
+                const int64_t mid = (lo + hi) >> 1;
+                if (tile_rowptr[mid] <= tiles) lo = mid;
+                else hi = mid;
+            }
+            trow = int(lo);
         }
+        tn = __builtin_amdgcn_readlane(tiles, int(j % kWave));
         const int st = int(g % NSG);
-        const int64_t qbase = lo * T + kStage * st;
-        gq.load(Q, qbase, n, H, h);
-        gg.load(dO, qbase, n, H, h);
+        const int64_t qbase = int64_t(__builtin_amdgcn_readlane(trow, int(j % kWave))) * T + kStage * st;
 #pragma unroll
-        for (int b = 0; b < NB; ++b) mword[b] = tile_mask[(k * T + kStage * st + lane) * W + (kl0 / 32 + b)];
-        stat = make_float2(__builtin_huge_valf(), 0.f);  // queries >= n take no weight
-        const int64_t qn = qbase + (threadIdx.x % kStage);
-        if (qn < n) stat = make_float2(LSE[qn * H + h] * kLog2e, Dv[qn * H + h]);
+        for (int b = 0; b < NB; ++b) mword[b] = tile_mask[(tn * T + kStage * st + lane) * W + (kl0 / 32 + b)];
+        if (wave == 0) {
+            stat = make_float2(__builtin_huge_valf(), 0.f);  // queries >= n take no weight
+            const int64_t qn = qbase + lane;
+            if (qn < n) stat = make_float2(LSE[qn * H + h] * kLog2e, Dv[qn * H + h]);
+        }
+        Tl::template fetch<kWaves>(nQ, Q, qbase, n, H, h, wave, lane);
+        Tl::template fetch<kWaves>(nG, dO, qbase, n, H, h, wave, lane);
     };
     // transposed masks: bit r of mt[b] <=> query r of the stage attends to key k0 + 32 b + lane % 32
     uint64_t mt[NB];
-    auto transpose = [&](uint64_t (&out)[NB]) {
+    auto stage = [&](int64_t g, const uint16_t* cQ, const uint16_t* cG, const float* cL, const float* cD,
+                     uint16_t* nQ, uint16_t* nG, float* nL, float* nD) {
 #pragma unroll
-        for (int b = 0; b < NB; ++b) out[b] = bit_transpose_64x32(mword[b], lane);
-    };
-    auto store = [&](int buf) {
-        gq.store_rm(sQ[buf]);
-        gq.store_tr(sQt[buf]);
-        gg.store_rm(sG[buf]);
-        gg.store_tr(sGt[buf]);
-        if (threadIdx.x < kStage) {
-            sL[buf][threadIdx.x] = stat.x;
-            sD[buf][threadIdx.x] = stat.y;
-        }
-    };
-#pragma unroll 1
-    for (int64_t g = 0; g < stages; ++g) {
-        const int buf = 0;
-        fetch(g);
-        transpose(mt);
-        __syncthreads();  // the previous stage's readers are done
-        store(0);
-        __syncthreads();
+        for (int b = 0; b < NB; ++b) mt[b] = bit_transpose_64x32(mword[b], lane);
+        tk = tn;
+        if (g + 1 < stages) prefetch(g + 1, nQ, nG);
 #pragma unroll
         for (int qb = 0; qb < kStage / 32; ++qb) {
             f32x16_t s[NB], dp[NB];
@@ -1470,10 +1394,10 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB =
             for (int b = 0; b < NB; ++b) s[b] = dp[b] = zero16();
 #pragma unroll
             for (int c = 0; c < D / 16; ++c) {
-                const bf16x8_t a = lds_row8<D>(sQ[buf], 32 * qb + (lane & 31), c, lane);
+                const bf16x8_t a = Tl::rows(cQ, 32 * qb + (lane & 31), c, lane);
 #pragma unroll
                 for (int b = 0; b < NB; ++b) s[b] = mma(a, kf[b].v[c], s[b]);
-                const bf16x8_t g8 = lds_row8<D>(sG[buf], 32 * qb + (lane & 31), c, lane);
+                const bf16x8_t g8 = Tl::rows(cG, 32 * qb + (lane & 31), c, lane);
 #pragma unroll
                 for (int b = 0; b < NB; ++b) dp[b] = mma(g8, vf[b].v[c], dp[b]);
             }
@@ -1481,8 +1405,8 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB =
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int r = 32 * qb + 8 * j + 4 * (lane >> 5);
-                const float4 lv = *reinterpret_cast<const float4*>(&sL[buf][r]);
-                const float4 d4 = *reinterpret_cast<const float4*>(&sD[buf][r]);
+                const float4 lv = *reinterpret_cast<const float4*>(&cL[r]);
+                const float4 d4 = *reinterpret_cast<const float4*>(&cD[r]);
                 Lr[4 * j] = lv.x, Lr[4 * j + 1] = lv.y, Lr[4 * j + 2] = lv.z, Lr[4 * j + 3] = lv.w;
                 Dr[4 * j] = d4.x, Dr[4 * j + 1] = d4.y, Dr[4 * j + 2] = d4.z, Dr[4 * j + 3] = d4.w;
             }
@@ -1511,8 +1435,8 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB =
             for (int db = 0; db < D / 32; ++db)
 #pragma unroll
                 for (int half = 0; half < 2; ++half) {
-                    const bf16x8_t g8 = lds_perm8(sGt[buf], 32 * db + (lane & 31), 32 * qb + 16 * half, lane);
-                    const bf16x8_t a = lds_perm8(sQt[buf], 32 * db + (lane & 31), 32 * qb + 16 * half, lane);
+                    const bf16x8_t g8 = Tl::cols(cG, db, 32 * qb + 16 * half, lane);
+                    const bf16x8_t a = Tl::cols(cQ, db, 32 * qb + 16 * half, lane);
 #pragma unroll
                     for (int b = 0; b < NB; ++b) {
                         bf16x8_t hi16, lo16;
@@ -1523,6 +1447,22 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB =
                     }
                 }
         }
+        if (wave == 0) {
+            nL[lane] = stat.x;
+            nD[lane] = stat.y;
+        }
+        stage_done();
+    };
+    prefetch(0, sQ0, sG0);
+    if (wave == 0) {
+        sL0[lane] = stat.x;
+        sD0[lane] = stat.y;
+    }
+    stage_done();
+#pragma unroll 1
+    for (int64_t g = 0; g < stages; g += 2) {
+        stage(g, sQ0, sG0, sL0, sD0, sQ1, sG1, sL1, sD1);
+        if (g + 1 < stages) stage(g + 1, sQ1, sG1, sL1, sD1, sQ0, sG0, sL0, sD0);
     }
 #pragma unroll
     for (int b = 0; b < NB; ++b) {

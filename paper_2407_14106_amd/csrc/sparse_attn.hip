@@ -525,7 +525,7 @@ __device__ __forceinline__ int64_t row_block(unsigned b, unsigned run) {
 // 0.20 ms a pass and their merge 0.13-0.23 ms; forward and backward 2.84 -> 2.34
 // ms.  128 molecules and a token row of 3,137 edges: 155 -> 82 us, with one launch
 // and a merge per pass instead of six.)
-constexpr int kMinRun = 64;
+constexpr int kMinRun = 32;
 constexpr int64_t kMaxSpread = 4096;
 // Up to one wavefront of long rows, every lane group finds its run from the
 // rows' lengths itself; beyond, k_long_plan lists the rows' first runs before.

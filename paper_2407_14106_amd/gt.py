@@ -153,16 +153,26 @@ def _check(status: int, where: str):
         raise GtError(status, where, lib.gt_last_error().decode() or lib.gt_status_string(status).decode())
 
 
+# The attention calls on small graphs are bound by this binding (a forward call at 4,096 nodes 14.2 us against an 8 us
+# kernel; 11.3 us now), so addresses and stream handles go to ctypes as plain integers (the signatures make them
+# pointers).
 def _ptr(t: torch.Tensor | None):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+# torch's current HIP stream of a device as an address (0.1 us; torch.cuda.current_stream(d).cuda_stream, the same
+# value through a Stream object, 2 us).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(device: torch.device):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    if _raw_stream is None or device.index is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return _raw_stream(device.index)
 
 
 def _workspace(nbytes: int, device) -> torch.Tensor:
-    return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
+    return torch.empty(nbytes if nbytes > 256 else 256, dtype=torch.uint8, device=device)
 
 
 def _need(cond: bool, msg: str):
@@ -443,20 +453,23 @@ def build_tiles(rowptr: torch.Tensor, col: torch.Tensor, T: int = 128, tau_ppm: 
 
 # ------------------------------------------------------------------------------ attention
 
+_DTYPE_CODES = {torch.float32: GT_F32, torch.bfloat16: GT_BF16}
+
+
 def _dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return GT_F32
-    if t.dtype == torch.bfloat16:
-        return GT_BF16
-    raise ValueError(f"unsupported dtype {t.dtype}")
+    code = _DTYPE_CODES.get(t.dtype)
+    if code is None:
+        raise ValueError(f"unsupported dtype {t.dtype}")
+    return code
 
 
 def _check_feats(n: int, *ts: torch.Tensor):
     ref = ts[0]
-    _need(ref.dim() == 3 and ref.shape[0] == n, "features must be [n, H, d]")
+    shape, dtype = ref.shape, ref.dtype
+    _need(len(shape) == 3 and shape[0] == n, "features must be [n, H, d]")
     for t in ts:
-        _need(t.shape == ref.shape and t.dtype == ref.dtype and t.is_cuda and t.is_contiguous(),
-              "feature tensors must share shape/dtype and be contiguous GPU tensors")
+        if not (t.is_cuda and t.is_contiguous() and (t is ref or (t.shape == shape and t.dtype == dtype))):
+            raise ValueError("feature tensors must share shape/dtype and be contiguous GPU tensors")
 
 
 def sparse_attn_fwd(plan: Plan, Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, scale: float | None = None):

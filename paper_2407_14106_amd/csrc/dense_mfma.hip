@@ -726,15 +726,16 @@ __device__ __forceinline__ int64_t out_row(int64_t q, int64_t I, int64_t slot, i
 }
 
 // The plan in one workgroup (a tile plan has at most 16,384 tile rows).
-// Wavefront w owns rows [1024 w, 1024 w + 1024) in 16 rounds of 64 consecutive
-// rows (one per lane), so every load and store is coalesced: the wavefront
-// totals give each wavefront its base, then each round's wavefront scan, plus
-// the running total of the rounds before it, gives every row its chunk
+// Wavefront w owns the 64 ROUNDS rows from 64 ROUNDS w, in rounds of 64
+// consecutive rows (one per lane), so every load and store is coalesced: the
+// wavefront totals give each wavefront its base, then each round's wavefront
+// scan, plus the running total of the rounds before it, gives every row its chunk
 // offset, extra-slot offset and place in the list of rows with extra slots.
+// ROUNDS fits the plan (16 rounds for any plan: 512 tile rows 10.5 us, with one
+// round 5.0; 7,600 tile rows 17, with 8 rounds 11).
 constexpr int kPlanThreads = 1024;
 constexpr int kPlanWaves = kPlanThreads / kWave;
 constexpr int64_t kPlanMaxRows = 16384;
-constexpr int kPlanRounds = int(kPlanMaxRows / kPlanThreads);
 
 // Inclusive wavefront sum scan on DPP moves (no LDS round trips): shifts by
 // 1, 2, 4 and 8 lanes scan each 16-lane row; broadcasting lane 15 into rows 1
@@ -760,6 +761,7 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x) {
     return x;
 }
 
+template <int ROUNDS>
 __global__ __launch_bounds__(kPlanThreads) void k_tile_chunk_plan1(int64_t R, const int64_t* __restrict__ ptr,
                                                                    int CH, int64_t* __restrict__ chunk_off,
                                                                    int64_t* __restrict__ extra_off,
@@ -768,16 +770,16 @@ __global__ __launch_bounds__(kPlanThreads) void k_tile_chunk_plan1(int64_t R, co
     // Counts fit in 32 bits: at most R <= 16,384 tiles per row and R rows.
     __shared__ uint32_t s_w[3][kPlanWaves];
     const int t = threadIdx.x, w = t / kWave, lane = lane_id();
-    const int64_t base = int64_t(w) * (kPlanRounds * kWave);
-    uint32_t k[kPlanRounds];  // chunks of row base + 64 j + lane
+    const int64_t base = int64_t(w) * (ROUNDS * kWave);
+    uint32_t k[ROUNDS];  // chunks of row base + 64 j + lane
 #pragma unroll
-    for (int j = 0; j < kPlanRounds; ++j) {
+    for (int j = 0; j < ROUNDS; ++j) {
         const int64_t I = base + kWave * j + lane;
         k[j] = I < R ? (uint32_t(ptr[I + 1] - ptr[I]) + uint32_t(CH) - 1u) / uint32_t(CH) : 0u;
     }
     uint32_t c = 0, e = 0, m = 0;
 #pragma unroll
-    for (int j = 0; j < kPlanRounds; ++j) {
+    for (int j = 0; j < ROUNDS; ++j) {
         c += k[j];
         e += k[j] > 1u ? k[j] - 1u : 0u;
         m += k[j] > 1u ? 1u : 0u;
@@ -804,7 +806,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_tile_chunk_plan1(int64_t R, co
         tm += s_w[2][x];
     }
 #pragma unroll
-    for (int j = 0; j < kPlanRounds; ++j) {
+    for (int j = 0; j < ROUNDS; ++j) {
         const int64_t I = base + kWave * j + lane;
         const uint32_t xe = k[j] > 1u ? k[j] - 1u : 0u, xm = k[j] > 1u ? 1u : 0u;
         const uint32_t ic = wave_incl_scan_u32(k[j]), ie = wave_incl_scan_u32(xe), im = wave_incl_scan_u32(xm);
@@ -827,8 +829,15 @@ __global__ __launch_bounds__(kPlanThreads) void k_tile_chunk_plan1(int64_t R, co
 gt_status tile_chunk_plan(const gt_tiles* p, const int64_t* ptr, const TileChunks& ck, hipStream_t s) {
     const int64_t R = p->n_row_tiles;
     if (R > kPlanMaxRows) return fail(GT_ERR_UNSUPPORTED, "dense tiles: more than 16384 tile rows");
-    k_tile_chunk_plan1<<<1, kPlanThreads, 0, s>>>(R, ptr, ck.CH, ck.chunk_off, ck.extra_off, ck.merge_rows,
-                                                  ck.merge_cnt);
+#define GT_CHUNK_PLAN(ROUNDS)                                                                                  \
+    k_tile_chunk_plan1<ROUNDS><<<1, kPlanThreads, 0, s>>>(R, ptr, ck.CH, ck.chunk_off, ck.extra_off, ck.merge_rows, \
+                                                          ck.merge_cnt)
+    if (R <= kPlanThreads) GT_CHUNK_PLAN(1);
+    else if (R <= 4 * kPlanThreads) GT_CHUNK_PLAN(4);
+    else if (R <= 8 * kPlanThreads) GT_CHUNK_PLAN(8);
+    else GT_CHUNK_PLAN(16);
+#undef GT_CHUNK_PLAN
+    static_assert(kPlanMaxRows == 16 * kPlanThreads, "16 rounds hold any plan");
     GT_LAUNCH_CHECK("tile_chunk_plan");
     return GT_OK;
 }

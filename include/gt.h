@@ -125,7 +125,8 @@ gt_status gt_reorder(int64_t n, int64_t nnz, const int64_t* rowptr, const int32_
  *     call has returned.
  * The side streams are used only when the rows of more than 64 entries hold
  * at least a quarter of the entries (else the short rows' kernel dominates a
- * sweep and the others gain nothing beside it).
+ * sweep and the others gain nothing beside it) and nnz is at least 4,194,304
+ * (below, a sweep is shorter than the ordering of the streams costs).
  * Same results, workspace and errors as gt_reorder (which is this call with
  * n_side = 0); a bad side-stream or event argument is GT_ERR_INVALID_ARG
  * before anything is enqueued.  When the call returns, every later call on

@@ -962,6 +962,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_big_prep(const int32_t* __rest
 // Tables of up to kFusedCap slots are reduced, decided and cleared by one
 // workgroup each (k_big_fused); the chunked passes below handle the larger ones.
 constexpr int64_t kFusedCap = 65536;
+constexpr int64_t kSideEntries = int64_t(1) << 22;  // entries from which a sweep's classes spread over side streams
 constexpr int kFusedThreads = 1024;
 
 // all: every table (its first use); else only those over kFusedCap slots.
@@ -1466,8 +1467,11 @@ extern "C" gt_status gt_reorder_streams(int64_t n, int64_t nnz, const int64_t* r
     const unsigned gwt = grid_cap(cnt[kClsWmed], kBlock / kWave, 1024);
     const unsigned gmed = grid_cap(cnt[kClsMed], 1, 1024);
     // side streams pay where the rows of more than kWaveRowMax entries hold at least a quarter of the
-    // entries; with fewer, their launches would mostly wait behind the short rows, so all stays on `stream`
-    const bool side = sp.n_side > 0 && 4 * info[2 * kClasses + 2] >= nnz;
+    // entries (with fewer, their launches would mostly wait behind the short rows) and a sweep's kernels are
+    // long beside the fork and the join (about 30 us a sweep); else all stays on `stream`.  Power-law graphs,
+    // gamma 2.1, side / one stream, us: 130K entries 1127 / 318, 1.3M 1279 / 623, 2.6M 1279 / 871,
+    // 4.55M 1501 / 1630, 6.5M 1861 / 2087, 13M 3021 / 3270.
+    const bool side = sp.n_side > 0 && nnz >= kSideEntries && 4 * info[2 * kClasses + 2] >= nnz;
     const hipStream_t s_short = stream, s_big = side ? sp.at(1) : stream, s_wide = side ? sp.at(2) : stream;
     for (int t = 0; t < iters; ++t) {
         const uint64_t key = seed + uint64_t(t + 1) * kGolden;

@@ -171,8 +171,8 @@ gt_status gt_scatter_rows(int64_t n, int64_t row_bytes, const void* src, const i
  * i/T = I, j/T = J; cnt is their number, area = min(T, n-I*T)*min(T, n-J*T).
  * The tile is dense iff cnt >= 1 and cnt*10^6 >= tau_ppm*area (exact integer
  * comparison).  T in {64, 128}; R <= 16384. */
-/* Remainder rows (columns) with more than GT_LONG_ROW edges are processed by
- * a whole workgroup each instead of a slice of a wavefront; the plan lists them. */
+/* Remainder rows (columns) with more than GT_LONG_ROW edges are cut into runs,
+ * spread over the chip and merged; the plan lists them. */
 #define GT_LONG_ROW 256
 
 typedef struct gt_tiles {

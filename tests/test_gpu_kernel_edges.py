@@ -1,0 +1,140 @@
+"""GPU attention at the sizes where the kernels' loops and dispatch rules change:
+row and column lengths around the id chunks and the long-row cut, few and many
+long rows and their folded runs, rows without edges beside infinite features,
+the full layer's workgroup shapes, and tile plans of every chunk-plan size."""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import attention as OA
+from synth import csr_from_pairs
+from synth.tensors import normal_tensor
+from tests.helpers import assert_close, dev_csr, dev_feat, host
+from tests.test_gpu_attention import CSR_ONLY, feats, run_case, say
+
+pytestmark = pytest.mark.gpu
+
+
+def both_ways(degs, m, seed):
+    """2 m nodes: node r < m attends to degs[r] of the nodes from m on, and node m + r is attended by degs[r]
+    of the nodes below m (columns beyond the first len(degs) rows' own picks), so rows and columns have the given
+    lengths where nothing else was drawn."""
+    rng = np.random.default_rng(seed)
+    u, v = [], []
+    for r, d in enumerate(degs):
+        u.append(np.full(d, r))
+        v.append(m + rng.choice(m, size=d, replace=False))
+        u.append(m + rng.choice(m, size=d, replace=False))
+        v.append(np.full(d, r))
+    return csr_from_pairs(2 * m, np.concatenate(u), np.concatenate(v), symmetric=False, self_loops=False)
+
+
+# around the id chunks of 2 to 64 entries, the edges taken at a time, the long-row cut (256) and the runs of 32
+DEGREES = list(range(0, 36)) + [47, 48, 49, 63, 64, 65, 127, 128, 129, 255, 256, 257, 287, 288, 289, 320, 513]
+
+
+@pytest.mark.parametrize("dtype,H,d", [("f32", 1, 32), ("f32", 8, 64), ("f32", 16, 64), ("bf16", 1, 32),
+                                       ("bf16", 4, 32), ("bf16", 8, 32), ("bf16", 8, 64), ("bf16", 16, 64)])
+def test_row_and_column_lengths(gt, dtype, H, d):
+    rowptr, col = both_ways(DEGREES, 520, H + d)
+    deg = np.diff(rowptr)
+    assert np.array_equal(deg[:len(DEGREES)], DEGREES)
+    assert np.array_equal(np.bincount(col, minlength=1040)[:len(DEGREES)], DEGREES)
+    run_case(gt, rowptr, col, H, d, dtype, taus=(CSR_ONLY,), seed=11)
+
+
+@pytest.mark.parametrize("n_long,length", [(1, 16_500), (64, 260), (65, 260), (130, 257), (2, 9_000)])
+def test_long_row_lists(gt, n_long, length):
+    # lists of one wavefront and beyond (their runs planned on the device), with the runs folded (more than
+    # 16,384 remainder edges) before the merge
+    degs = [length + (r % 3) for r in range(n_long)] + [0, 1, 5]
+    rowptr, col = both_ways(degs, max(length + 3, 600), n_long)
+    assert len(col) > 16_384
+    run_case(gt, rowptr, col, 2, 32, "bf16", taus=(CSR_ONLY,), seed=n_long)
+    # fp32 where the rows hold 28 edges and more: a row of one edge has dS = dP - D = 0, and what is left is the
+    # rounding of its terms (2^-24 scale |dO| |V| |K|, about 1e-6 for d = 64), above 1e-5 of a result that is zero
+    # in all rows but one
+    if n_long in (65, 130):
+        run_case(gt, rowptr, col, 1, 64, "f32", taus=(CSR_ONLY,), seed=n_long)
+
+
+@pytest.mark.parametrize("n", [16_384, 32_767, 32_768, 33_001])
+def test_node_runs_over_the_dies(gt, n):
+    # from some size on each die walks runs of the node range: every node exactly once
+    rng = np.random.default_rng(n)
+    u = rng.integers(0, n, size=2 * n)
+    v = (u + rng.integers(-40, 41, size=2 * n)) % n
+    rowptr, col = csr_from_pairs(n, u, v, symmetric=False, self_loops=True)
+    run_case(gt, rowptr, col, 8, 32, "bf16", taus=(CSR_ONLY,), seed=n)
+
+
+@pytest.mark.parametrize("dtype,H,d", [("f32", 2, 32), ("bf16", 1, 32), ("bf16", 8, 64)])
+def test_infinite_features_stay_with_their_edges(gt, dtype, H, d):
+    # The last node x (which ends the edge list) holds infinities; it attends to itself and node 1, and only node 2
+    # attends to it.  Every other row, with edges or without, and every other column is as with finite features.
+    n, x = 203, 202
+    rng = np.random.default_rng(7)
+    u = np.concatenate([rng.integers(3, 150, size=700), [2, x, x]])
+    v = np.concatenate([rng.integers(3, 200, size=700), [x, 1, x]])
+    rowptr, col = csr_from_pairs(n, u, v, symmetric=False, self_loops=False)
+    rp, cl = dev_csr(rowptr, col)
+    plan = gt.build_tiles(rp, cl, 64, CSR_ONLY)
+    outs = []
+    for value in (0.5, np.inf):
+        arrays = feats(n, H, d, dtype, 5)
+        for a in arrays:
+            a[x] = value
+        Q, K, V, dO = (dev_feat(a, dtype) for a in arrays)
+        O, L = gt.sparse_attn_fwd(plan, Q, K, V, 0.25)
+        dQ, dK, dV = gt.sparse_attn_bwd(plan, Q, K, V, dO, L, 0.25)
+        torch.cuda.synchronize()
+        outs.append((O, L, dQ, dK, dV))
+    for k, name in enumerate(("O", "LSE", "dQ", "dK", "dV")):
+        keep = torch.ones(n, dtype=torch.bool, device="cuda")
+        keep[[2, x] if k < 3 else [1, x]] = False
+        a, b = outs[0][k][keep], outs[1][k][keep]
+        assert torch.equal(a, b), name
+        assert k == 1 or bool(torch.isfinite(a).all()), name
+
+
+@pytest.mark.parametrize("n,H,d", [(1, 2, 32), (31, 2, 64), (32, 1, 32), (33, 1, 32), (64, 16, 64), (65, 4, 32),
+                                   (1025, 16, 32), (2047, 16, 64), (2049, 16, 32), (4065, 8, 64), (4097, 16, 32)])
+def test_full_layer_shapes(gt, n, H, d):
+    # up to 128, 256, 512 and more workgroups of 128 rows; the keys grow by powers of two along the partners (exact
+    # in bf16), so the rows' maxima move late in the walk.  Weights are rounded to 8 bits: |error of O| <= 2^-8 max |v|
+    # <= 0.02 for these normals, the tolerance's floor.
+    say("full", n, H, d)
+    q, k, v, do = (normal_tensor((n, H, d), (n, H, d, t), "bf16") for t in range(4))
+    scale = 1.0 / np.sqrt(d)
+    Q, K, V, dO = (dev_feat(a, "bf16") for a in (q, k, v, do))
+    grown = k * (2.0 ** (4 * np.arange(n) // n))[:, None, None].astype(k.dtype)
+    O, L = gt.dense_attn_fwd(Q, dev_feat(grown, "bf16"), V, scale)
+    O_ref, L_ref = OA.dense_attn_fwd(q, grown, v, scale)
+    assert_close(host(O), O_ref, "bf16", "O, growing keys")
+    assert_close(L.cpu().numpy(), L_ref, "bf16", "LSE, growing keys")
+    O, L = gt.dense_attn_fwd(Q, K, V, scale)
+    dQ, dK, dV = gt.dense_attn_bwd(Q, K, V, O, dO, L, scale)
+    torch.cuda.synchronize()
+    O_ref, L_ref = OA.dense_attn_fwd(q, k, v, scale)
+    assert_close(host(O), O_ref, "bf16", "O")
+    assert_close(L.cpu().numpy(), L_ref, "bf16", "LSE")
+    for name, a, r in zip(("dQ", "dK", "dV"), (dQ, dK, dV), OA.dense_attn_bwd(q, k, v, do, scale)):
+        assert_close(host(a), r, "bf16", name)
+
+
+@pytest.mark.parametrize("R", [1024, 1025, 4097, 8193])
+def test_tile_plans_of_every_size(gt, R):
+    # six dense tiles (more than one chunk) in tile rows and tile columns at both ends of the plan and of its
+    # rounds of 64 and 1,024 rows; one node in the last tile row
+    T = 64
+    n = T * (R - 1) + 1
+    rng = np.random.default_rng(R)
+    u, v = [np.arange(n)], [np.arange(n)]
+    for I in sorted({0, 63, 64, 1023, 1024, R - 2} & set(range(R - 1))):
+        for J in range(2, 8):
+            a, b = I * T + rng.integers(0, T, size=900), J * T + rng.integers(0, T, size=900)
+            u += [a, b]
+            v += [b, a]
+    rowptr, col = csr_from_pairs(n, np.concatenate(u), np.concatenate(v), symmetric=False, self_loops=False)
+    run_case(gt, rowptr, col, 1, 32, "bf16", taus=(100_000,), T=T, seed=R)

@@ -102,6 +102,24 @@ struct Frag {
     }
 };
 
+// Make the exp2-domain scale positive, so that a score masked with -inf stays
+// -inf when scaled: a negative scale negates the owned rows (exact in bf16), a
+// zero scale becomes 1 on rows of zeros.
+template <int D, int NB>
+__device__ __forceinline__ void positive_scale(Frag<D> (&q)[NB], float& sl2) {
+    if (!(sl2 <= 0.f)) return;
+    const uint32_t keep = sl2 < 0.f ? ~0u : 0u, flip = sl2 < 0.f ? 0x80008000u : 0u;
+    sl2 = sl2 < 0.f ? -sl2 : 1.f;
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int c = 0; c < D / 16; ++c) {
+            uint4 x = __builtin_bit_cast(uint4, q[b].v[c]);
+            x = make_uint4((x.x & keep) ^ flip, (x.y & keep) ^ flip, (x.z & keep) ^ flip, (x.w & keep) ^ flip);
+            q[b].v[c] = __builtin_bit_cast(bf16x8_t, x);
+        }
+}
+
 // --------------------------------------------------------- staged operands
 // Partner rows are staged 64 at a time by loads that write LDS directly (no
 // registers, no stores), one row-major copy of each operand, double buffered:
@@ -248,16 +266,7 @@ __global__ __launch_bounds__(WAVES * KS * kWave) __attribute__((amdgpu_waves_per
     Frag<D> qf[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) qf[b].load(Q, q0 + 32 * b + (lane & 31), n, H, h, lane);
-    if (sl2 < 0.f) {  // keep the exp2-domain scale positive: negate Q instead (exact in bf16)
-        sl2 = -sl2;
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int c = 0; c < D / 16; ++c)
-                qf[b].v[c] = __builtin_bit_cast(bf16x8_t, __builtin_bit_cast(uint4, qf[b].v[c]) ^
-                                                              make_uint4(0x80008000u, 0x80008000u, 0x80008000u,
-                                                                         0x80008000u));
-    }
+    positive_scale<D, NB>(qf, sl2);
     f32x16_t acc[NB][D / 32];
     float m[NB], l[NB];
 #pragma unroll
@@ -446,6 +455,7 @@ __global__ __launch_bounds__(WAVES * KS * kWave) __attribute__((amdgpu_waves_per
         if (q < n && lane < 32) Dv[q * H + h] = Dq;
         nD[b] = splat16(-Dq);
     }
+    positive_scale<D, NB>(qf, sl2);
     f32x16_t acc[NB][D / 32];
 #pragma unroll
     for (int b = 0; b < NB; ++b)
@@ -974,16 +984,7 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(D >=
     Frag<D> qf[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) qf[b].load(Q, q0 + 32 * b + (lane & 31), n, H, h, lane);
-    if (sl2 < 0.f) {  // keep the exp2-domain scale positive: negate Q instead (exact in bf16)
-        sl2 = -sl2;
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int c = 0; c < D / 16; ++c)
-                qf[b].v[c] = __builtin_bit_cast(bf16x8_t, __builtin_bit_cast(uint4, qf[b].v[c]) ^
-                                                              make_uint4(0x80008000u, 0x80008000u, 0x80008000u,
-                                                                         0x80008000u));
-    }
+    positive_scale<D, NB>(qf, sl2);
     f32x16_t acc[NB][D / 32];
     float m[NB], l[NB];
 #pragma unroll

@@ -138,3 +138,44 @@ def test_tile_plans_of_every_size(gt, R):
             v += [b, a]
     rowptr, col = csr_from_pairs(n, np.concatenate(u), np.concatenate(v), symmetric=False, self_loops=False)
     run_case(gt, rowptr, col, 1, 32, "bf16", taus=(100_000,), T=T, seed=R)
+
+
+@pytest.mark.parametrize("scale", [-0.2, 0.0])
+@pytest.mark.parametrize("n,H,d,dtype", [(33, 1, 32, "bf16"), (64, 2, 64, "bf16"), (1025, 4, 64, "bf16"),
+                                         (4097, 16, 32, "bf16"), (300, 2, 32, "f32")])
+def test_full_layer_scale_of_either_sign(gt, n, H, d, dtype, scale):
+    # a scale that is not positive leaves the partners past the end (n is ragged for the stages of 64) without weight
+    say("full", n, H, d, dtype, scale)
+    q, k, v, do = (normal_tensor((n, H, d), (n, H, d, t), dtype) for t in range(4))
+    Q, K, V, dO = (dev_feat(a, dtype) for a in (q, k, v, do))
+    O, L = gt.dense_attn_fwd(Q, K, V, scale)
+    dQ, dK, dV = gt.dense_attn_bwd(Q, K, V, O, dO, L, scale)
+    torch.cuda.synchronize()
+    O_ref, L_ref = OA.dense_attn_fwd(q, k, v, scale)
+    assert_close(host(O), O_ref, dtype, "O")
+    assert_close(L.cpu().numpy(), L_ref, dtype, "LSE")
+    for name, a, r in zip(("dQ", "dK", "dV"), (dQ, dK, dV), OA.dense_attn_bwd(q, k, v, do, scale)):
+        assert_close(host(a), r, dtype, name)
+
+
+@pytest.mark.parametrize("scale", [-0.2, 0.0])
+@pytest.mark.parametrize("T", [64, 128])
+def test_dense_tiles_scale_of_either_sign(gt, T, scale):
+    # every non-empty tile dense, most of its pairs masked, and none
+    rng = np.random.default_rng(T)
+    n, H, d = 203, 2, 32
+    rowptr, col = csr_from_pairs(n, rng.integers(0, n, size=1500), rng.integers(0, n, size=1500), symmetric=False,
+                                 self_loops=False)
+    q, k, v, do = feats(n, H, d, "bf16", T)
+    Q, K, V, dO = (dev_feat(a, "bf16") for a in (q, k, v, do))
+    O_ref, L_ref = OA.sparse_attn_fwd(rowptr, col, q, k, v, scale)
+    ref = OA.sparse_attn_bwd(rowptr, col, q, k, v, do, scale)
+    for tau in (0, CSR_ONLY):
+        plan = gt.build_tiles(*dev_csr(rowptr, col), T, tau)
+        O, L = gt.sparse_attn_fwd(plan, Q, K, V, scale)
+        dQ, dK, dV = gt.sparse_attn_bwd(plan, Q, K, V, dO, L, scale)
+        torch.cuda.synchronize()
+        assert_close(host(O), O_ref, "bf16", f"O tau={tau}")
+        assert_close(L.cpu().numpy(), L_ref, "bf16", f"LSE tau={tau}")
+        for name, a, r in zip(("dQ", "dK", "dV"), (dQ, dK, dV), ref):
+            assert_close(host(a), r, "bf16", f"{name} tau={tau}")

@@ -156,6 +156,17 @@ struct Tile {
                 16, 0, 0);
         }
     }
+    // Zero the rows past the end of a staged operand, for the same reason as drop_past_end; the whole workgroup, once
+    // the stage is in LDS.  (The tiles' column pass has no use for it: its weights come in two parts, whose products
+    // with an infinity cancel to NaN.)
+    template <int THREADS>
+    __device__ __forceinline__ static void zero_past_end(uint16_t* s, int64_t base, int64_t n) {
+        if (__builtin_expect(base + kStage <= n, 1)) return;
+        const int rows = n > base ? int(n - base) : 0;
+        for (int q = rows * kPieces + int(threadIdx.x); q < kStage * kPieces; q += THREADS)
+            *reinterpret_cast<uint4*>(s + 8 * q) = make_uint4(0, 0, 0, 0);
+        __syncthreads();
+    }
     // Row operand: row r, features 16 c + 8 (lane / 32) .. + 7.
     __device__ __forceinline__ static bf16x8_t rows(const uint16_t* s, int r, int c, int lane) {
         return __builtin_bit_cast(
@@ -177,6 +188,23 @@ struct Tile {
         return __builtin_bit_cast(bf16x8_t, s16x8_t{x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]});
     }
 };
+
+// Zero what a transposed operand (features x the 32 partners of a block, Tile::cols at 0 and 16) holds of partners past
+// the end: the staged rows there repeat the last node, and their zero weights times an infinity would be NaN.  Only a
+// ragged last stage needs it (and the masks), so the forward and the column pass of the full layer have that stage
+// apart from the loop (in the loop, as a branch: 16,384 x 8 x 32 step 1,538 -> 1,573 us, apart 1,596; the boxes
+// differ, 1,597 without it on the second).
+template <int D>
+__device__ __forceinline__ void drop_past_end(bf16x8_t (&a)[D / 32][2], int64_t first, int64_t n, int lane) {
+    const int left = int(n - first) - 4 * (lane >> 5);
+#pragma unroll
+    for (int half = 0; half < 2; ++half)
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+            if (16 * half + 8 * (t / 4) + t % 4 >= left)
+#pragma unroll
+                for (int db = 0; db < D / 32; ++db) a[db][half][t] = (__bf16)0.f;
+}
 
 // The stage fetched last is in LDS for every wavefront, and every wavefront is done with the one before.
 __device__ __forceinline__ void stage_done() {
@@ -278,9 +306,9 @@ __global__ __launch_bounds__(WAVES * KS * kWave) __attribute__((amdgpu_waves_per
     }
     stage_done();
     const int64_t stages = cdiv(n, kStage);
-    auto stage = [&](int64_t t, const uint16_t* cK, const uint16_t* cV, uint16_t* nK, uint16_t* nV) {
+    auto stage = [&](int64_t t, auto ragged, const uint16_t* cK, const uint16_t* cV, uint16_t* nK, uint16_t* nV) {
         const int64_t kbase = t * kStage;
-        if (t + 1 < stages) {
+        if (!ragged.value && t + 1 < stages) {
             Tl::template fetch<WAVES * KS>(nK, K, kbase + kStage, n, H, h, wave, lane);
             Tl::template fetch<WAVES * KS>(nV, V, kbase + kStage, n, H, h, wave, lane);
         }
@@ -288,7 +316,7 @@ __global__ __launch_bounds__(WAVES * KS * kWave) __attribute__((amdgpu_waves_per
         for (int kx = 0; kx < kStage / 32 / KS; ++kx) {
             const int kb = kx + part * (kStage / 32 / KS);
             const int64_t key0 = kbase + 32 * kb;
-            if (KS > 1 && key0 >= n) break;  // no partner left for this share (its maximum may still be -inf)
+            if (ragged.value && KS > 1 && key0 >= n) break;  // no partner left for this share (its maximum may still be -inf)
             f32x16_t s[NB];
             auto scores = [&] {
 #pragma unroll
@@ -299,10 +327,7 @@ __global__ __launch_bounds__(WAVES * KS * kWave) __attribute__((amdgpu_waves_per
 #pragma unroll
                     for (int b = 0; b < NB; ++b) s[b] = mma(a, qf[b].v[c], s[b]);
                 }
-                if (__builtin_expect(key0 + 32 > n, 0)) {  // ragged last block: partners >= n take no weight
-                    // kept as a branch (the empty asm stops the compiler from turning
-                    // it into selects on every block)
-                    asm volatile("" ::: "memory");
+                if constexpr (ragged.value) {  // partners >= n take no weight
 #pragma unroll
                     for (int i = 0; i < 16; ++i)
                         if (key0 + crow(i, lane) >= n)
@@ -330,6 +355,7 @@ __global__ __launch_bounds__(WAVES * KS * kWave) __attribute__((amdgpu_waves_per
             for (int db = 0; db < D / 32; ++db)
 #pragma unroll
                 for (int half = 0; half < 2; ++half) vt[db][half] = Tl::cols(cV, db, 32 * kb + 16 * half, lane);
+            if constexpr (ragged.value) drop_past_end<D>(vt, key0, n, lane);
             __builtin_amdgcn_sched_barrier(0);
             weights();
             bool high = false;
@@ -371,10 +397,12 @@ __global__ __launch_bounds__(WAVES * KS * kWave) __attribute__((amdgpu_waves_per
         }
         stage_done();
     };
-    for (int64_t t = 0; t < stages; t += 2) {
-        stage(t, sK0, sV0, sK1, sV1);
-        if (t + 1 < stages) stage(t + 1, sK1, sV1, sK0, sV0);
+    const int64_t whole = n / kStage;
+    for (int64_t t = 0; t < whole; t += 2) {
+        stage(t, Flag<false>{}, sK0, sV0, sK1, sV1);
+        if (t + 1 < whole) stage(t + 1, Flag<false>{}, sK1, sV1, sK0, sV0);
     }
+    if (whole < stages) stage(whole, Flag<true>{}, whole & 1 ? sK1 : sK0, whole & 1 ? sV1 : sV0, sK0, sV0);
     if constexpr (KS == 2) {  // the second share's states to the first's wavefronts
         __shared__ float s_x[NB * (16 * (D / 32) + 2)][WAVES * kWave];
         const int at = int(threadIdx.x) % (WAVES * kWave);
@@ -455,7 +483,6 @@ __global__ __launch_bounds__(WAVES * KS * kWave) __attribute__((amdgpu_waves_per
         if (q < n && lane < 32) Dv[q * H + h] = Dq;
         nD[b] = splat16(-Dq);
     }
-    positive_scale<D, NB>(qf, sl2);
     f32x16_t acc[NB][D / 32];
 #pragma unroll
     for (int b = 0; b < NB; ++b)
@@ -489,13 +516,15 @@ __global__ __launch_bounds__(WAVES * KS * kWave) __attribute__((amdgpu_waves_per
                 }
             }
             const int64_t key0 = kbase + 32 * kb;
-            if (__builtin_expect(key0 + 32 > n, 0)) {  // ragged last block
+            if (__builtin_expect(key0 + 32 > n, 0)) {  // ragged last block: no dS for partners >= n
+                // kept as a branch (the empty asm stops the compiler from turning
+                // it into selects on every block)
                 asm volatile("" ::: "memory");
 #pragma unroll
                 for (int i = 0; i < 16; ++i)
                     if (key0 + crow(i, lane) >= n)
 #pragma unroll
-                        for (int b = 0; b < NB; ++b) s[b][i] = kNegInf;
+                        for (int b = 0; b < NB; ++b) dp[b][i] = 0.f;
             }
             bf16x8_t kt[D / 32][2];
 #pragma unroll
@@ -591,10 +620,10 @@ __global__ __launch_bounds__(WAVES * KS * kWave) __attribute__((amdgpu_waves_per
     store_rows(sL0, sD0);
     stage_done();
     const int64_t stages = cdiv(n, kStage);
-    auto stage = [&](int64_t t, const uint16_t* cQ, const uint16_t* cG, uint16_t* nQ, uint16_t* nG, const float* cL, const float* cD, float* nL,
-                     float* nD) {
+    auto stage = [&](int64_t t, auto ragged, const uint16_t* cQ, const uint16_t* cG, uint16_t* nQ, uint16_t* nG,
+                     const float* cL, const float* cD, float* nL, float* nD) {
         const int64_t qbase = t * kStage;
-        if (t + 1 < stages) {
+        if (!ragged.value && t + 1 < stages) {
             load_rows(qbase + kStage);
             Tl::template fetch<WAVES * KS>(nQ, Q, qbase + kStage, n, H, h, wave, lane);
             Tl::template fetch<WAVES * KS>(nG, dO, qbase + kStage, n, H, h, wave, lane);
@@ -636,6 +665,7 @@ __global__ __launch_bounds__(WAVES * KS * kWave) __attribute__((amdgpu_waves_per
                     gt_[db][half] = Tl::cols(cG, db, 32 * qb + 16 * half, lane);
                     qt_[db][half] = Tl::cols(cQ, db, 32 * qb + 16 * half, lane);
                 }
+            if constexpr (ragged.value) drop_past_end<D>(gt_, qbase + 32 * qb, n, lane);
             __builtin_amdgcn_sched_barrier(0);
             bf16x8_t pb[NB][2], sb[NB][2];
 #pragma unroll
@@ -663,12 +693,17 @@ __global__ __launch_bounds__(WAVES * KS * kWave) __attribute__((amdgpu_waves_per
                     }
                 }
         }
-        if (t + 1 < stages) store_rows(nL, nD);
+        if (!ragged.value && t + 1 < stages) store_rows(nL, nD);
         stage_done();
     };
-    for (int64_t t = 0; t < stages; t += 2) {
-        stage(t, sQ0, sG0, sQ1, sG1, sL0, sD0, sL1, sD1);
-        if (t + 1 < stages) stage(t + 1, sQ1, sG1, sQ0, sG0, sL1, sD1, sL0, sD0);
+    const int64_t whole = n / kStage;
+    for (int64_t t = 0; t < whole; t += 2) {
+        stage(t, Flag<false>{}, sQ0, sG0, sQ1, sG1, sL0, sD0, sL1, sD1);
+        if (t + 1 < whole) stage(t + 1, Flag<false>{}, sQ1, sG1, sQ0, sG0, sL1, sD1, sL0, sD0);
+    }
+    if (whole < stages) {
+        const bool odd = whole & 1;
+        stage(whole, Flag<true>{}, odd ? sQ1 : sQ0, odd ? sG1 : sG0, sQ0, sG0, odd ? sL1 : sL0, odd ? sD1 : sD0, sL0, sD0);
     }
     if constexpr (KS > 1) {
         add_shares<KS, WAVES, NB * (D / 32)>(&dk[0][0], part);
@@ -1013,8 +1048,9 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(D >=
         Tl::template fetch<kWaves>(nK, K, kcol + kStage * (g % NSG), n, H, h, wave, lane);
         Tl::template fetch<kWaves>(nV, V, kcol + kStage * (g % NSG), n, H, h, wave, lane);
     };
-    auto stage = [&](int64_t g, const uint16_t* cK, const uint16_t* cV, uint16_t* nK, uint16_t* nV) {
+    auto stage = [&](int64_t g, const uint16_t* cK, uint16_t* cV, uint16_t* nK, uint16_t* nV) {
         const int st = int(g % NSG);
+        Tl::template zero_past_end<kWaves * kWave>(cV, kcol + kStage * st, n);
         if (st == 0)
 #pragma unroll
             for (int b = 0; b < NB; ++b)

@@ -179,3 +179,47 @@ def test_dense_tiles_scale_of_either_sign(gt, T, scale):
         assert_close(L.cpu().numpy(), L_ref, "bf16", f"LSE tau={tau}")
         for name, a, r in zip(("dQ", "dK", "dV"), (dQ, dK, dV), ref):
             assert_close(host(a), r, "bf16", f"{name} tau={tau}")
+
+
+@pytest.mark.parametrize("n,H,d", [(33, 2, 64), (97, 1, 32), (1025, 4, 64), (4097, 16, 32)])
+def test_full_layer_infinite_last_node(gt, n, H, d):
+    # one infinite feature of the last node's V (dO): that feature of every O (dV) row is infinite, every weight being
+    # positive, and all other features are those of the finite layer bit for bit
+    q, k, v, do = (normal_tensor((n, H, d), (n, H, d, t), "bf16") for t in range(4))
+    scale, f = 1.0 / np.sqrt(d), 5
+    Q, K = dev_feat(q, "bf16"), dev_feat(k, "bf16")
+    outs = []
+    for value in (0.5, np.inf):
+        v[-1, :, f] = do[-1, :, f] = value
+        V, dO = dev_feat(v, "bf16"), dev_feat(do, "bf16")
+        O, L = gt.dense_attn_fwd(Q, K, V, scale)
+        if not outs:
+            O_finite = O
+        dV = gt.dense_attn_bwd(Q, K, V, O_finite, dO, L, scale)[2]
+        torch.cuda.synchronize()
+        outs.append((O, L, dV))
+    assert torch.equal(outs[0][1], outs[1][1])
+    for k_, name in ((0, "O"), (2, "dV")):
+        a, b = outs[0][k_], outs[1][k_]
+        assert bool((b[:, :, f] == np.inf).all()), name
+        rest = [x for x in range(d) if x != f]
+        assert torch.equal(a[:, :, rest], b[:, :, rest]), name
+
+
+@pytest.mark.parametrize("n,T", [(70, 64), (129, 128), (200, 128)])
+def test_dense_tiles_infinite_last_node(gt, n, T):
+    # as above for O on dense tiles: every pair is an edge, the last tiles hold columns past the end
+    H, d, f = 2, 64, 5
+    rowptr, col = csr_from_pairs(n, np.repeat(np.arange(n), n), np.tile(np.arange(n), n), symmetric=False,
+                                 self_loops=False)
+    plan = gt.build_tiles(*dev_csr(rowptr, col), T, 0)
+    assert plan.nnz_sparse == 0
+    q, k, v, _ = feats(n, H, d, "bf16", n)
+    outs = []
+    for value in (0.5, np.inf):
+        v[-1, :, f] = value
+        outs.append(gt.sparse_attn_fwd(plan, *(dev_feat(x, "bf16") for x in (q, k, v)), 0.125)[0])
+    torch.cuda.synchronize()
+    assert bool((outs[1][:, :, f] == np.inf).all())
+    rest = [x for x in range(d) if x != f]
+    assert torch.equal(outs[0][:, :, rest], outs[1][:, :, rest])

@@ -86,9 +86,10 @@ struct Acc {
     }
 };
 
-// A running maximum starts at a finite value below every finite score, so
-// that a missing edge (score -inf) weighs exp2(-inf - m) = 0 with no test.
-constexpr float kMinRef = -3.0e38f;
+// A running maximum starts at the lowest finite value, which no finite score
+// is below, so that a missing edge (score -inf) weighs exp2(-inf - m) = 0 with
+// no test.
+constexpr float kMinRef = -3.402823466e38f;
 
 // Online-softmax state of one (node, head) slice.
 template <int F>

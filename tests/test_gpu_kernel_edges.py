@@ -223,3 +223,29 @@ def test_dense_tiles_infinite_last_node(gt, n, T):
     assert bool((outs[1][:, :, f] == np.inf).all())
     rest = [x for x in range(d) if x != f]
     assert torch.equal(outs[0][:, :, rest], outs[1][:, :, rest])
+
+
+@pytest.mark.parametrize("dtype,H,d", [("f32", 2, 32), ("f32", 8, 64), ("bf16", 1, 32), ("bf16", 8, 32)])
+def test_bias_near_the_lowest_value(gt, dtype, H, d):
+    # A row whose every score is one large negative finite number (-2.2e38: -3.17e38 in the exp2 domain, where it
+    # absorbs the scaled product) takes the mean of its partners; beside finite scores the same bias gives no weight.
+    # Rows of 1 edge, of a few, around the long-row cut, and long.
+    degs = [1, 2, 3, 31, 255, 256, 257, 700]
+    m = len(degs)
+    rowptr, col = both_ways(degs + degs, 720, H + d)
+    n, nnz, low = len(rowptr) - 1, len(col), -2.2e38
+    q, k, v, _ = feats(n, H, d, dtype, 21)
+    bias = np.random.default_rng(3).normal(size=(nnz, H)).astype(np.float32)
+    for r in range(2 * m):
+        a, b = rowptr[r], rowptr[r + 1]
+        bias[a:b if r < m else a + (b - a) // 2] = low
+    plan = gt.build_tiles(*dev_csr(rowptr, col), 64, CSR_ONLY)
+    O, L = gt.sparse_attn_fwd_bias(plan, *(dev_feat(x, dtype) for x in (q, k, v)), torch.from_numpy(bias).cuda(), 0.25)
+    torch.cuda.synchronize()
+    # the same rows with equal scores of ordinary size (in 64 bits too, the low score would absorb log l of the LSE)
+    bias[:rowptr[m]] = 0
+    q[:m] = 0
+    O_ref, L_ref = OA.sparse_attn_fwd(rowptr, col, q, k, v, 0.25, bias=bias)
+    L_ref[:m] = low
+    assert_close(host(O), O_ref, dtype, "O")
+    assert_close(L.cpu().numpy(), L_ref, dtype, "LSE")

@@ -34,6 +34,9 @@
  *   - Feature tensors Q, K, V, O, dO, dQ, dK, dV are [n, H, d] row-major
  *     (node, head, feature) in the element type `dtype`; LSE is [n, H] fp32.
  *     Supported: d in {32, 64}; H in {1, 2, 4, 8, 16}; dtype GT_F32 or GT_BF16.
+ *     They need no alignment beyond their element's; on dense tiles and in the
+ *     full layer, bf16 features that all start at multiples of 16 bytes (as
+ *     allocations do) run faster kernels.
  *     bf16: bf16 storage, scores, softmax statistics and every sum accumulated
  *     in fp32, bf16 results rounded to nearest even; where a softmax weight
  *     multiplies a bf16 row (the value sums, and the dense tiles' products of

@@ -1,6 +1,7 @@
 // Full softmax attention (§2.1 Eq. (1)): the interleaved fully-connected layer
 // of §3.2.  bf16 features run the streaming kernels of dense_mfma.hip; fp32
-// features run the matrix-core tile kernels with every pair attended.
+// features, and bf16 features at addresses that are not multiples of 16, run
+// the matrix-core tile kernels with every pair attended.
 #include <atomic>
 
 #include "tile_attn.h"
@@ -59,8 +60,9 @@ gt_status run_dense_fwd(int64_t n, const void* Q, const void* K, const void* V, 
                         hipStream_t s) {
     if (n == 0) return GT_OK;
     if constexpr (sizeof(T) == 2)
-        return full_fwd_bf16<D>(n, H, static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V),
-                                scale * kLog2e, static_cast<T*>(O), LSE, s);
+        if (aligned16(Q, K, V))
+            return full_fwd_bf16<D>(n, H, static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V),
+                                    scale * kLog2e, static_cast<T*>(O), LSE, s);
     return full_fwd<T, D, H>(n, static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V),
                              scale * kLog2e, static_cast<T*>(O), LSE, s);
 }
@@ -72,9 +74,10 @@ gt_status run_dense_bwd(int64_t n, const void* Q, const void* K, const void* V, 
     Ws w(ws);
     float* Dv = w.take<float>(size_t(n) * H);
     if constexpr (sizeof(T) == 2)
-        return full_bwd_bf16<D>(n, H, static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V),
-                                static_cast<const T*>(O), static_cast<const T*>(dO), LSE, scale * kLog2e, scale,
-                                static_cast<T*>(dQ), static_cast<T*>(dK), static_cast<T*>(dV), Dv, s);
+        if (aligned16(Q, K, V, dO))
+            return full_bwd_bf16<D>(n, H, static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V),
+                                    static_cast<const T*>(O), static_cast<const T*>(dO), LSE, scale * kLog2e, scale,
+                                    static_cast<T*>(dQ), static_cast<T*>(dK), static_cast<T*>(dV), Dv, s);
     return full_bwd<T, D, H>(n, static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V),
                              static_cast<const T*>(O), static_cast<const T*>(dO), LSE, scale * kLog2e, scale,
                              static_cast<T*>(dQ), static_cast<T*>(dK), static_cast<T*>(dV), Dv, s);

@@ -40,6 +40,14 @@ __device__ __forceinline__ f32x16_t zero16() {
 
 // ---------------------------------------------------------------- operands
 
+// 16 bytes of global memory at any address (one load: global accesses need no alignment on this target).
+template <typename T>
+__device__ __forceinline__ uint4 load16(const T* p) {
+    uint4 v;
+    __builtin_memcpy(&v, p, 16);
+    return v;
+}
+
 template <typename T>
 struct Mma;
 
@@ -97,7 +105,7 @@ struct RowFrag<uint16_t, D> {
 #pragma unroll
         for (int c = 0; c < D / 16; ++c) {
             uint4 x = make_uint4(0, 0, 0, 0);
-            if (ok) x = *reinterpret_cast<const uint4*>(row + 16 * c + 8 * (lane >> 5));
+            if (ok) x = load16(row + 16 * c + 8 * (lane >> 5));
             v[c] = __builtin_bit_cast(bf16x8_t, x);
         }
     }
@@ -213,7 +221,7 @@ __device__ __forceinline__ void stage(T* rm, T* tr, const T* __restrict__ X, int
         }
         const int64_t node = base + r;
         uint4 v = make_uint4(0, 0, 0, 0);
-        if (node < n) v = *reinterpret_cast<const uint4*>(X + (node * H + h) * D + part * kPer);
+        if (node < n) v = load16(X + (node * H + h) * D + part * kPer);
         if (rm) *reinterpret_cast<uint4*>(rm + r * Pad<T, D>::kRow + part * kPer) = v;
         if (tr) {
             const T* e = reinterpret_cast<const T*>(&v);
@@ -614,7 +622,8 @@ __global__ __launch_bounds__(2 * TT) void k_tile_dkdv(int64_t n, const int64_t* 
 template <typename T, int D, int H>
 gt_status tile_fwd(const gt_tiles* p, const T* Q, const T* K, const T* V, float sl2, TilePartials tp, TileBias tb,
                    hipStream_t s) {
-    if constexpr (Mma<T>::kBf16) return tiles_fwd_bf16<D>(p, H, Q, K, V, sl2, tp, tb, s);
+    if constexpr (Mma<T>::kBf16)
+        if (aligned16(Q, K, V)) return tiles_fwd_bf16<D>(p, H, Q, K, V, sl2, tp, tb, s);
     const dim3 grid(unsigned(p->n_row_tiles), H);
     if (tb.b)
         GT_TILE_SWITCH(p->T, (k_tile_fwd<T, D, H, TT, false, true><<<grid, 2 * TT, 0, s>>>(
@@ -631,7 +640,8 @@ gt_status tile_fwd(const gt_tiles* p, const T* Q, const T* K, const T* V, float 
 template <typename T, int D, int H>
 gt_status tile_bwd_dq(const gt_tiles* p, const T* Q, const T* K, const T* V, const T* dO, const float* LSE,
                       float sl2, TilePartials dq, TileBias tb, hipStream_t s) {
-    if constexpr (Mma<T>::kBf16) return tiles_dq_bf16<D>(p, H, Q, K, V, dO, LSE, sl2, dq, tb, s);
+    if constexpr (Mma<T>::kBf16)
+        if (aligned16(Q, K, V, dO)) return tiles_dq_bf16<D>(p, H, Q, K, V, dO, LSE, sl2, dq, tb, s);
     const dim3 grid(unsigned(p->n_row_tiles), H);
     if (tb.b)
         GT_TILE_SWITCH(p->T, (k_tile_dq<T, D, H, TT, false, true><<<grid, 2 * TT, 0, s>>>(
@@ -648,7 +658,8 @@ gt_status tile_bwd_dq(const gt_tiles* p, const T* Q, const T* K, const T* V, con
 template <typename T, int D, int H>
 gt_status tile_bwd_dkdv(const gt_tiles* p, const T* Q, const T* K, const T* V, const T* dO, const float* LSE,
                         const float* Dv, float sl2, TilePartials dk, TilePartials dv, TileBias tb, hipStream_t s) {
-    if constexpr (Mma<T>::kBf16) return tiles_dkdv_bf16<D>(p, H, Q, K, V, dO, LSE, Dv, sl2, dk, dv, tb, s);
+    if constexpr (Mma<T>::kBf16)
+        if (aligned16(Q, K, V, dO)) return tiles_dkdv_bf16<D>(p, H, Q, K, V, dO, LSE, Dv, sl2, dk, dv, tb, s);
     const dim3 grid(unsigned(p->n_row_tiles), H);
     if (tb.b)
         GT_TILE_SWITCH(p->T, (k_tile_dkdv<T, D, H, TT, false, true, true><<<grid, 2 * TT, 0, s>>>(

@@ -249,3 +249,61 @@ def test_bias_near_the_lowest_value(gt, dtype, H, d):
     L_ref[:m] = low
     assert_close(host(O), O_ref, dtype, "O")
     assert_close(L.cpu().numpy(), L_ref, dtype, "LSE")
+
+
+def shifted(x, off):
+    """The same tensor as a contiguous view `off` elements into a larger buffer."""
+    buf = torch.empty(x.numel() + 16, dtype=x.dtype, device=x.device)
+    out = buf[off:off + x.numel()].view(x.shape)
+    out.copy_(x)
+    assert out.is_contiguous() and out.data_ptr() % 16 == off * x.element_size() % 16
+    return out
+
+
+# which of Q, K, V, dO lie at which offset (elements; 8 are 16 bytes)
+OFFSETS = [(1, 1, 1, 1), (4, 4, 4, 4), (8, 8, 8, 8), (1, 0, 0, 0), (0, 4, 0, 0), (0, 0, 2, 0), (0, 0, 0, 1)]
+
+
+@pytest.mark.parametrize("offs", OFFSETS)
+@pytest.mark.parametrize("n,H,d", [(129, 2, 32), (300, 4, 64)])
+def test_full_layer_features_at_any_address(gt, n, H, d, offs):
+    arrays = [normal_tensor((n, H, d), (n, H, d, t), "bf16") for t in range(4)]
+    scale = 1.0 / np.sqrt(d)
+    Q, K, V, dO = (shifted(dev_feat(x, "bf16"), off) for x, off in zip(arrays, offs))
+    O, L = gt.dense_attn_fwd(Q, K, V, scale)
+    dQ, dK, dV = gt.dense_attn_bwd(Q, K, V, O, dO, L, scale)
+    torch.cuda.synchronize()
+    O_ref, L_ref = OA.dense_attn_fwd(*arrays[:3], scale)
+    assert_close(host(O), O_ref, "bf16", "O")
+    assert_close(L.cpu().numpy(), L_ref, "bf16", "LSE")
+    for name, a, r in zip(("dQ", "dK", "dV"), (dQ, dK, dV), OA.dense_attn_bwd(*arrays, scale)):
+        assert_close(host(a), r, "bf16", name)
+
+
+@pytest.mark.parametrize("offs", OFFSETS)
+@pytest.mark.parametrize("T,tau,H,d", [(64, 0, 2, 64), (128, 0, 4, 32), (128, CSR_ONLY, 8, 32)])
+def test_sparse_layer_features_at_any_address(gt, T, tau, H, d, offs):
+    # every non-empty tile dense, or none; without and with a bias
+    n, scale = 203, 0.2
+    rng = np.random.default_rng(T + H)
+    rowptr, col = csr_from_pairs(n, rng.integers(0, n, size=3000), rng.integers(0, n, size=3000), symmetric=False,
+                                 self_loops=True)
+    arrays = feats(n, H, d, "bf16", T)
+    bias = rng.normal(size=(len(col), H)).astype(np.float32)
+    plan = gt.build_tiles(*dev_csr(rowptr, col), T, tau, edge_positions=True)
+    B = torch.from_numpy(bias).cuda()
+    Q, K, V, dO = (shifted(dev_feat(x, "bf16"), off) for x, off in zip(arrays, offs))
+    for b in (None, bias):
+        if b is None:
+            O, L = gt.sparse_attn_fwd(plan, Q, K, V, scale)
+            grads = gt.sparse_attn_bwd(plan, Q, K, V, dO, L, scale)
+        else:
+            O, L = gt.sparse_attn_fwd_bias(plan, Q, K, V, B, scale)
+            grads = gt.sparse_attn_bwd_bias(plan, gt.edge_map(plan), Q, K, V, B, dO, L, scale)
+        torch.cuda.synchronize()
+        O_ref, L_ref = OA.sparse_attn_fwd(rowptr, col, *arrays[:3], scale, bias=b)
+        assert_close(host(O), O_ref, "bf16", "O")
+        assert_close(L.cpu().numpy(), L_ref, "bf16", "LSE")
+        ref = OA.sparse_attn_bwd(rowptr, col, *arrays, scale, bias=b)
+        for name, a, r in zip(("dQ", "dK", "dV", "dB"), grads, ref):
+            assert_close(host(a), r, "bf16", name)

@@ -519,15 +519,21 @@ __device__ __forceinline__ int64_t row_block(unsigned b, unsigned run) {
 // attends to every node, are cut into runs: a run is walked by one lane group
 // like a short row, in the same launch (the runs' workgroups first, the short
 // rows fill the chip behind them), leaves its partial state, and one
-// workgroup per long row merges its runs with the row's dense-tile partial.  A
-// run holds kMinRun edges, more where the long rows' edges would give more than
-// kMaxSpread runs.  (A token row and column of 980K edges beside 1M short rows:
+// workgroup per long row merges its runs with the row's dense-tile partial.
+// (A token row and column of 980K edges beside 1M short rows:
 // chunks of 2,048 edges, a workgroup each, launched after the short rows took
 // 0.20 ms a pass and their merge 0.13-0.23 ms; forward and backward 2.84 -> 2.34
-// ms.  128 molecules and a token row of 3,137 edges: 155 -> 82 us, with one launch
+// ms.  128 molecules and a token row of 3,137 edges: 155 -> 60 us, with one launch
 // and a merge per pass instead of six.)
+// A run holds kMinRun edges, more where the long rows' edges would give more
+// runs than run_spread: lane groups of 4 wavefronts on each of the chip's 1,024
+// SIMDs.  But no more than kMaxRun, the longest short row: a run's sums are
+// serial fp32 chains.  Past kMaxRuns runs (268M edges of long rows) the
+// partial states, up to 8 KB each, would outgrow the features, so runs lengthen.
 constexpr int kMinRun = 32;
-constexpr int64_t kMaxSpread = 4096;
+constexpr int kMaxRun = GT_LONG_ROW;
+constexpr int64_t kMaxRuns = int64_t(1) << 20;
+constexpr int64_t run_spread(int H, int D) { return 1024 * int64_t(H * D >= 256 ? 4 : 1024 / (H * D)); }
 // Up to one wavefront of long rows, every lane group finds its run from the
 // rows' lengths itself; beyond, k_long_plan lists the rows' first runs before.
 constexpr int64_t kPlanFree = kWave;
@@ -537,11 +543,20 @@ struct LongRows {
     int64_t n = 0;
     const int64_t* ptr = nullptr;
     const int64_t* off = nullptr;  // [n + 2]: first run of each row, their number, the run length; null: none listed
+    int64_t spread = 1;            // run_spread of the features
 };
 
-__device__ __forceinline__ int run_length(int64_t edges) {
-    const int64_t c = (cdiv(edges, kMaxSpread) + kMinRun - 1) / kMinRun * kMinRun;
-    return c > kMinRun ? int(c) : kMinRun;
+// Edges of a run, `edges` being those of all long rows.
+__host__ __device__ __forceinline__ int run_length(int64_t edges, int64_t spread) {
+    int64_t c = cdiv(edges, spread);
+    if (c > kMaxRun) c = cdiv(edges, kMaxRuns) > kMaxRun ? cdiv(edges, kMaxRuns) : kMaxRun;
+    return c > kMinRun ? int((c + kMinRun - 1) / kMinRun * kMinRun) : kMinRun;
+}
+// At most so many runs beyond one per row: edges <= nnz over the run length.
+inline int64_t run_bound(int64_t nnz, int64_t spread) {
+    const int64_t a = nnz / kMinRun < spread ? nnz / kMinRun : spread;
+    const int64_t b = nnz / kMaxRun < kMaxRuns ? nnz / kMaxRun : kMaxRuns;
+    return a > b ? a : b;
 }
 
 // Every long row's runs, one row per lane (lr.n <= kPlanFree).
@@ -554,7 +569,7 @@ struct LaneRuns {
             const int64_t i = lr.list[lane];
             deg = lr.ptr[i + 1] - lr.ptr[i];
         }
-        len = run_length(wave_sum(deg));
+        len = run_length(wave_sum(deg), lr.spread);
         cnt = int(cdiv(deg, len));
         incl = cnt;
 #pragma unroll
@@ -658,7 +673,7 @@ __global__ __launch_bounds__(kPlanThr) void k_long_plan(LongRows lr, int64_t* __
     __syncthreads();
     int64_t total = 0;
     for (int k = 0; k < kPlanThr / kWave; ++k) total += s_w[k];
-    const int len = run_length(total);
+    const int len = run_length(total, lr.spread);
     int64_t base = 0;
     for (int64_t r0 = 0; r0 < lr.n; r0 += kPlanThr) {
         const int64_t cnt = cdiv(length(r0 + t), len);
@@ -692,6 +707,7 @@ constexpr int64_t fwd_run_floats(int H, int D) { return int64_t(H) * D + pad4(2 
 constexpr int64_t row_run_floats(int H, int D) { return 2 * int64_t(H) * D + pad4(H); }
 constexpr int64_t col_run_floats(int H, int D) { return 2 * int64_t(H) * D; }
 
+constexpr int64_t kFoldBlocks = 4096;
 struct LongPlan {
     int64_t* off = nullptr;  // [n_long + 2] where k_long_plan runs
     float* part = nullptr;   // [max_runs, floats per run]
@@ -702,26 +718,27 @@ struct LongPlan {
     }
 };
 
-inline LongPlan long_plan_take(Ws& ws, int64_t n_long, int64_t nnz, int64_t per_run) {
+inline LongPlan long_plan_take(Ws& ws, int64_t n_long, int64_t nnz, int64_t spread, int64_t per_run) {
     LongPlan lp;
     if (n_long <= 0) return lp;
-    const int64_t spread = nnz / kMinRun < kMaxSpread ? nnz / kMinRun : kMaxSpread;
-    lp.max_runs = n_long + spread;
+    const int64_t more = run_bound(nnz, spread), parts = kFoldBlocks / n_long;
+    lp.max_runs = n_long + more;
     // few long rows may hold thousands of runs each: 64 workgroups a row fold
     // them first (more rows: fewer each, none from 2,048 rows on)
-    if (spread > 512) lp.fold = int(kMaxSpread / n_long < 1 ? 1 : kMaxSpread / n_long > 64 ? 64 : kMaxSpread / n_long);
+    if (more > 512) lp.fold = int(parts < 1 ? 1 : parts > 64 ? 64 : parts);
     if (n_long > kPlanFree) lp.off = ws.take<int64_t>(size_t(n_long + 2));
     lp.part = ws.take<float>(size_t(lp.max_runs * per_run));
     return lp;
 }
 
-gt_status long_rows(const int32_t* list, int64_t n_long, const int64_t* ptr, const LongPlan& lp, LongRows& lr,
-                    hipStream_t s) {
+gt_status long_rows(const int32_t* list, int64_t n_long, const int64_t* ptr, int64_t spread, const LongPlan& lp,
+                    LongRows& lr, hipStream_t s) {
     lr = LongRows{};
     if (n_long <= 0) return GT_OK;
     lr.list = list;
     lr.n = n_long;
     lr.ptr = ptr;
+    lr.spread = spread;
     if (lp.off) {
         k_long_plan<<<1, kPlanThr, 0, s>>>(lr, lp.off);
         GT_LAUNCH_CHECK("long_plan");
@@ -1341,7 +1358,7 @@ gt_status run_fwd_t(const gt_tiles* p, const void* Q, const void* K, const void*
     Ws ws(ws_ptr);
     ws.take<char>(256);
     TilePartials tp = tile_partials_fwd(ws, p, H, D);
-    LongPlan lp = long_plan_take(ws, p->n_long_rows, p->nnz_sparse, fwd_run_floats(H, D));
+    LongPlan lp = long_plan_take(ws, p->n_long_rows, p->nnz_sparse, run_spread(H, D), fwd_run_floats(H, D));
     const float sl2 = scale * kLog2e;
     gt_status st;
     if (p->n_dense > 0) {
@@ -1352,7 +1369,7 @@ gt_status run_fwd_t(const gt_tiles* p, const void* Q, const void* K, const void*
         tp = TilePartials{};
     }
     LongRows lr;
-    if ((st = long_rows(p->long_rows, p->n_long_rows, p->sp_rowptr, lp, lr, s)) != GT_OK) return st;
+    if ((st = long_rows(p->long_rows, p->n_long_rows, p->sp_rowptr, run_spread(H, D), lp, lr, s)) != GT_OK) return st;
     const RowGrid rg = row_grid(n, C::NPW * (kThreads / kWave));
     const unsigned runs = lp.blocks(C::NPW * (kThreads / kWave));
     k_fwd_rows<T, D, H, kBias><<<runs + rg.grid, kThreads, 0, s>>>(
@@ -1388,7 +1405,7 @@ gt_status run_bwd_rows_t(const gt_tiles* p, const void* Q, const void* K, const 
     Ws ws(ws_ptr);
     ws.take<char>(256);
     TileBwdPartials tb = tile_partials_bwd(ws, p, H, D, true, false);
-    LongPlan lp = long_plan_take(ws, p->n_long_rows, p->nnz_sparse, row_run_floats(H, D));
+    LongPlan lp = long_plan_take(ws, p->n_long_rows, p->nnz_sparse, run_spread(H, D), row_run_floats(H, D));
     const float sl2 = scale * kLog2e;
     const T *q = static_cast<const T*>(Q), *k = static_cast<const T*>(K), *v = static_cast<const T*>(V);
     const T* g = static_cast<const T*>(dO);
@@ -1397,7 +1414,7 @@ gt_status run_bwd_rows_t(const gt_tiles* p, const void* Q, const void* K, const 
         if ((st = tile_bwd_dq<T, D, H>(p, q, k, v, g, LSE, sl2, tb.dq, eb.tile, s)) != GT_OK) return st;
     }
     LongRows lr;
-    if ((st = long_rows(p->long_rows, p->n_long_rows, p->sp_rowptr, lp, lr, s)) != GT_OK) return st;
+    if ((st = long_rows(p->long_rows, p->n_long_rows, p->sp_rowptr, run_spread(H, D), lp, lr, s)) != GT_OK) return st;
     const RowGrid rg = row_grid(n, C::NPW * (kThreads / kWave));
     const unsigned runs = lp.blocks(C::NPW * (kThreads / kWave));
     k_bwd_rows<T, D, H, kBias><<<runs + rg.grid, kThreads, 0, s>>>(
@@ -1435,7 +1452,7 @@ gt_status run_bwd_cols_t(const gt_tiles* p, const void* Q, const void* K, const 
     Ws ws(ws_ptr);
     ws.take<char>(256);
     TileBwdPartials tb = tile_partials_bwd(ws, p, H, D, false, true);
-    LongPlan lp = long_plan_take(ws, p->n_long_cols, p->nnz_sparse, col_run_floats(H, D));
+    LongPlan lp = long_plan_take(ws, p->n_long_cols, p->nnz_sparse, run_spread(H, D), col_run_floats(H, D));
     float2* stat = packed ? nullptr : ws.take<float2>(size_t(n) * H);
     const float sl2 = scale * kLog2e;
     const T *q = static_cast<const T*>(Q), *k = static_cast<const T*>(K), *v = static_cast<const T*>(V);
@@ -1450,7 +1467,7 @@ gt_status run_bwd_cols_t(const gt_tiles* p, const void* Q, const void* K, const 
         GT_LAUNCH_CHECK("sparse_bwd_pack_stats");
     }
     LongRows lr;
-    if ((st = long_rows(p->long_cols, p->n_long_cols, p->sp_colptr, lp, lr, s)) != GT_OK) return st;
+    if ((st = long_rows(p->long_cols, p->n_long_cols, p->sp_colptr, run_spread(H, D), lp, lr, s)) != GT_OK) return st;
     const RowGrid rg = row_grid(n, C::NPW * (kThreads / kWave));
     const unsigned runs = lp.blocks(C::NPW * (kThreads / kWave));
     k_bwd_cols<T, D, H, kBias><<<runs + rg.grid, kThreads, 0, s>>>(
@@ -1514,16 +1531,16 @@ size_t fwd_ws(const gt_tiles* p, int32_t H, int32_t d) {
     Ws ws(nullptr);
     ws.take<char>(256);
     tile_partials_fwd(ws, p, H, d);
-    long_plan_take(ws, p->n_long_rows, p->nnz_sparse, fwd_run_floats(H, d));
+    long_plan_take(ws, p->n_long_rows, p->nnz_sparse, run_spread(H, d), fwd_run_floats(H, d));
     return ws.size();
 }
 size_t bwd_part_ws(const gt_tiles* p, int32_t H, int32_t d, bool rows, bool cols, bool with_stat = true) {
     Ws ws(nullptr);
     ws.take<char>(256);
     tile_partials_bwd(ws, p, H, d, rows, cols);
-    if (rows) long_plan_take(ws, p->n_long_rows, p->nnz_sparse, row_run_floats(H, d));
+    if (rows) long_plan_take(ws, p->n_long_rows, p->nnz_sparse, run_spread(H, d), row_run_floats(H, d));
     if (cols) {
-        long_plan_take(ws, p->n_long_cols, p->nnz_sparse, col_run_floats(H, d));
+        long_plan_take(ws, p->n_long_cols, p->nnz_sparse, run_spread(H, d), col_run_floats(H, d));
         if (with_stat) ws.take<float2>(size_t(p->n > 0 ? p->n : 1) * H);
     }
     return ws.size();

@@ -59,6 +59,26 @@ def test_long_row_lists(gt, n_long, length):
         run_case(gt, rowptr, col, 1, 64, "f32", taus=(CSR_ONLY,), seed=n_long)
 
 
+@pytest.mark.parametrize("H,d", [(1, 32), (8, 64)])
+def test_long_rows_sum_in_short_chains(gt, H, d):
+    # 9M edges of long rows, equal weights and equal partners, so that every addition of a run rounds the same way.
+    # No serial chain is longer than that of the longest short row, 256 edges: its k-th sum errs by 2^-24 k / 256
+    # of the result at most, 128 2^-24 in all; the merge of a row's 94 runs or fewer, the sum of the weights, exp2 and
+    # log add less than 30 (a run of 2,208 edges gave 390).
+    n = 3000
+    Q = torch.zeros(n, H, d, device="cuda")
+    x = torch.from_numpy(np.random.default_rng(1).uniform(1, 2, size=(1, H, d)).astype(np.float32)).cuda()
+    X = x.expand(n, H, d).contiguous()
+    plan = gt.build_tiles(torch.arange(n + 1, dtype=torch.int64, device="cuda") * n,
+                          torch.arange(n, dtype=torch.int32, device="cuda").repeat(n), 128, CSR_ONLY)
+    O, L = gt.sparse_attn_fwd(plan, Q, X, X, 1.0)
+    dV = gt.sparse_attn_bwd(plan, Q, X, X, X, L, 1.0)[2]
+    torch.cuda.synchronize()
+    for name, a in (("O", O), ("dV", dV)):
+        err = float((a.double() / X.double() - 1).abs().max()) * 2 ** 24
+        assert err <= 158, (name, err)
+
+
 @pytest.mark.parametrize("n", [16_384, 32_767, 32_768, 33_001])
 def test_node_runs_over_the_dies(gt, n):
     # from some size on each die walks runs of the node range: every node exactly once

@@ -988,8 +988,13 @@ __global__ __launch_bounds__(kMergeThreads) void k_tiles_merge_sum(int64_t n, in
 // feeds two products; 1: half the registers, twice the wavefronts).  The
 // tiles are launched with NB = 1 (kTileNB): a chunk holds only a few tiles, so
 // the kernels are latency-bound and more resident wavefronts pay more than
-// the operand reuse; the occupancy hints keep the accumulators out of the
-// AGPRs (forward: 4 wavefronts per SIMD at d = 32 and 64; dQ, dK/dV: 2-3).
+// the operand reuse.  Wavefronts per SIMD: forward 4 at d = 32, 3 at d = 64; dQ
+// and dK/dV 3 at d = 32, 2 at d = 64 (dK/dV at d = 32, T = 64 without a bias 2: its
+// registers spill at 3).  Measured on 65,536 nodes, 8 heads, tiles from 5% on (us,
+// backward of the layer): d = 32 at 2 wavefronts 406, at 3 387; with a bias dK/dV
+// at 1 wavefront in a SIMD 4120 (d = 64) and 3870 (d = 32), at 2 and 3 3650 and 3320.
+// A stage's cells of the bias are addressed from a uniform base, with one offset a
+// lane: an address a cell is what took the registers (256 and 186 AGPRs).
 template <int D, int T, int NB, bool kBias = false>
 __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(D >= 64 ? 3 : 4))) void k_tiles_fwd(
     int64_t n, int H, const int64_t* __restrict__ tile_rowptr,
@@ -1074,13 +1079,14 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(D >=
                 const uint32_t w = mw[b][2 * st + kb];
                 if constexpr (kBias) {
                     // scores in the exp2 domain with the bias added: s sl2 + b log2 e
-                    const int64_t tk = t0 + g / NSG;
-                    const int r = ql0 + 32 * b + (lane & 31);
+                    const float* cell = tb.b + TileBias::at(t0 + g / NSG, H, h, T, 32 * (NB * wave + b),
+                                                            kStage * st + 32 * kb);
+                    const int xl = (lane & 31) * T + 4 * (lane >> 5);
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
                         // the per-tile bias is -inf off the edges, so it masks the cell itself: no test and
                         // no branch, which keeps the wait states of the accumulator reads that follow
-                        const float bb = tb.b[TileBias::at(tk, H, h, T, r, kStage * st + 32 * kb + crow(i, lane))];
+                        const float bb = (cell + (8 * (i >> 2) + (i & 3)))[xl];
                         s[b][i] = fmaf(s[b][i], sl2, bb * kLog2e);
                     }
                 } else {
@@ -1177,7 +1183,7 @@ __device__ __forceinline__ void split_b16(const f32x16_t& w, int half, bf16x8_t&
 // Row pass over the dense tiles: A = sum P dP K, B = sum P K and the D sum
 // sum P dP of every owned row (the edge kernels form dQ = scale (A - D B)).
 template <int D, int T, int NB, bool kBias = false>
-__global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB == 1 ? 2 : 1))) void k_tiles_dq(
+__global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB > 1 ? 1 : D < 64 ? 3 : 2))) void k_tiles_dq(
     int64_t n, int H, const int64_t* __restrict__ tile_rowptr,
                                                 const int32_t* __restrict__ tile_col,
                                                 const uint32_t* __restrict__ tile_mask,
@@ -1263,13 +1269,15 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB =
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
                 const uint32_t w = mw[b][2 * st + kb];
+                const float* cell = nullptr;
+                const int xl = (lane & 31) * T + 4 * (lane >> 5);
+                if constexpr (kBias)
+                    cell = tb.b + TileBias::at(t0 + g / NSG, H, h, T, 32 * (NB * wave + b), kStage * st + 32 * kb);
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     float p;
                     if constexpr (kBias) {
-                        const int64_t tk = t0 + g / NSG;
-                        const int r = ql0 + 32 * b + (lane & 31), c = kStage * st + 32 * kb + crow(i, lane);
-                        const float bb = tb.b[TileBias::at(tk, H, h, T, r, c)];
+                        const float bb = (cell + (8 * (i >> 2) + (i & 3)))[xl];
                         p = ex2(fmaf(s[b][i], sl2, bb * kLog2e - lse2[b]));  // 0 off the edges (bias -inf)
                     } else {
                         p = (w >> crow(i, lane)) & 1u ? ex2(fmaf(s[b][i], sl2, -lse2[b])) : 0.f;
@@ -1354,7 +1362,7 @@ __device__ __forceinline__ uint64_t bit_transpose_64x32(uint32_t w, int lane) {
 // The stage's masks are transposed so that each lane holds, for its key, one
 // 64-bit word over the stage's 64 queries.
 template <int D, int T, int NB, bool kBias = false>
-__global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB == 1 && !kBias ? 2 : 1))) void k_tiles_dkdv(
+__global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB > 1 ? 1 : D < 64 && (kBias || T == 128) ? 3 : 2))) void k_tiles_dkdv(
     int64_t n, int H, int64_t n_row_tiles,
                                                   const int64_t* __restrict__ tileT_ptr,
                                                   const int32_t* __restrict__ tileT_idx,
@@ -1458,17 +1466,19 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB =
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
                 const uint32_t w = uint32_t(mt[b] >> (32 * qb));
+                int64_t x0 = 0;
+                const int xl = 4 * (lane >> 5) * T + (lane & 31);
+                if constexpr (kBias)
+                    x0 = TileBias::at(tk, H, h, T, kStage * int(g % NSG) + 32 * qb, 32 * (NB * wave + b));
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     const bool on = (w >> crow(i, lane)) & 1u;
                     float p = 0.f;
                     if constexpr (kBias) {
-                        const int st = int(g % NSG);
-                        const int r = kStage * st + 32 * qb + crow(i, lane), c = kl0 + 32 * b + (lane & 31);
-                        const int64_t x = TileBias::at(tk, H, h, T, r, c);
-                        p = ex2(fmaf(s[b][i], sl2, tb.b[x] * kLog2e - Lr[i]));  // 0 off the edges (bias -inf)
+                        const int64_t x = x0 + (8 * (i >> 2) + (i & 3)) * T;
+                        p = ex2(fmaf(s[b][i], sl2, (tb.b + x)[xl] * kLog2e - Lr[i]));  // 0 off the edges (bias -inf)
                         s[b][i] = p * (dp[b][i] - Dr[i]);
-                        tb.db[x] = s[b][i];  // every cell (0 off the edges), so no branch is needed
+                        (tb.db + x)[xl] = s[b][i];  // every cell (0 off the edges), so no branch is needed
                     } else {
                         p = on ? ex2(fmaf(s[b][i], sl2, -Lr[i])) : 0.f;
                         s[b][i] = p * (dp[b][i] - Dr[i]);

@@ -12,6 +12,7 @@ from synth import csr_from_pairs
 from synth.tensors import normal_tensor
 from tests.helpers import assert_close, dev_csr, dev_feat, host
 from tests.test_gpu_attention import CSR_ONLY, feats, run_case, say
+from tests.test_gpu_bias import run_bias_case
 
 pytestmark = pytest.mark.gpu
 
@@ -44,12 +45,14 @@ def test_row_and_column_lengths(gt, dtype, H, d):
     run_case(gt, rowptr, col, H, d, dtype, taus=(CSR_ONLY,), seed=11)
 
 
-@pytest.mark.parametrize("n_long,length", [(1, 16_500), (64, 260), (65, 260), (130, 257), (2, 9_000)])
+@pytest.mark.parametrize("n_long,length", [(1, 16_500), (64, 260), (65, 260), (130, 257), (2, 9_000),
+                                           (1025, 257), (2049, 257)])
 def test_long_row_lists(gt, n_long, length):
     # lists of one wavefront and beyond (their runs planned on the device), with the runs folded (more than
-    # 16,384 remainder edges) before the merge
+    # 16,384 remainder edges) before the merge or, over 2,048 rows, not; over 1,024 rows take the planning workgroup
+    # a second round
     degs = [length + (r % 3) for r in range(n_long)] + [0, 1, 5]
-    rowptr, col = both_ways(degs, max(length + 3, 600), n_long)
+    rowptr, col = both_ways(degs, max(length + 3, 600, n_long + 3), n_long)
     assert len(col) > 16_384
     run_case(gt, rowptr, col, 2, 32, "bf16", taus=(CSR_ONLY,), seed=n_long)
     # fp32 where the rows hold 28 edges and more: a row of one edge has dS = dP - D = 0, and what is left is the
@@ -57,6 +60,33 @@ def test_long_row_lists(gt, n_long, length):
     # in all rows but one
     if n_long in (65, 130):
         run_case(gt, rowptr, col, 1, 64, "f32", taus=(CSR_ONLY,), seed=n_long)
+
+
+@pytest.mark.parametrize("dtype,H,d", [("f32", 1, 64), ("f32", 8, 64), ("bf16", 1, 32), ("bf16", 8, 32),
+                                       ("bf16", 8, 64)])
+def test_bias_row_and_column_lengths(gt, dtype, H, d):
+    # the positions' chunks and the quads at every row length; the positions read from the plan, then taken from the
+    # list position
+    rowptr, col = both_ways(DEGREES, 520, H + d)
+    run_bias_case(gt, rowptr, col, H, d, dtype, seed=12)
+    rp, cl = dev_csr(rowptr, col)
+    arrays = [dev_feat(x, dtype) for x in feats(len(rowptr) - 1, H, d, dtype, 13)]
+    B = torch.from_numpy(np.random.default_rng(4).normal(size=(len(col), H)).astype(np.float32)).cuda()
+    outs = []
+    for positions in (True, False):
+        plan = gt.build_tiles(rp, cl, 128, CSR_ONLY, edge_positions=positions)
+        O, L = gt.sparse_attn_fwd_bias(plan, *arrays[:3], B)
+        outs.append((O, L, *gt.sparse_attn_bwd_bias(plan, gt.edge_map(plan), *arrays[:3], B, arrays[3], L)))
+    torch.cuda.synchronize()
+    for name, a, b in zip(("O", "LSE", "dQ", "dK", "dV", "dB"), *outs):
+        assert torch.equal(a, b), name
+
+
+@pytest.mark.parametrize("dtype,H,d", [("bf16", 2, 32), ("f32", 1, 64)])
+def test_bias_on_many_long_rows(gt, dtype, H, d):
+    # 65 long rows and columns: their runs are planned on the device
+    rowptr, col = both_ways([260 + (r % 3) for r in range(65)] + [0, 2, 5], 600, 65)
+    run_bias_case(gt, rowptr, col, H, d, dtype, seed=14)
 
 
 @pytest.mark.parametrize("H,d", [(1, 32), (8, 64)])

@@ -7,7 +7,6 @@
 
 namespace gt {
 
-
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
@@ -33,8 +32,6 @@ struct EdgeCfg {
     static constexpr int RUN = sizeof(T) == 4 ? 4 : F;  // consecutive features of a lane
     static constexpr int STR = L * RUN;                 // features between a lane's runs
     static_assert(D % F == 0 && F % RUN == 0 && G <= kWave && kWave % G == 0, "unsupported (d, H)");
-    // The head's feature held as value i of lane `part`.
-    __device__ __forceinline__ static int feat(int part, int i) { return (i / RUN) * STR + part * RUN + i % RUN; }
 };
 
 // F features of one row slice, stored packed as loaded: a run of 16 (bf16), or

@@ -1345,10 +1345,6 @@ gt_status run_probe(const gt_tiles* p, const void* A, const void* B, uint32_t* s
 
 // ---------------------------------------------------------------- launchers
 
-struct FwdWs {
-    TilePartials tp;
-};
-
 template <typename T, int D, int H, bool kBias>
 gt_status run_fwd_t(const gt_tiles* p, const void* Q, const void* K, const void* V, float scale, void* O, float* LSE,
                     void* ws_ptr, EdgeBias eb, hipStream_t s) {

@@ -30,7 +30,6 @@ constexpr float kNegInf = -__builtin_huge_valf();
 // Row (M index) of accumulator element i held by lane l: 8*(i/4) + 4*(l/32) + i%4.
 __device__ __forceinline__ int crow(int i, int lane) { return 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3); }
 
-
 __device__ __forceinline__ f32x16_t zero16() {
     f32x16_t z;
 #pragma unroll

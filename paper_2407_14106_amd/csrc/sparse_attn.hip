@@ -656,18 +656,48 @@ struct Work {
     __device__ __forceinline__ bool own() const { return run < 0 && deg >= 0; }
 };
 
-// The first runs of more than kPlanFree long rows, in one workgroup.
+// The first runs of more than kPlanFree long rows: in one workgroup, which takes
+// 2.2 us for every 1,024 rows, up to kPlanOne rows; beyond, the edges' total, the
+// rows' runs and their scan take a launch or two each, 20 us in all (20,000 rows
+// 45 us in one workgroup, 200,000 rows 430).
 constexpr int kPlanThr = 1024;
+constexpr int64_t kPlanOne = 8192;
+constexpr int kPlanSums = 64;
+
+__device__ __forceinline__ int64_t long_length(const LongRows& lr, int64_t r) {
+    if (r >= lr.n) return 0;
+    const int64_t i = lr.list[r];
+    return lr.ptr[i + 1] - lr.ptr[i];
+}
+
+__global__ __launch_bounds__(kThreads) void k_long_total(LongRows lr, int64_t* __restrict__ sums) {
+    __shared__ int64_t s_w[kThreads / kWave];
+    const int t = threadIdx.x;
+    int64_t sum = 0;
+    for (int64_t r = blockIdx.x * int64_t(kThreads) + t; r < lr.n; r += int64_t(kPlanSums) * kThreads)
+        sum += long_length(lr, r);
+    sum = wave_sum(sum);
+    if (t % kWave == 0) s_w[t / kWave] = sum;
+    __syncthreads();
+    if (t > 0) return;
+    for (int k = 1; k < kThreads / kWave; ++k) sum += s_w[k];
+    sums[blockIdx.x] = sum;
+}
+
+__global__ __launch_bounds__(kThreads) void k_long_counts(LongRows lr, const int64_t* __restrict__ sums,
+                                                          int32_t* __restrict__ counts, int64_t* __restrict__ off) {
+    static_assert(kPlanSums == kWave, "one sum a lane");
+    const int len = run_length(wave_sum(sums[lane_id()]), lr.spread);
+    const int64_t r = blockIdx.x * int64_t(kThreads) + threadIdx.x;
+    if (r < lr.n) counts[r] = int32_t(cdiv(long_length(lr, r), len));
+    if (r == 0) off[lr.n + 1] = len;
+}
+
 __global__ __launch_bounds__(kPlanThr) void k_long_plan(LongRows lr, int64_t* __restrict__ off) {
     __shared__ int64_t s_w[kPlanThr / kWave];
     const int t = threadIdx.x, w = t / kWave, lane = lane_id();
-    auto length = [&](int64_t r) -> int64_t {
-        if (r >= lr.n) return 0;
-        const int64_t i = lr.list[r];
-        return lr.ptr[i + 1] - lr.ptr[i];
-    };
     int64_t sum = 0;
-    for (int64_t r = t; r < lr.n; r += kPlanThr) sum += length(r);
+    for (int64_t r = t; r < lr.n; r += kPlanThr) sum += long_length(lr, r);
     sum = wave_sum(sum);
     if (lane == 0) s_w[w] = sum;
     __syncthreads();
@@ -676,7 +706,7 @@ __global__ __launch_bounds__(kPlanThr) void k_long_plan(LongRows lr, int64_t* __
     const int len = run_length(total, lr.spread);
     int64_t base = 0;
     for (int64_t r0 = 0; r0 < lr.n; r0 += kPlanThr) {
-        const int64_t cnt = cdiv(length(r0 + t), len);
+        const int64_t cnt = cdiv(long_length(lr, r0 + t), len);
         int64_t incl = cnt;
 #pragma unroll
         for (int o = 1; o < kWave; o <<= 1) {
@@ -709,7 +739,10 @@ constexpr int64_t col_run_floats(int H, int D) { return 2 * int64_t(H) * D; }
 
 constexpr int64_t kFoldBlocks = 4096;
 struct LongPlan {
-    int64_t* off = nullptr;  // [n_long + 2] where k_long_plan runs
+    int64_t* off = nullptr;  // [n_long + 2] where the runs are planned before
+    int64_t* sums = nullptr; // [kPlanSums], counts [n_long] and a scan's scratch: over kPlanOne rows
+    int32_t* counts = nullptr;
+    ScanTmp scan;
     float* part = nullptr;   // [max_runs, floats per run]
     int64_t max_runs = 0;
     int fold = 1;            // parts a row's runs are folded into before the merge (1: not folded)
@@ -727,6 +760,11 @@ inline LongPlan long_plan_take(Ws& ws, int64_t n_long, int64_t nnz, int64_t spre
     // them first (more rows: fewer each, none from 2,048 rows on)
     if (more > 512) lp.fold = int(parts < 1 ? 1 : parts > 64 ? 64 : parts);
     if (n_long > kPlanFree) lp.off = ws.take<int64_t>(size_t(n_long + 2));
+    if (n_long > kPlanOne) {
+        lp.sums = ws.take<int64_t>(kPlanSums);
+        lp.counts = ws.take<int32_t>(size_t(n_long));
+        lp.scan.block_sums = ws.take<int64_t>(size_t(scan_tmp_elems(n_long)));
+    }
     lp.part = ws.take<float>(size_t(lp.max_runs * per_run));
     return lp;
 }
@@ -739,11 +777,18 @@ gt_status long_rows(const int32_t* list, int64_t n_long, const int64_t* ptr, int
     lr.n = n_long;
     lr.ptr = ptr;
     lr.spread = spread;
-    if (lp.off) {
+    if (n_long > kPlanOne) {
+        k_long_total<<<kPlanSums, kThreads, 0, s>>>(lr, lp.sums);
+        GT_LAUNCH_CHECK("long_total");
+        k_long_counts<<<unsigned(cdiv(n_long, kThreads)), kThreads, 0, s>>>(lr, lp.sums, lp.counts, lp.off);
+        GT_LAUNCH_CHECK("long_counts");
+        const gt_status st = exclusive_scan_i32(lp.counts, n_long, lp.off, lp.scan, s);
+        if (st != GT_OK) return st;
+    } else if (lp.off) {
         k_long_plan<<<1, kPlanThr, 0, s>>>(lr, lp.off);
         GT_LAUNCH_CHECK("long_plan");
-        lr.off = lp.off;
     }
+    lr.off = lp.off;
     return GT_OK;
 }
 

@@ -62,6 +62,29 @@ def test_long_row_lists(gt, n_long, length):
         run_case(gt, rowptr, col, 1, 64, "f32", taus=(CSR_ONLY,), seed=n_long)
 
 
+@pytest.mark.parametrize("n_long", [8192, 8193])
+def test_long_row_lists_planned_by_many_workgroups(gt, n_long):
+    # rows of 257 and 258 partners among 300 nodes, which attend to themselves: every output is the partners' mean, as
+    # every key is the same (weights of 2^-8 relative error in bf16, 300 values of size 1)
+    rng = np.random.default_rng(n_long)
+    n = n_long + 300
+    deg = np.concatenate([257 + np.arange(n_long) % 2, np.ones(300, np.int64)])
+    rowptr = np.concatenate([[0], np.cumsum(deg)])
+    first = rng.integers(0, 300 - 258, size=n_long)
+    col = np.concatenate([(n_long + first[:, None] + np.arange(258))[np.arange(258) < deg[:n_long, None]],
+                          n_long + np.arange(300)])
+    q, k, v, _ = feats(n, 1, 32, "bf16", 3)
+    k[:] = k[:1]
+    plan = gt.build_tiles(*dev_csr(rowptr, col), 128, CSR_ONLY)
+    O, L = gt.sparse_attn_fwd(plan, *(dev_feat(x, "bf16") for x in (q, k, v)), 0.25)
+    torch.cuda.synchronize()
+    sums = np.concatenate([np.zeros((1, 1, 32)), np.cumsum(np.asarray(v[n_long:], np.float64), axis=0)])
+    a = np.concatenate([first, np.arange(300)])
+    assert_close(host(O), (sums[a + deg] - sums[a]) / deg[:, None, None], "bf16", "O")
+    s = 0.25 * np.einsum("nhc,hc->nh", np.asarray(q, np.float64), np.asarray(k[0], np.float64))
+    assert_close(L.cpu().numpy(), s + np.log(deg)[:, None], "bf16", "LSE")
+
+
 @pytest.mark.parametrize("dtype,H,d", [("f32", 1, 64), ("f32", 8, 64), ("bf16", 1, 32), ("bf16", 8, 32),
                                        ("bf16", 8, 64)])
 def test_bias_row_and_column_lengths(gt, dtype, H, d):

@@ -26,8 +26,9 @@ constexpr float kNegInf = -__builtin_huge_valf();
 
 // The passes are bound by the rate of the row gathers through L2 and L1: over
 // 1M nodes of 8 x 32 bf16 features and 31 edges a node of a clustered graph the
-// gathers alone take 1.51 ms, with each node's own row read and a result row
-// written 1.76 ms (100K nodes of 8 x 64, 17 edges: 0.150 and 0.206).  The forward takes two
+// gathers alone take 1.58 ms (gt_gather_probe), and in a copy of that probe with
+// each node's own row read and a result row written 1.76 ms (100K nodes of 8 x 64,
+// 17 edges: 0.150 and 0.206).  The forward takes two
 // edges at a time with nothing in flight meanwhile, at 6 wavefronts per SIMD:
 // 1.88 ms (0.225), no slower than with rows in flight at 4 (1.87; with pairs in
 // flight 2.0, the registers spill).  The row pass holds 4 wavefronts, so it keeps
@@ -526,16 +527,22 @@ __device__ __forceinline__ int64_t row_block(unsigned b, unsigned run) {
 // ms.  128 molecules and a token row of 3,137 edges: 155 -> 60 us, with one launch
 // and a merge per pass instead of six.)
 // A run holds kMinRun edges, more where the long rows' edges would give more
-// runs than run_spread: lane groups of 4 wavefronts on each of the chip's 1,024
-// SIMDs.  But no more than kMaxRun, the longest short row: a run's sums are
-// serial fp32 chains.  Past kMaxRuns runs (268M edges of long rows) the
-// partial states, up to 8 KB each, would outgrow the features, so runs lengthen.
+// runs than run_spread: a wavefront of them for each of the chip's 1,024 SIMDs,
+// and 4,096 at least.  (1M power-law nodes, 4.6M edges in 4,000 long rows, forward
+// / backward, us: 1 x 32 in 4,096 runs 590 / 1425, in 32,768 421 / 997, in 131,072
+// 414 / 1027; 4 x 32 in 4,096 885 / 2095, at most 256 edges each 893 / 2113, in
+// 32,768 897 / 2128.)  But no more than kMaxRun, the longest short row: a run's sums are
+// serial fp32 chains.  (Moving the sums of longer runs to their partial state
+// every 256 edges instead costs the short rows registers: 1M x 8 x 32 forward 1.87 ->
+// 1.92 ms, and 1.90 where the runs' walk is apart from theirs.)  Past
+// kMaxRuns runs (268M edges of long rows) the partial states, up to 8 KB each, would
+// outgrow the features, so runs lengthen.
 constexpr int kMinRun = 32;
 constexpr int kMaxRun = GT_LONG_ROW;
 constexpr int64_t kMaxRuns = int64_t(1) << 20;
 constexpr int64_t run_spread(int H, int D) { return 1024 * int64_t(H * D >= 256 ? 4 : 1024 / (H * D)); }
 // Up to one wavefront of long rows, every lane group finds its run from the
-// rows' lengths itself; beyond, k_long_plan lists the rows' first runs before.
+// rows' lengths itself; beyond, the rows' first runs are listed before.
 constexpr int64_t kPlanFree = kWave;
 
 struct LongRows {

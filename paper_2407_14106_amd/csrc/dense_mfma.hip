@@ -989,12 +989,12 @@ __global__ __launch_bounds__(kMergeThreads) void k_tiles_merge_sum(int64_t n, in
 // tiles are launched with NB = 1 (kTileNB): a chunk holds only a few tiles, so
 // the kernels are latency-bound and more resident wavefronts pay more than
 // the operand reuse.  Wavefronts per SIMD: forward 4 at d = 32, 3 at d = 64; dQ
-// and dK/dV 3 at d = 32, 2 at d = 64 (dK/dV at d = 32, T = 64 without a bias 2: its
-// registers spill at 3).  Measured on 65,536 nodes, 8 heads, tiles from 5% on (us,
-// backward of the layer): d = 32 at 2 wavefronts 406, at 3 387; with a bias dK/dV
-// at 1 wavefront in a SIMD 4120 (d = 64) and 3870 (d = 32), at 2 and 3 3650 and 3320.
-// A stage's cells of the bias are addressed from a uniform base, with one offset a
-// lane: an address a cell is what took the registers (256 and 186 AGPRs).
+// and dK/dV 3 at d = 32, 2 at d = 64.  Measured on 65,536 nodes, 8 heads, tiles from
+// 5% on (us, backward of the layer): d = 32 at 2 wavefronts 406, at 3 371; with a
+// bias dK/dV at 1 wavefront in a SIMD 4120 (d = 64) and 3870 (d = 32), at 2 and 3
+// 3650 and 3320.  A stage's cells of the bias are addressed from a uniform base,
+// with one offset a lane: an address a cell is what took the registers (256 and 186
+// AGPRs).
 template <int D, int T, int NB, bool kBias = false>
 __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(D >= 64 ? 3 : 4))) void k_tiles_fwd(
     int64_t n, int H, const int64_t* __restrict__ tile_rowptr,
@@ -1362,7 +1362,7 @@ __device__ __forceinline__ uint64_t bit_transpose_64x32(uint32_t w, int lane) {
 // The stage's masks are transposed so that each lane holds, for its key, one
 // 64-bit word over the stage's 64 queries.
 template <int D, int T, int NB, bool kBias = false>
-__global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB > 1 ? 1 : D < 64 && (kBias || T == 128) ? 3 : 2))) void k_tiles_dkdv(
+__global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB > 1 ? 1 : D < 64 ? 3 : 2))) void k_tiles_dkdv(
     int64_t n, int H, int64_t n_row_tiles,
                                                   const int64_t* __restrict__ tileT_ptr,
                                                   const int32_t* __restrict__ tileT_idx,
@@ -1454,17 +1454,9 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB >
 #pragma unroll
                 for (int b = 0; b < NB; ++b) dp[b] = mma(g8, vf[b].v[c], dp[b]);
             }
-            float Lr[16], Dr[16];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int r = 32 * qb + 8 * j + 4 * (lane >> 5);
-                const float4 lv = *reinterpret_cast<const float4*>(&cL[r]);
-                const float4 d4 = *reinterpret_cast<const float4*>(&cD[r]);
-                Lr[4 * j] = lv.x, Lr[4 * j + 1] = lv.y, Lr[4 * j + 2] = lv.z, Lr[4 * j + 3] = lv.w;
-                Dr[4 * j] = d4.x, Dr[4 * j + 1] = d4.y, Dr[4 * j + 2] = d4.z, Dr[4 * j + 3] = d4.w;
-            }
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
+                float4 lv, d4;  // read where used: all 32 held spilled 12 registers at d = 32 (385 us)
                 const uint32_t w = uint32_t(mt[b] >> (32 * qb));
                 int64_t x0 = 0;
                 const int xl = 4 * (lane >> 5) * T + (lane & 31);
@@ -1472,16 +1464,24 @@ __global__ __launch_bounds__(T * 2 / NB) __attribute__((amdgpu_waves_per_eu(NB >
                     x0 = TileBias::at(tk, H, h, T, kStage * int(g % NSG) + 32 * qb, 32 * (NB * wave + b));
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
+                    const int r4 = 32 * qb + 8 * (i >> 2) + 4 * (lane >> 5);
+                    if (i % 4 == 0) {
+                        lv = *reinterpret_cast<const float4*>(&cL[r4]);
+                        d4 = *reinterpret_cast<const float4*>(&cD[r4]);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    const float Li = i % 4 == 0 ? lv.x : i % 4 == 1 ? lv.y : i % 4 == 2 ? lv.z : lv.w;
+                    const float Di = i % 4 == 0 ? d4.x : i % 4 == 1 ? d4.y : i % 4 == 2 ? d4.z : d4.w;
                     const bool on = (w >> crow(i, lane)) & 1u;
                     float p = 0.f;
                     if constexpr (kBias) {
                         const int64_t x = x0 + (8 * (i >> 2) + (i & 3)) * T;
-                        p = ex2(fmaf(s[b][i], sl2, (tb.b + x)[xl] * kLog2e - Lr[i]));  // 0 off the edges (bias -inf)
-                        s[b][i] = p * (dp[b][i] - Dr[i]);
+                        p = ex2(fmaf(s[b][i], sl2, (tb.b + x)[xl] * kLog2e - Li));  // 0 off the edges (bias -inf)
+                        s[b][i] = p * (dp[b][i] - Di);
                         (tb.db + x)[xl] = s[b][i];  // every cell (0 off the edges), so no branch is needed
                     } else {
-                        p = on ? ex2(fmaf(s[b][i], sl2, -Lr[i])) : 0.f;
-                        s[b][i] = p * (dp[b][i] - Dr[i]);
+                        p = on ? ex2(fmaf(s[b][i], sl2, -Li)) : 0.f;
+                        s[b][i] = p * (dp[b][i] - Di);
                     }
                     dp[b][i] = p;
                 }

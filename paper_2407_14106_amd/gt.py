@@ -399,9 +399,9 @@ def tau_to_ppm(tau: float) -> int:
 
 
 # Default density threshold: the break-even density measured on MI355X for bf16
-# features (a 128 x 128 tile, forward and backward, costs about what 6.6% (d=32)
-# to 12% (d=64, partial sums merged by the edge kernels included) of its pairs
-# cost as edges), so a tile the plan makes dense is not slower than its edges.
+# features (a 128 x 128 tile, forward and backward, costs about what 6.3% (d=32)
+# to 12.6% (d=64, partial sums merged by the edge kernels included) of its pairs
+# cost as edges), so a tile the plan makes dense is hardly slower than its edges.
 # The paper's lower thresholds remain available through tau_ppm.
 BREAK_EVEN_TAU_PPM = 120_000
 

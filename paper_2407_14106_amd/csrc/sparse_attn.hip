@@ -540,7 +540,8 @@ __device__ __forceinline__ int64_t row_block(unsigned b, unsigned run) {
 constexpr int kMinRun = 32;
 constexpr int kMaxRun = GT_LONG_ROW;
 constexpr int64_t kMaxRuns = int64_t(1) << 20;
-constexpr int64_t run_spread(int H, int D) { return 1024 * int64_t(H * D >= 256 ? 4 : 1024 / (H * D)); }
+constexpr int run_spread_bits(int H, int D) { return H * D >= 256 ? 12 : H * D >= 128 ? 13 : H * D >= 64 ? 14 : 15; }
+constexpr int64_t run_spread(int H, int D) { return int64_t(1) << run_spread_bits(H, D); }
 // Up to one wavefront of long rows, every lane group finds its run from the
 // rows' lengths itself; beyond, the rows' first runs are listed before.
 constexpr int64_t kPlanFree = kWave;
@@ -550,12 +551,12 @@ struct LongRows {
     int64_t n = 0;
     const int64_t* ptr = nullptr;
     const int64_t* off = nullptr;  // [n + 2]: first run of each row, their number, the run length; null: none listed
-    int64_t spread = 1;            // run_spread of the features
+    int spread_bits = 0;           // run_spread_bits of the features
 };
 
 // Edges of a run, `edges` being those of all long rows.
-__host__ __device__ __forceinline__ int run_length(int64_t edges, int64_t spread) {
-    int64_t c = cdiv(edges, spread);
+__device__ __forceinline__ int run_length(int64_t edges, int spread_bits) {
+    int64_t c = (edges + (int64_t(1) << spread_bits) - 1) >> spread_bits;
     if (c > kMaxRun) c = cdiv(edges, kMaxRuns) > kMaxRun ? cdiv(edges, kMaxRuns) : kMaxRun;
     return c > kMinRun ? int((c + kMinRun - 1) / kMinRun * kMinRun) : kMinRun;
 }
@@ -576,7 +577,7 @@ struct LaneRuns {
             const int64_t i = lr.list[lane];
             deg = lr.ptr[i + 1] - lr.ptr[i];
         }
-        len = run_length(wave_sum(deg), lr.spread);
+        len = run_length(wave_sum(deg), lr.spread_bits);
         cnt = int(cdiv(deg, len));
         incl = cnt;
 #pragma unroll
@@ -694,7 +695,7 @@ __global__ __launch_bounds__(kThreads) void k_long_total(LongRows lr, int64_t* _
 __global__ __launch_bounds__(kThreads) void k_long_counts(LongRows lr, const int64_t* __restrict__ sums,
                                                           int32_t* __restrict__ counts, int64_t* __restrict__ off) {
     static_assert(kPlanSums == kWave, "one sum a lane");
-    const int len = run_length(wave_sum(sums[lane_id()]), lr.spread);
+    const int len = run_length(wave_sum(sums[lane_id()]), lr.spread_bits);
     const int64_t r = blockIdx.x * int64_t(kThreads) + threadIdx.x;
     if (r < lr.n) counts[r] = int32_t(cdiv(long_length(lr, r), len));
     if (r == 0) off[lr.n + 1] = len;
@@ -710,7 +711,7 @@ __global__ __launch_bounds__(kPlanThr) void k_long_plan(LongRows lr, int64_t* __
     __syncthreads();
     int64_t total = 0;
     for (int k = 0; k < kPlanThr / kWave; ++k) total += s_w[k];
-    const int len = run_length(total, lr.spread);
+    const int len = run_length(total, lr.spread_bits);
     int64_t base = 0;
     for (int64_t r0 = 0; r0 < lr.n; r0 += kPlanThr) {
         const int64_t cnt = cdiv(long_length(lr, r0 + t), len);
@@ -776,14 +777,14 @@ inline LongPlan long_plan_take(Ws& ws, int64_t n_long, int64_t nnz, int64_t spre
     return lp;
 }
 
-gt_status long_rows(const int32_t* list, int64_t n_long, const int64_t* ptr, int64_t spread, const LongPlan& lp,
+gt_status long_rows(const int32_t* list, int64_t n_long, const int64_t* ptr, int spread_bits, const LongPlan& lp,
                     LongRows& lr, hipStream_t s) {
     lr = LongRows{};
     if (n_long <= 0) return GT_OK;
     lr.list = list;
     lr.n = n_long;
     lr.ptr = ptr;
-    lr.spread = spread;
+    lr.spread_bits = spread_bits;
     if (n_long > kPlanOne) {
         k_long_total<<<kPlanSums, kThreads, 0, s>>>(lr, lp.sums);
         GT_LAUNCH_CHECK("long_total");
@@ -1417,7 +1418,7 @@ gt_status run_fwd_t(const gt_tiles* p, const void* Q, const void* K, const void*
         tp = TilePartials{};
     }
     LongRows lr;
-    if ((st = long_rows(p->long_rows, p->n_long_rows, p->sp_rowptr, run_spread(H, D), lp, lr, s)) != GT_OK) return st;
+    if ((st = long_rows(p->long_rows, p->n_long_rows, p->sp_rowptr, run_spread_bits(H, D), lp, lr, s)) != GT_OK) return st;
     const RowGrid rg = row_grid(n, C::NPW * (kThreads / kWave));
     const unsigned runs = lp.blocks(C::NPW * (kThreads / kWave));
     k_fwd_rows<T, D, H, kBias><<<runs + rg.grid, kThreads, 0, s>>>(
@@ -1462,7 +1463,7 @@ gt_status run_bwd_rows_t(const gt_tiles* p, const void* Q, const void* K, const 
         if ((st = tile_bwd_dq<T, D, H>(p, q, k, v, g, LSE, sl2, tb.dq, eb.tile, s)) != GT_OK) return st;
     }
     LongRows lr;
-    if ((st = long_rows(p->long_rows, p->n_long_rows, p->sp_rowptr, run_spread(H, D), lp, lr, s)) != GT_OK) return st;
+    if ((st = long_rows(p->long_rows, p->n_long_rows, p->sp_rowptr, run_spread_bits(H, D), lp, lr, s)) != GT_OK) return st;
     const RowGrid rg = row_grid(n, C::NPW * (kThreads / kWave));
     const unsigned runs = lp.blocks(C::NPW * (kThreads / kWave));
     k_bwd_rows<T, D, H, kBias><<<runs + rg.grid, kThreads, 0, s>>>(
@@ -1515,7 +1516,7 @@ gt_status run_bwd_cols_t(const gt_tiles* p, const void* Q, const void* K, const 
         GT_LAUNCH_CHECK("sparse_bwd_pack_stats");
     }
     LongRows lr;
-    if ((st = long_rows(p->long_cols, p->n_long_cols, p->sp_colptr, run_spread(H, D), lp, lr, s)) != GT_OK) return st;
+    if ((st = long_rows(p->long_cols, p->n_long_cols, p->sp_colptr, run_spread_bits(H, D), lp, lr, s)) != GT_OK) return st;
     const RowGrid rg = row_grid(n, C::NPW * (kThreads / kWave));
     const unsigned runs = lp.blocks(C::NPW * (kThreads / kWave));
     k_bwd_cols<T, D, H, kBias><<<runs + rg.grid, kThreads, 0, s>>>(
